@@ -89,16 +89,17 @@ def counter_figures(path: str = COUNTERS_JSON):
     return d if d.get("source_hash") == kernel_source_hash() else None
 
 
-# the library's defaults (include/tpmvs.h): chunk length, first-chunk cap when
-# the planet map runs alongside, work items per tile and chunk
+# the library's defaults (include/tpmvs.h): chunk length, first-chunk cap of a
+# run of several chunks, work items per tile and chunk
 DEFAULT_CHUNK_STEPS, FIRST_CHUNK_STEPS, DEFAULT_SUB_CHUNKS = 8192, 1024, 64
 
 
 def default_chunks(nsteps: int) -> list:
     """Chunk lengths of an on-the-fly run of nsteps with the default options."""
     out, done = [], 0
+    first = FIRST_CHUNK_STEPS if nsteps > DEFAULT_CHUNK_STEPS else DEFAULT_CHUNK_STEPS
     while done < nsteps:
-        k = min(FIRST_CHUNK_STEPS if not out else DEFAULT_CHUNK_STEPS, nsteps - done)
+        k = min(first if not out else DEFAULT_CHUNK_STEPS, nsteps - done)
         out.append(k)
         done += k
     return out

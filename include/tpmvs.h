@@ -64,14 +64,16 @@ enum {
 typedef struct {
   int32_t kepler_iters;   /* fixed Newton iterations per drift (sec. 2.2: five); default 5 */
   int32_t chunk_steps;    /* steps per particle launch ("planetary chunk", sec. 2.2); 0 = 8192.
-                             When the planet map runs alongside the particles (no table
-                             supplied), the first launch of each integrate call covers at
-                             most 1,024 steps: the particles wait for its whole planet chunk */
+                             The planet map runs inside the particle launches (no table or
+                             history supplied); an integrate call of more than one chunk, or
+                             with the hand-off on, then starts with a launch of at most
+                             1,024 steps                                                     */
   int32_t resync_chunks;  /* chunks between compactions ("resync interval", sec. 2.2); 0 = 1 */
   int32_t block_threads;  /* particle-kernel workgroup size (64..256, multiple of 64); 0 = 64 */
   int32_t sub_chunks;     /* work items per tile in a full chunk (dynamic load balance); a
                              shorter chunk gets proportionally fewer items of the same
-                             length; 0 = 64 */
+                             length; 0 = 64, or one where every tile and the planet map
+                             have a SIMD of their own */
   int32_t waves_per_simd; /* particle wavefronts launched per SIMD (upper bound); 0 = as many
                              as the working set's tiles fill on every SIMD alike, 1..4,
                              chosen per launch */
@@ -390,9 +392,7 @@ int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_t* planet_o
  * mutual Hill radius at step t, -2 a planet orbit found unbound) and the
  * work-queue error flag (0 = none).  Work is enqueued on the caller's stream
  * (NULL = null stream) without synchronising; options as in tpm_create (NULL =
- * defaults; time_kernels is ignored).  The planet map and the particles run one
- * after the other on that one stream, so a run takes about the sum of the two
- * stages rather than the larger.  Every call on one GPU uses that GPU's array,
+ * defaults; time_kernels is ignored).  Every call on one GPU uses that GPU's array,
  * which keeps the last call's contents (each call initialises what it uses):
  * calls that overlap on one GPU, from any stream or thread, race. */
 int tpm_integrate_static(const tpm_options* opt, double mu0, int32_t np, const double* mu,

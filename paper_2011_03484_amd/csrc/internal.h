@@ -101,6 +101,32 @@ struct EphConst {
   double hill2[MAX_NP + 1][MAX_NP + 1];
 };
 
+// Planet rows written by the particle launch that uses them (particle_queue's
+// first work item; planet_rows): the launch's chunk, and the chunks after it
+// that the map may run ahead into.
+constexpr int STREAM_CHUNKS = 8;
+struct RowStream {
+  double* rj;                  // Jacobi planet state [np][3], at step `done`
+  double* vj;
+  double* ring;                // [nslots][slot_rows][3 np + 3]; chunk j in slot (slot0 + j) % nslots
+  double* vring;               // planet velocities per row [nslots][vslot_rows][np][3], or null
+  double* vside;               // planet velocities at chunk ends [nslots][2][np][3], or null
+  int64_t slot_rows, vslot_rows, slot0, nslots;
+  double dt;
+  int64_t step0;               // global step of the launch's chunk
+  int64_t begin;               // the count *done where the launch's chunk starts
+  int64_t* done;               // steps whose rows are published (monotonic)
+  int64_t* flag;               // first planet event
+  unsigned long long* ticks;   // time spent in the map, in 10 ns (accumulated)
+  // the work queue: its item counter, the counter at launch, and how far above
+  // that it stands once the map's wavefront is the last one at work
+  const unsigned long long* ctr;
+  unsigned long long ctr_base, ctr_alone;
+  int32_t* error;              // set on an over-long wait
+  int len[STREAM_CHUNKS];      // steps of the launch's chunk and of those after it (0: none)
+  int on;
+};
+
 // Work-queue bookkeeping of one particle launch (see particle_queue).
 struct QueueLaunch {
   unsigned long long* ctr;     // device item counter
@@ -113,7 +139,35 @@ struct QueueLaunch {
   int32_t* error;              // device flag set on an over-long wait
   bool deep = false;           // planet rows fetched three steps ahead, not one (for
                                // launches of one wavefront per SIMD)
+  bool spread = false;         // at most one wavefront per SIMD (see lds())
+  const RowStream* stream = nullptr;   // the launch writes its own planet rows
+  const EphConst* eph = nullptr;       // with the planet map's constants
+
+  // One wavefront more for the planet map.
+  int blocks() const {
+    const int wpb = block / 64, w = workers + (stream ? 1 : 0);
+    return (w + wpb - 1) / wpb;
+  }
+  // What the launch adds to the item counter: every item, and one last grab
+  // per wavefront (a failing one, or the planet map's).
+  unsigned long long grabs(int ntiles) const {
+    return (unsigned long long)ntiles * nsub + (unsigned long long)blocks() * (block / 64);
+  }
+  // LDS a workgroup asks for and does not use: a quarter of a compute unit's
+  // keeps one-wavefront workgroups to four a unit, one per SIMD.
+  unsigned lds() const { return spread && block == 64 ? 40u * 1024 - 512 : 0; }
 };
+
+// A launch with its own planet map whose tiles and map fit one wavefront per
+// SIMD takes each tile through the whole chunk as one item, at most one
+// wavefront to a SIMD: the wavefronts follow the map's rows with their
+// particles in registers, and none shares a SIMD with the map, which would
+// take most of its issue slots.
+inline void lone_tiles(QueueLaunch& QL, int ntiles, int ncu) {
+  if (!QL.stream || ntiles + 1 > 4 * ncu || QL.block != 64) return;
+  QL.nsub = 1;
+  QL.spread = true;
+}
 
 // Particle chunk: nsteps steps through rows[0..nsteps] (row 0 = step0) over
 // the first grid_n (>= active count) working-set entries.

@@ -3,10 +3,11 @@
 //  * particle_queue  - one lane per particle; the particle stays in registers
 //    for hundreds of steps (sec. 2.2: a single kernel loops over the planet
 //    chunk so each particle is read and written once per chunk), with the
-//    chunk's (tile, sub-chunk) items handed out dynamically to wavefronts.
+//    chunk's (tile, sub-chunk) items handed out dynamically to wavefronts and
+//    the planet map of the chunk run by one more wavefront of the same launch.
 //    Every lane reads the same planet-table row: broadcast vector loads into
 //    VGPRs, one step ahead of its use.
-//  * ephemeris_chunk - one wavefront; lane b holds Jacobi body b.  Wisdom-Holman
+//  * ephemeris_chunk (and planet_rows, inside particle_queue) - one wavefront; lane b holds Jacobi body b.  Wisdom-Holman
 //    kick-drift-kick of the planets (sec. 2.2, planet integration) writing the
 //    heliocentric positions and the indirect term h0 per step.
 //  * compact_*       - stable partition of the working set so removed particles
@@ -30,19 +31,77 @@ struct ChunkArgs {
   int handoff;   // within rcrit: hand off to the encounter integrator, not removal
 };
 
-// The work-queue kernel's leading arguments as its argument segment lays them
-// out (particle_queue: w, d_nactive, out, ...); see karg_field.
+// Work queue of one launch (see particle_queue).
+struct QueueArgs {
+  unsigned long long* ctr;     // monotonic item counter
+  unsigned long long base;     // counter value at this launch's start
+  uint32_t* progress;          // per tile: sub-chunks completed (monotonic over launches)
+  uint32_t epoch;              // progress value of every tile at this launch's start
+  int ntiles, nsub, sub_steps, nsteps;
+  int32_t* error;
+};
+
+// The work-queue kernel's arguments as its argument segment lays them out
+// (particle_queue); see karg_field.
 struct QueueArgsHead {
   Work w;
   const int32_t* n;
   Out out;
+  RowStream R;
+};
+template <int NP>
+struct QueueKernelArgs {
+  QueueArgsHead head;
+  const double* rows;
+  ChunkArgs<NP> A;
+  QueueArgs Q;
+  EphConst E;
 };
 TPM_DEV Work karg_work(KargPtr p) { return karg_field<Work>(p, offsetof(QueueArgsHead, w)); }
 TPM_DEV Out karg_out(KargPtr p) { return karg_field<Out>(p, offsetof(QueueArgsHead, out)); }
+template <typename T>
+TPM_DEV T karg_stream(KargPtr p, size_t off) {
+  return karg_field<T>(p, offsetof(QueueArgsHead, R) + off);
+}
+
+constexpr uint32_t SPIN_LIMIT = 1u << 22;   // about 4 s of polling
+
+TPM_DEV unsigned long long wave_uniform(unsigned long long v) {
+  uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+  uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// Steps of the launch's chunk whose closing rows are published, once that is
+// more than s (`have` already known to be): the planet map of the same launch
+// writes the rows as the particles follow (planet_rows).  The whole wavefront
+// polls the count with relaxed loads and acquires once when it has moved, so
+// that the rows behind it are read from memory and not from a stale line.
+// A wait ends when the map, which always runs (see particle_queue), publishes
+// its next block; one in which it publishes nothing for the spin limit flags
+// an error and returns s.
+TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
+  const int64_t* cnt = karg_stream<const int64_t*>(ka, offsetof(RowStream, done));
+  const int64_t begin = karg_stream<int64_t>(ka, offsetof(RowStream, begin));
+  for (uint32_t spins = 0; spins <= SPIN_LIMIT; ++spins) {
+    const int64_t p = (int64_t)wave_uniform((unsigned long long)__hip_atomic_load(
+                          cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) - begin;
+    if (p > s) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      return p < nsteps ? (int)p : nsteps;
+    }
+    __builtin_amdgcn_s_sleep(16);
+  }
+  atomicOr(karg_stream<int32_t*>(ka, offsetof(RowStream, error)), 1);
+  return s;
+}
 
 // Advance particle i of the working set through steps [s_begin, s_end) of a
-// chunk whose rows start at `rows` (row k = step step0 + k; all rows of the
-// chunk are written before the launch).  The step loop is uniform across the
+// chunk whose rows start at `rows` (row k = step step0 + k).  The rows are
+// written before the launch, or (KA with a row stream) by the launch's own
+// planet map as the particles follow: `have` counts the steps whose closing
+// rows are published, and the wavefront waits for more where it runs out
+// (wait_rows).  The step loop is uniform across the
 // wavefront (s_begin, s_end are wave-uniform); removed lanes are masked off
 // and the wavefront leaves early once none is active.  KIT > 0 fixes the
 // Newton count at compile time; DEPTH > 0 fetches each planet row DEPTH
@@ -56,8 +115,8 @@ TPM_DEV Out karg_out(KargPtr p) { return karg_field<Out>(p, offsetof(QueueArgsHe
 // where they are used (the item's start and end, a record), which leaves the
 // step loop's scalar registers to its constants.
 template <int NP, int KIT, int DEPTH, bool UNIV = false, bool KA = false>
-TPM_DEV void advance(Work w, Out out, const double* __restrict__ rows, const ChunkArgs<NP>& A,
-                     int i, bool valid, int s_begin, int s_end, KargPtr ka = nullptr) {
+TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A, int i,
+                     bool valid, int s_begin, int s_end, KargPtr ka, int& have) {
   constexpr int ROW = 3 * NP + 3;
   const int kiters = KIT > 0 ? KIT : A.kiters;
   if (KA) w = karg_work(ka);
@@ -95,6 +154,10 @@ TPM_DEV void advance(Work w, Out out, const double* __restrict__ rows, const Chu
     reason = why;
   };
   double ax, ay, az;
+  if (KA && have <= s_begin) {
+    have = wait_rows(ka, s_begin, A.nsteps);
+    if (have <= s_begin) return;            // the wait gave up (flagged)
+  }
   int hit = accel<NP>(rows + (size_t)s_begin * ROW, A.P, x, y, z, ax, ay, az);
   if (valid) {
     if (hit >= 0) record(ST_ENCOUNTER, A.step0 + s_begin, hit, x, y, z, vx, vy, vz);
@@ -135,50 +198,59 @@ TPM_DEV void advance(Work w, Out out, const double* __restrict__ rows, const Chu
   auto all_removed = [&](int s) {
     return ((s - s_begin) & 7) == 0 && wave_all(reason != ST_ACTIVE);
   };
-  if (DEPTH == 1) {
-    // The row that ends step s is fetched during step s - 1, into the one of
-    // two alternating VGPR buffers that step s - 1 does not use: with few
-    // wavefronts per SIMD nothing else hides that load's latency.
-    const int zero = opaque_zero_vgpr();
-    Row<NP> ra, rb;
-    load_row<NP>(ra, rows + (size_t)(s_begin + 1) * ROW, zero);
-    for (int s = s_begin; s < s_end; s += 2) {
-      if (all_removed(s)) break;
-      load_row<NP>(rb, rows + (size_t)min(s + 2, s_end) * ROW, zero);
-      step(s, ra.v);
-      if (s + 1 >= s_end) break;
-      load_row<NP>(ra, rows + (size_t)min(s + 3, s_end) * ROW, zero);
-      step(s + 1, rb.v);
+  for (int s0 = s_begin;;) {
+    if (KA && have <= s0) {
+      have = wait_rows(ka, s0, A.nsteps);
+      if (have <= s0) break;                // the wait gave up (flagged)
     }
-  } else if (DEPTH == 3) {
-    // Three steps ahead, four buffers in turn: with one wavefront per SIMD
-    // the particles run right behind the planet map, and a row just written
-    // on another die can take longer than a step to arrive.
-    const int zero = opaque_zero_vgpr();
-    Row<NP> ra, rb, rc, rd;
-    load_row<NP>(ra, rows + (size_t)(s_begin + 1) * ROW, zero);
-    load_row<NP>(rb, rows + (size_t)min(s_begin + 2, s_end) * ROW, zero);
-    load_row<NP>(rc, rows + (size_t)min(s_begin + 3, s_end) * ROW, zero);
-    for (int s = s_begin; s < s_end; s += 4) {
-      if (all_removed(s)) break;
-      load_row<NP>(rd, rows + (size_t)min(s + 4, s_end) * ROW, zero);
-      step(s, ra.v);
-      if (s + 1 >= s_end) break;
-      load_row<NP>(ra, rows + (size_t)min(s + 5, s_end) * ROW, zero);
-      step(s + 1, rb.v);
-      if (s + 2 >= s_end) break;
-      load_row<NP>(rb, rows + (size_t)min(s + 6, s_end) * ROW, zero);
-      step(s + 2, rc.v);
-      if (s + 3 >= s_end) break;
-      load_row<NP>(rc, rows + (size_t)min(s + 7, s_end) * ROW, zero);
-      step(s + 3, rd.v);
+    const int lim = KA ? min(s_end, have) : s_end;
+    if (DEPTH == 1) {
+      // The row that ends step s is fetched during step s - 1, into the one of
+      // two alternating VGPR buffers that step s - 1 does not use: with few
+      // wavefronts per SIMD nothing else hides that load's latency.
+      const int zero = opaque_zero_vgpr();
+      Row<NP> ra, rb;
+      load_row<NP>(ra, rows + (size_t)(s0 + 1) * ROW, zero);
+      for (int s = s0; s < lim; s += 2) {
+        if (all_removed(s)) break;
+        load_row<NP>(rb, rows + (size_t)min(s + 2, lim) * ROW, zero);
+        step(s, ra.v);
+        if (s + 1 >= lim) break;
+        load_row<NP>(ra, rows + (size_t)min(s + 3, lim) * ROW, zero);
+        step(s + 1, rb.v);
+      }
+    } else if (DEPTH == 3) {
+      // Three steps ahead, four buffers in turn: with one wavefront per SIMD
+      // the particles run right behind the planet map, and a row just written
+      // on another die can take longer than a step to arrive.
+      const int zero = opaque_zero_vgpr();
+      Row<NP> ra, rb, rc, rd;
+      load_row<NP>(ra, rows + (size_t)(s0 + 1) * ROW, zero);
+      load_row<NP>(rb, rows + (size_t)min(s0 + 2, lim) * ROW, zero);
+      load_row<NP>(rc, rows + (size_t)min(s0 + 3, lim) * ROW, zero);
+      for (int s = s0; s < lim; s += 4) {
+        if (all_removed(s)) break;
+        load_row<NP>(rd, rows + (size_t)min(s + 4, lim) * ROW, zero);
+        step(s, ra.v);
+        if (s + 1 >= lim) break;
+        load_row<NP>(ra, rows + (size_t)min(s + 5, lim) * ROW, zero);
+        step(s + 1, rb.v);
+        if (s + 2 >= lim) break;
+        load_row<NP>(rb, rows + (size_t)min(s + 6, lim) * ROW, zero);
+        step(s + 2, rc.v);
+        if (s + 3 >= lim) break;
+        load_row<NP>(rc, rows + (size_t)min(s + 7, lim) * ROW, zero);
+        step(s + 3, rd.v);
+      }
+    } else {
+      // many wavefronts per SIMD: rows by scalar loads at their use
+      for (int s = s0; s < lim; ++s) {
+        if (all_removed(s)) break;
+        step(s, rows + (size_t)(s + 1) * ROW);
+      }
     }
-  } else {
-    // many wavefronts per SIMD: rows by scalar loads at their use
-    for (int s = s_begin; s < s_end; ++s) {
-      if (all_removed(s)) break;
-      step(s, rows + (size_t)(s + 1) * ROW);
-    }
+    s0 = lim;
+    if (!KA || s0 >= s_end || wave_all(reason != ST_ACTIVE)) break;
   }
   if (reason == ST_ACTIVE) {
     const Work we = KA ? karg_work(ka) : w;
@@ -194,37 +266,45 @@ TPM_DEV void advance(Work w, Out out, const double* __restrict__ rows, const Chu
 // waits for item (s-1, t) through a per-tile progress counter; that item was
 // taken earlier by a running wavefront, so the wait always ends.  A wait
 // longer than the spin limit flags an error and drops the item.
-struct QueueArgs {
-  unsigned long long* ctr;     // monotonic item counter
-  unsigned long long base;     // counter value at this launch's start
-  uint32_t* progress;          // per tile: sub-chunks completed (monotonic over launches)
-  uint32_t epoch;              // progress value of every tile at this launch's start
-  int ntiles, nsub, sub_steps, nsteps;
-  int32_t* error;
-};
-
-constexpr uint32_t SPIN_LIMIT = 1u << 22;   // about 4 s of polling
-
-TPM_DEV unsigned long long wave_uniform(unsigned long long v) {
-  uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-  uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-  return ((unsigned long long)hi << 32) | lo;
-}
+//
+// With a row stream (R.on) the queue's first item is the planet map itself:
+// the wavefront that takes it writes the chunk's planet rows (planet_rows)
+// while the others follow it through them, a block of steps behind.  That
+// wavefront runs by definition and waits for nobody, whichever order the
+// launch's workgroups start in, so every wait for rows ends.  As launches of
+// its own the map had to finish a chunk before the particles could start on
+// it, so a call of one or two chunks took the sum of both: 10,000 steps of
+// 13,313 particles 16.7 ms, now 9.5; 1,000 steps of 16,384 particles on one
+// stream 1.74 ms, now 1.01; 10,000 steps of 200,000 particles 29.2 ms, now 21.8.
 
 // No part of the item loop runs on a subset of the lanes: the grab, the wait
 // and the publish are executed by the whole wavefront (lane 0 alone adds 1 to
 // the counter), so the readfirstlane that makes their results wave-uniform
 // always sees the full wavefront and the loop's branches stay scalar.
+template <int NP>
+TPM_DEV void run_planet_rows(KargPtr ka);
+
 template <int NP, int KIT, bool UNIV, int DEPTH>
-__global__ void __launch_bounds__(256)
-particle_queue(Work w, const int32_t* __restrict__ d_nactive, Out out,
-               const double* __restrict__ rows, ChunkArgs<NP> A, QueueArgs Q) {
+__global__ void __launch_bounds__(256, 2)
+particle_queue(Work w, const int32_t* __restrict__ d_nactive, Out out, RowStream R,
+               const double* rows, ChunkArgs<NP> A, QueueArgs Q, EphConst E) {
+  (void)E;                             // read by planet_rows from the argument segment
+  const KargPtr ka = (KargPtr)__builtin_amdgcn_kernarg_segment_ptr();
   const int lane = threadIdx.x & 63;
   const int n = *d_nactive;
+  const unsigned long long map_item = R.on ? 1ull : 0ull;
+  int have = R.on ? 0 : Q.nsteps;
   const unsigned long long total = (unsigned long long)Q.ntiles * Q.nsub;
   const unsigned long long one = lane == 0 ? 1ull : 0ull;
-  for (;;) {
-    const unsigned long long item = wave_uniform(atomicAdd(Q.ctr, one) - Q.base);
+  unsigned long long grab = wave_uniform(atomicAdd(Q.ctr, one) - Q.base);
+  if (grab < map_item) {
+    // the launch's first grab; this wavefront does nothing else (so that no
+    // value of the item loop has to outlive the call)
+    run_planet_rows<NP>(ka);
+    return;
+  }
+  for (;; grab = wave_uniform(atomicAdd(Q.ctr, one) - Q.base)) {
+    const unsigned long long item = grab - map_item;
     if (item >= total) break;
     const int s = (int)(item / Q.ntiles);
     const int t = (int)(item % Q.ntiles);
@@ -252,8 +332,7 @@ particle_queue(Work w, const int32_t* __restrict__ d_nactive, Out out,
     const int s_end = min(Q.nsteps, s_begin + Q.sub_steps);
     if (go && s_begin < s_end) {       // the last sub-chunks of a short chunk may be empty
       const int i = t * 64 + lane;
-      advance<NP, KIT, DEPTH, UNIV, true>(w, out, rows, A, i, i < n, s_begin, s_end,
-                                          (KargPtr)__builtin_amdgcn_kernarg_segment_ptr());
+      advance<NP, KIT, DEPTH, UNIV, true>(w, out, rows, A, i, i < n, s_begin, s_end, ka, have);
     }
     // publish completion; the release orders every store of this item
     __hip_atomic_store(Q.progress + t, Q.epoch + (uint32_t)s + 1u, __ATOMIC_RELEASE,
@@ -286,10 +365,11 @@ TPM_DEV void batch_item(const SysDev& S, Work w, Out out, const double* __restri
   const double* rows = ring + S.ring_off + (int64_t)Q.slot * Q.slot_rows * (3 * NP + 3);
   const int i = T.first + lane;
   const bool valid = lane < T.count;
+  int have = s_end;                    // the rows are written before the launch
   if (S.kiters == 5)
-    advance<NP, 5, 0>(w, out, rows, A, i, valid, s_begin, s_end);
+    advance<NP, 5, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
   else
-    advance<NP, 0, 0>(w, out, rows, A, i, valid, s_begin, s_end);
+    advance<NP, 0, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
 }
 
 __global__ void __launch_bounds__(256)
@@ -460,12 +540,22 @@ static hipError_t launch_np(const SysConst& S, Work w, const int32_t* d_nactive,
   Q.sub_steps = (nsteps + QL.nsub - 1) / QL.nsub;
   Q.nsteps = nsteps;
   Q.error = QL.error;
-  if (Q.ntiles <= 0) return hipSuccess;
-  const int waves_per_block = QL.block / 64;
-  const int nblocks = (QL.workers + waves_per_block - 1) / waves_per_block;
-#define TPM_PQ(KIT, UNIV, DEPTH)                                                              \
-  hipLaunchKernelGGL((particle_queue<NP, KIT, UNIV, DEPTH>), dim3(nblocks), dim3(QL.block), 0, st, \
-                     w, d_nactive, out, rows, A, Q)
+  RowStream R{};
+  EphConst E{};
+  if (QL.stream) {
+    R = *QL.stream;
+    E = *QL.eph;
+  }
+  R.error = QL.error;
+  R.ctr = QL.ctr;
+  R.ctr_base = QL.base;
+  R.ctr_alone = QL.grabs(Q.ntiles);
+  if (Q.ntiles <= 0 && !R.on) return hipSuccess;
+  const int nblocks = QL.blocks();
+#define TPM_PQ(KIT, UNIV, DEPTH)                                                                \
+  hipLaunchKernelGGL((particle_queue<NP, KIT, UNIV, DEPTH>), dim3(nblocks), dim3(QL.block),     \
+                     QL.lds(), st,                                                              \
+                     w, d_nactive, out, R, rows, A, Q, E)
   if (QL.deep) {
     if (S.kiters == 5) {
       if (S.universal) TPM_PQ(5, true, 3);
@@ -786,24 +876,34 @@ TPM_DEV bool eph_step(const EphConst& E, const EphLane& L, const EphW<NP>& W, do
   return bad;
 }
 
-// Steps of one fast block (see ephemeris_body).
+// Steps of one fast block (see ephemeris_body), and what ephemeris_body calls
+// after each block of steps: here nothing to do, go on.
 constexpr int EPH_BLOCK = 64;
+struct EphNoBlockEnd {
+  TPM_DEV int block(int left) const { return min(left, EPH_BLOCK); }
+  TPM_DEV bool operator()(int) const { return true; }
+};
 
 // vside (may be null): receives the planets' heliocentric velocities at the
 // chunk's first and last rows, [2][NP][3] (for the sampled diagnostics).
 // VEL: vrows receives them at every row, [nsteps+1][NP][3] (for the
 // encounter integrator).
-template <int NP, bool ROWB, bool VEL = false>
-TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* __restrict__ vj,
-                            double* __restrict__ rows, int nsteps, double dt, int64_t step0,
-                            int64_t* __restrict__ flag, double* __restrict__ vside = nullptr,
-                            double* __restrict__ vrows = nullptr) {
+// resumed: row 0 (and vside's first entry) was written by the call that
+// stopped there and is left alone.  block_end(t) is called once rows 1..t are
+// final and says whether to go on; the return value is the steps carried out
+// (vside's second entry is written only if that is all of them).
+template <int NP, bool ROWB, bool VEL = false, typename BlockEnd = EphNoBlockEnd>
+TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* __restrict__ vj,
+                           double* __restrict__ rows, int nsteps, double dt, int64_t step0,
+                           int64_t* __restrict__ flag, double* __restrict__ vside = nullptr,
+                           double* __restrict__ vrows = nullptr, bool resumed = false,
+                           BlockEnd block_end = BlockEnd()) {
   constexpr int ROW = 3 * NP + 3;
   // This wave is a serial chain that shares its SIMD with particle waves:
   // let it issue first.
   __builtin_amdgcn_s_setprio(3);
   EphLane L;
-  L.lane = threadIdx.x;
+  L.lane = threadIdx.x & 63;
   L.body = L.lane >= 1 && L.lane <= NP;
   L.mup = 1.0; L.ie_prev = 0.0; L.nb = L.body ? 0.0 : 1.0;
 #pragma unroll
@@ -838,7 +938,7 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
   const int roff = L.body ? 3 * (L.lane - 1) : 3 * NP;
   const double rsign = L.body ? 0.0 : -1.0;
   // row 0: the current state
-  if (writer) {
+  if (writer && !resumed) {
     rows[roff + 0] = fma_(rsign, ax, ox);
     rows[roff + 1] = fma_(rsign, ay, oy);
     rows[roff + 2] = fma_(rsign, az, oz);
@@ -851,9 +951,10 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
   // the first event is the smallest key.
   uint32_t first_ev = UINT32_MAX;
   if (NP > 1 && hill_violation<NP>(W, ox, oy, oz, hx, hy, hz)) first_ev = 1u;
-  if (vside) write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside);
-  if (VEL) write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vrows);
-  // Blocks of EPH_BLOCK steps.  Giant planets on near-circular orbits take
+  if (vside && !resumed)
+    write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside);
+  if (VEL && !resumed) write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vrows);
+  // Blocks of steps.  Giant planets on near-circular orbits take
   // the general drift's short sin/cos path and leave its Newton loop after
   // two steps every time, and meet no event; the fast form runs exactly that,
   // with none of the general form's wave-uniform branches, and only notes on
@@ -866,8 +967,11 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
   // wavefronts share SIMDs with the particles, which hide its branches.)
   const bool events = *flag == -1;
   bool fast = !ROWB;
-  for (int s0 = 0; s0 < nsteps; s0 += EPH_BLOCK) {
-    const int nb = nsteps - s0 < EPH_BLOCK ? nsteps - s0 : EPH_BLOCK;
+  int done = 0;
+  while (done < nsteps) {
+    const int s0 = done;
+    const int nb = ROWB ? nsteps : block_end.block(nsteps - s0);
+    done = s0 + nb;
     if (!ROWB && fast) {
       const double sjx = jx, sjy = jy, sjz = jz, swx = wx, swy = wy, swz = wz;
       const double sax = ax, say = ay, saz = az;
@@ -880,7 +984,10 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
                         VEL ? vrows + (size_t)(s + 1) * 3 * NP : nullptr, 2u * (uint32_t)(s + 1),
                         events, first_ev);
       }
-      if (wave_all(!bad)) continue;
+      if (wave_all(!bad)) {
+        if (!block_end(done)) break;
+        continue;
+      }
       jx = sjx; jy = sjy; jz = sjz; wx = swx; wy = swy; wz = swz;
       ax = sax; ay = say; az = saz;
       fast = false;
@@ -892,8 +999,10 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
                                      VEL ? vrows + (size_t)(s + 1) * 3 * NP : nullptr,
                                      2u * (uint32_t)(s + 1), events, first_ev);
     }
+    if (!block_end(done)) break;
   }
-  if (vside) write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside + 3 * NP);
+  if (vside && done == nsteps)
+    write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside + 3 * NP);
   if (L.body) {
     rj[3 * (L.lane - 1) + 0] = jx; rj[3 * (L.lane - 1) + 1] = jy; rj[3 * (L.lane - 1) + 2] = jz;
     vj[3 * (L.lane - 1) + 0] = wx; vj[3 * (L.lane - 1) + 1] = wy; vj[3 * (L.lane - 1) + 2] = wz;
@@ -907,6 +1016,76 @@ TPM_DEV void ephemeris_body(const EphConst& E, double* __restrict__ rj, double* 
   }
   if (L.lane == 0 && *flag == -1 && ev != UINT32_MAX)
     *flag = (ev & 1u) ? step0 + (int64_t)(ev >> 1) : -2;
+  return done;
+}
+
+// The row stream's blocks: what the particles of the same launch follow the
+// map by, so they are short, a quarter of the steps to go but at least 8 and at
+// most 32 (publishing a block costs the map nothing that shows: 0.924 us per
+// step with blocks of 32 as with blocks of 128).  After each the count of
+// published steps goes up; a map that runs ahead of its launch's chunk stops
+// once no other wavefront of the launch is at work.
+struct EphPublish {
+  const RowStream& R;
+  int64_t done;                              // the count when the body started
+  bool ahead;
+  TPM_DEV int block(int left) const { return min(left, max(8, min(32, left >> 2))); }
+  TPM_DEV bool operator()(int t) const {
+    // the release makes the rows written so far visible before the count
+    __hip_atomic_store(R.done, done + t, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (!ahead) return true;
+    const unsigned long long c = wave_uniform(
+        __hip_atomic_load(R.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return c - R.ctr_base < R.ctr_alone;     // others still at work
+  }
+};
+
+// The planet map of a particle launch (see particle_queue), run by the one
+// wavefront that took the launch's first work item: publishes the rows of the
+// launch's chunk block by block, then goes on into the following chunks'
+// slots for as long as other wavefronts of the launch are at work, so the
+// next launch finds rows to start from.  A function of its own, not inlined:
+// it has the planet map's instruction choice (TPM_PLANET_KERNEL) and its own
+// registers.  ka_any: the launch's argument segment (in VGPRs by the calling
+// convention, wave-uniform).
+template <int NP, bool VEL>
+static __device__ __attribute__((noinline)) TPM_PLANET_KERNEL void planet_rows(uint64_t ka_any) {
+  constexpr int ROW = 3 * NP + 3;
+  const KargPtr ka = (KargPtr)wave_uniform(ka_any);
+  const RowStream R = karg_stream<RowStream>(ka, 0);
+  const EphConst E = karg_field<EphConst>(ka, offsetof(QueueKernelArgs<NP>, E));
+  const unsigned long long t0 = __builtin_readsteadycounter();
+  int64_t done = (int64_t)wave_uniform((unsigned long long)__hip_atomic_load(
+      R.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  int64_t b = R.begin;                       // first step of chunk j
+  for (int j = 0; j < STREAM_CHUNKS; ++j) {
+    const int len = karg_stream<int>(ka, offsetof(RowStream, len) + sizeof(int) * j);
+    if (len <= 0) break;
+    if (done >= b + len) {                   // an earlier launch's map ran ahead
+      b += len;
+      continue;
+    }
+    const int s0 = (int)(done - b);
+    const int64_t slot = (R.slot0 + j) % R.nslots;
+    const int n = ephemeris_body<NP, false, VEL>(
+        E, R.rj, R.vj, R.ring + (size_t)(slot * R.slot_rows + s0) * ROW, len - s0, R.dt,
+        R.step0 + (b - R.begin) + s0, R.flag,
+        R.vside ? R.vside + (size_t)slot * 6 * NP : nullptr,
+        VEL ? R.vring + (size_t)(slot * R.vslot_rows + s0) * 3 * NP : nullptr, s0 > 0,
+        EphPublish{R, done, j > 0});
+    done += n;
+    if (n < len - s0) break;
+    b += len;
+  }
+  __builtin_amdgcn_s_setprio(0);
+  if ((threadIdx.x & 63) == 0) *R.ticks += __builtin_readsteadycounter() - t0;
+}
+
+template <int NP>
+TPM_DEV void run_planet_rows(KargPtr ka) {
+  const uint64_t p = (uint64_t)ka;
+  if (karg_stream<double*>(ka, offsetof(RowStream, vring))) planet_rows<NP, true>(p);
+  else planet_rows<NP, false>(p);
 }
 
 template <int NP, bool VEL>

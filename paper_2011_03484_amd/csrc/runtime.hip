@@ -2,11 +2,13 @@
 //
 // One simulation = one device and the device's two HIP streams (default
 // priority, shared by every simulation on the device):
-//   stream E runs the planet map chunk by chunk into a ring of planet-table
-//   slots in HBM; stream P runs the particle kernel over each slot once its
-//   rows are written.  The planet map for chunk c+1 thus overlaps the particle
-//   work of chunk c (sec. 2.2: the next planetary chunk is prepared while the
-//   particles are advanced), with events guarding slot reuse.  Every
+//   stream P runs the particle launches, one per chunk.  Each launch holds its
+//   own planet map: one of its wavefronts writes the chunk's planet rows into a
+//   slot of a ring in HBM, block by block, the others follow it through them,
+//   and while they finish the map goes on into the next chunks' slots (sec.
+//   2.2: the next planetary chunk is prepared while the particles are
+//   advanced).  Planet rows from a history are interpolated on stream E, up to
+//   NSLOT - 1 chunks ahead, with events guarding slot reuse.  Every
 //   resync_chunks chunks the working set is compacted (sec. 2.2, resync
 //   interval) and its new size read back to shrink the next launches.
 #include <hip/hip_runtime.h>
@@ -88,7 +90,7 @@ hipError_t ensure_device_streams(DeviceStreams& D) {
 }
 
 constexpr int NSLOT = 8;   // planet-table ring slots
-constexpr int FIRST_CHUNK_STEPS = 1024;   // longest first chunk of an on-the-fly run
+constexpr int FIRST_CHUNK_STEPS = 1024;   // longest first chunk of a run of several chunks
 // With the close-encounter hand-off an integrate call keeps all its planet
 // rows (and planet velocities); a call that would need more than this (the
 // environment variable TPM_HANDOFF_RING_BYTES may set it) is run as several
@@ -198,6 +200,9 @@ struct tpm_sim {
   double* d_vj = nullptr;
   double* d_tmp = nullptr;               // [4][np][3] scratch for conversions
   int64_t* d_flag = nullptr;
+  int64_t* d_stream = nullptr;           // row stream: [0] steps published, [1] map time (10 ns)
+  int64_t rows_done = 0;                 // host copy of d_stream[0] between calls
+  int64_t map_ticks = 0;                 // d_stream[1] at the end of the last integrate
   int64_t n = 0;
   Work work[2]{};
   int cur = 0;
@@ -222,6 +227,7 @@ struct tpm_sim {
   double hist_dt = 0.0;                  // dt of the last integrate (the current time)
   int64_t step = 0;
   int ncu = 0;                           // compute units of the device
+  bool auto_sub = false;                 // sub_chunks left to the library
   int last_wps = 0;                      // wavefronts per SIMD of the last particle launch
   unsigned long long* d_qctr = nullptr;  // work-queue item counter
   uint32_t* d_progress = nullptr;        // per-tile progress counters
@@ -386,7 +392,7 @@ struct tpm_sim {
     for (auto e : {t0P, t1P, t0E, t1E}) if (e) (void)hipEventDestroy(e);
     for (auto e : kev) (void)hipEventDestroy(e);
     for (auto e : ev_cnt) if (e) (void)hipEventDestroy(e);
-    dfree(d_flag); dfree(d_nactive); dfree(d_acc);
+    dfree(d_flag); dfree(d_stream); dfree(d_nactive); dfree(d_acc);
     if (h_pin) (void)hipHostFree(h_pin);
   }
 
@@ -617,7 +623,8 @@ int tpm_create(const tpm_options* opt, tpm_sim** out) {
   if (o.chunk_steps < 0 || o.resync_chunks < 0 || o.block_threads < 0 || o.sub_chunks < 0 ||
       o.waves_per_simd < 0)
     return fail(TPM_EINVAL, "negative option");
-  if (o.sub_chunks == 0) o.sub_chunks = 64;
+  const bool auto_sub = o.sub_chunks == 0;
+  if (auto_sub) o.sub_chunks = 64;
   if (o.waves_per_simd > 8) return fail(TPM_EINVAL, "waves_per_simd > 8");
   if (o.chunk_steps == 0) o.chunk_steps = 8192;
   if (o.chunk_steps > (1 << 30)) return fail(TPM_EINVAL, "chunk_steps > 2^30");
@@ -641,6 +648,7 @@ int tpm_create(const tpm_options* opt, tpm_sim** out) {
   TPM_HIP(hipSetDevice(o.device));
   tpm_sim* s = new tpm_sim();
   s->opt = o;
+  s->auto_sub = auto_sub;
   s->ncu = prop.multiProcessorCount;
   auto bad = [&](hipError_t e, const char* what) {
     if (e == hipSuccess) return false;
@@ -665,6 +673,8 @@ int tpm_create(const tpm_options* opt, tpm_sim** out) {
   if (bad(hipEventCreate(&s->t0P), "event") || bad(hipEventCreate(&s->t1P), "event") ||
       bad(hipEventCreate(&s->t0E), "event") || bad(hipEventCreate(&s->t1E), "event") ||
       bad(hipMalloc(&s->d_flag, sizeof(int64_t)), "alloc") ||
+      bad(hipMalloc(&s->d_stream, 2 * sizeof(int64_t)), "alloc") ||
+      bad(hipMemset(s->d_stream, 0, 2 * sizeof(int64_t)), "memset") ||
       bad(hipMalloc(&s->d_nactive, sizeof(int32_t)), "alloc") ||
       bad(hipMalloc(&s->d_acc, sizeof(unsigned long long)), "alloc") ||
       bad(hipHostMalloc(&s->h_pin, 256, hipHostMallocDefault), "pinned alloc")) {
@@ -897,10 +907,13 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   const int K = s->opt.chunk_steps;
   const int R = s->opt.resync_chunks;
   const int rl = 3 * s->np + 3;
-  // The particles wait for the whole first chunk of the planet map before
-  // they start, so when the map runs on the fly the first chunk is short;
-  // chunk c covers steps [begin(c), begin(c + 1)) of this call.
-  const int K0 = (s->d_table || s->d_hist) ? K : std::min(K, FIRST_CHUNK_STEPS);
+  // The planet map runs inside the particle launches unless a table or a
+  // history takes its place.  A call of several chunks then starts with a
+  // short one: its compaction drops what is removed in the first orbits, and
+  // with the hand-off the encounter stream starts early. 
+  const bool live = !s->d_table && !s->d_hist;
+  const int K0 = live && (nsteps > K || s->opt.handoff_substeps > 0)
+                     ? std::min(K, FIRST_CHUNK_STEPS) : K;
   auto& D = s->diag;
   if (D.on && D.nres > 0 && s->d_table)
     return fail(TPM_ESTATE, "resonant angles need planet velocities, which a supplied planet "
@@ -956,28 +969,47 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   s->stats.compactions = 0;
   TPM_HIP(hipEventRecord(s->t0P, s->sP));
   TPM_HIP(hipEventRecord(s->t0E, s->sE));
-  // The planet map is enqueued up to NSLOT-1 chunks ahead of the particles so
-  // that it keeps running while the host waits on anything else.
-  int64_t eph_next = 0;
-  auto enqueue_eph = [&](int64_t upto) -> int {
-    for (; eph_next <= upto && eph_next < nchunks; ++eph_next) {
-      const int64_t c = eph_next;
-      const int ks = length(c);
+  // A history's rows are enqueued up to NSLOT-1 chunks ahead of the particles.
+  int64_t hist_next = 0;
+  auto enqueue_hist = [&](int64_t upto) -> int {
+    for (; hist_next <= upto && hist_next < nchunks; ++hist_next) {
+      const int64_t c = hist_next;
       const int slot = (int)(c % NSLOT);
       double* srow = s->d_ring + (size_t)row_slot(c) * s->ring_rows * rl;
       TPM_HIP(hipStreamWaitEvent(s->sE, s->ev_done[slot], 0));
       double* vs = s->d_vside ? s->d_vside + (size_t)slot * 6 * s->np : nullptr;
-      // with the hand-off, the planets' velocities at every row too (for the
-      // encounter integrator's interpolation; the slot is this chunk's alone)
-      double* vr = ho ? s->d_vring + (size_t)c * s->vring_rows * 3 * s->np : nullptr;
-      if (s->d_hist)
-        TPM_HIP(launch_history_rows(s->hist(), srow, ks + 1, s->step + begin(c), dt, vs, s->sE));
-      else
-        TPM_HIP(launch_ephemeris_chunk(E, s->d_rj, s->d_vj, srow, ks, dt, s->step + begin(c),
-                                       s->d_flag, s->sE, vs, vr));
+      TPM_HIP(launch_history_rows(s->hist(), srow, length(c) + 1, s->step + begin(c), dt, vs,
+                                  s->sE));
       TPM_HIP(hipEventRecord(s->ev_eph[slot], s->sE));
     }
     return TPM_OK;
+  };
+  // The planet rows that chunk c's launch writes itself: its own, and those of
+  // the chunks after it that the map may run ahead into (their slots are free:
+  // the launches that read them before are over).
+  auto row_stream = [&](int64_t c) {
+    RowStream R{};
+    R.on = 1;
+    R.rj = s->d_rj;
+    R.vj = s->d_vj;
+    R.ring = s->d_ring;
+    R.slot_rows = s->ring_rows;
+    R.slot0 = row_slot(c);
+    R.nslots = ring_slots;
+    // with the hand-off, the planets' velocities at every row too (for the
+    // encounter integrator's interpolation)
+    R.vring = ho ? s->d_vring : nullptr;
+    R.vslot_rows = s->vring_rows;
+    R.vside = s->d_vside;
+    R.dt = dt;
+    R.step0 = s->step + begin(c);
+    R.begin = s->rows_done + begin(c);
+    R.done = s->d_stream;
+    R.ticks = (unsigned long long*)(s->d_stream + 1);
+    R.flag = s->d_flag;
+    for (int64_t j = 0; j < std::min<int64_t>(STREAM_CHUNKS, ring_slots) && c + j < nchunks; ++j)
+      R.len[j] = length(c + j);
+    return R;
   };
   // Newest active count whose readback has completed (never blocks); the
   // count is only an upper bound for the grid, the kernels read the exact
@@ -1060,9 +1092,11 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
     if (s->d_table) {
       rows = s->d_table + (size_t)step0 * rl;
     } else {
-      int rc = enqueue_eph(c + NSLOT - 1);
-      if (rc) return rc;
-      TPM_HIP(hipStreamWaitEvent(s->sP, s->ev_eph[slot], 0));
+      if (s->d_hist) {
+        int rc = enqueue_hist(c + NSLOT - 1);
+        if (rc) return rc;
+        TPM_HIP(hipStreamWaitEvent(s->sP, s->ev_eph[slot], 0));
+      }
       rows = s->d_ring + (size_t)row_slot(c) * s->ring_rows * rl;
     }
     {
@@ -1071,14 +1105,24 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
       n_grid = std::min(n_grid, s->n_active);
     }
     const double* vel = s->d_vside ? s->d_vside + (size_t)slot * 6 * s->np : nullptr;
-    if (c == 0 && D.on && step0 % D.every == 0 && step0 != D.last_step) {
+    const bool opening = c == 0 && D.on && step0 % D.every == 0 && step0 != D.last_step;
+    if (opening) {
+      // sampled before the chunk's launch: its first row is needed now
+      if (live)
+        TPM_HIP(launch_ephemeris_chunk(E, s->d_rj, s->d_vj, (double*)rows, 0, dt, step0, s->d_flag,
+                                       s->sP, (double*)vel, nullptr));
       int rc = sample(step0, rows, vel, n_grid);
       if (rc) return rc;
     }
-    if (n_grid > 0) {
+    if (n_grid > 0 || live) {             // the map runs on without particles
       Work& w = s->work[s->cur];
       if (timed) TPM_HIP(hipEventRecord(s->kev[2 * s->stats.chunks], s->sP));
       QueueLaunch QL;
+      const RowStream R = live ? row_stream(c) : RowStream{};
+      if (live) {
+        QL.stream = &R;
+        QL.eph = &E;
+      }
       QL.ctr = s->d_qctr;
       QL.base = s->q_base;
       QL.progress = s->d_progress;
@@ -1096,15 +1140,13 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
       QL.workers = std::min(QL.workers, ntiles);
       QL.block = s->opt.block_threads;
       QL.error = s->d_qerr;
+      if (s->auto_sub) lone_tiles(QL, ntiles, s->ncu);
       TPM_HIP(launch_particle_chunk(S, w, s->d_nactive, n_grid, s->out, rows, ks, dt, step0, QL,
                                     s->sP));
-      // every wavefront takes exactly one failing item at the end
-      const int wpb = QL.block / 64;
-      const unsigned long long waves = (unsigned long long)((QL.workers + wpb - 1) / wpb) * wpb;
-      s->q_base += (unsigned long long)ntiles * QL.nsub + waves;
+      s->q_base += QL.grabs(ntiles);
       s->q_epoch += (uint32_t)QL.nsub;
       if (timed) TPM_HIP(hipEventRecord(s->kev[2 * s->stats.chunks + 1], s->sP));
-      s->stats.chunks++;
+      if (n_grid > 0) s->stats.chunks++;
     }
     if (D.on && (step0 + ks) % D.every == 0) {
       int rc = sample(step0 + ks, rows + (size_t)ks * rl, vel ? vel + 3 * s->np : nullptr, n_grid);
@@ -1190,7 +1232,15 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   s->hist_dt = dt;
   float msP = 0.f, msE = 0.f;
   TPM_HIP(hipEventElapsedTime(&msP, s->t0P, s->t1P));
-  TPM_HIP(hipEventElapsedTime(&msE, s->t0E, s->t1E));
+  if (live) {
+    s->rows_done += nsteps;
+    int64_t ticks = 0;
+    TPM_HIP(hipMemcpy(&ticks, s->d_stream + 1, sizeof(ticks), hipMemcpyDeviceToHost));
+    msE = (float)((double)(ticks - s->map_ticks) * 1e-5);
+    s->map_ticks = ticks;
+  } else {
+    TPM_HIP(hipEventElapsedTime(&msE, s->t0E, s->t1E));
+  }
   // active particle-steps of this call
   TPM_HIP(hipMemsetAsync(s->d_acc, 0, sizeof(unsigned long long), s->sP));
   TPM_HIP(launch_active_steps(s->out.step, (int)s->n, step_begin, s->step, s->d_acc, s->sP));

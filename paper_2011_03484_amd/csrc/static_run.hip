@@ -58,6 +58,8 @@ struct Misc {
   int64_t flag;              // planet event (see tpm_integrate_static)
   int32_t nactive;
   int32_t qerr;              // work-queue error flag
+  int64_t done;              // planet rows published (steps)
+  unsigned long long ticks;  // time of the planet map
 };
 static_assert(sizeof(Misc) <= MISC_BYTES, "misc block");
 
@@ -97,6 +99,8 @@ static_setup_kernel(unsigned char* base, PlanetsIn P, int np, int n, int ntiles)
     m->flag = -1;
     m->nactive = n;
     m->qerr = 0;
+    m->done = 0;
+    m->ticks = 0;
   }
 }
 
@@ -181,7 +185,8 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
   if (o.block_threads == 0) o.block_threads = 64;
   if (o.block_threads % 64 || o.block_threads > 256)
     return sfail(TPM_EINVAL, "block_threads must be 64, 128, 192 or 256");
-  if (o.sub_chunks == 0) o.sub_chunks = 64;
+  const bool auto_sub = o.sub_chunks == 0;
+  if (auto_sub) o.sub_chunks = 64;
   if (o.waves_per_simd > 8) return sfail(TPM_EINVAL, "waves_per_simd > 8");
   if (!(o.kepler_ftol > 0.0)) o.kepler_ftol = 1e-13;
   if (!std::isfinite(o.r_escape)) return sfail(TPM_EINVAL, "r_escape not finite");
@@ -266,7 +271,7 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
   unsigned char* base = D.base;
   const int nn = (int)n;
   const int K = o.chunk_steps;
-  const int R = o.resync_chunks;
+  const int resync = o.resync_chunks;
   const int ntiles = (nn + 63) / 64;
   Misc* misc = reinterpret_cast<Misc*>(base + OFF_MISC);
   double* plan = reinterpret_cast<double*>(base + OFF_PLAN);
@@ -296,9 +301,26 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
   for (int64_t c = 0; c < nchunks; ++c) {
     const int ks = (int)std::min<int64_t>(K, nsteps - c * K);
     const int64_t step0 = c * K;
-    S_HIP(launch_ephemeris_chunk(E, rj, vj, ring, ks, dt, step0, &misc->flag, st));
-    if (nn > 0) {
+    // the chunk's particle launch holds its planet map (see particle_queue);
+    // the ring has one slot, so the map stops at the chunk's end
+    RowStream R{};
+    R.on = 1;
+    R.rj = rj;
+    R.vj = vj;
+    R.ring = ring;
+    R.slot_rows = K + 1;
+    R.nslots = 1;
+    R.dt = dt;
+    R.step0 = step0;
+    R.begin = step0;
+    R.done = &misc->done;
+    R.ticks = &misc->ticks;
+    R.flag = &misc->flag;
+    R.len[0] = ks;
+    {
       QueueLaunch QL;
+      QL.stream = &R;
+      QL.eph = &E;
       QL.ctr = &misc->qctr;
       QL.base = q_base;
       QL.progress = reinterpret_cast<uint32_t*>(base + OFF_PROG);
@@ -311,12 +333,11 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
       QL.workers = std::min(QL.workers, ntiles);
       QL.block = o.block_threads;
       QL.error = &misc->qerr;
+      if (auto_sub) lone_tiles(QL, ntiles, D.ncu);
       S_HIP(launch_particle_chunk(S, w[cur], &misc->nactive, nn, out, ring, ks, dt, step0, QL, st));
-      const int wpb = QL.block / 64;
-      const unsigned long long waves = (unsigned long long)((QL.workers + wpb - 1) / wpb) * wpb;
-      q_base += (unsigned long long)ntiles * QL.nsub + waves;
+      q_base += QL.grabs(ntiles);
       q_epoch += (uint32_t)QL.nsub;
-      if (((c + 1) % R == 0) || c == nchunks - 1) {
+      if (nn > 0 && (((c + 1) % resync == 0) || c == nchunks - 1)) {
         S_HIP(launch_compact(w[cur], w[1 - cur], &misc->nactive, nn, cscr, st));
         cur = 1 - cur;
       }
