@@ -10,7 +10,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtpmvs.so")
 SOURCES = ["kernels_core.hip", "ad_kernels.hip", "diag_kernels.hip", "history.hip",
            "handoff.hip", "runtime.hip", "static_run.hip"]
-HEADERS = ["dmath.hpp", "kepler.hpp", "particle.hpp", "universal.hpp", "ad.hpp", "internal.h",
+HEADERS = ["dmath.hpp", "kepler.hpp", "particle.hpp", "universal.hpp", "planet_quad.hpp", "ad.hpp", "internal.h",
            "ad_internal.h", "diag_internal.h", "history_internal.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

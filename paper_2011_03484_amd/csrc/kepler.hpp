@@ -268,30 +268,31 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
   return ok;
 }
 
-// Converged drift for the planets (a handful of lanes in one wavefront):
-// Newton until every lane has made a step whose correction is at most
-// 2^-30 |x| (converged to rounding; planet_newton), at most 40 steps.  A lane
-// that holds no body, or whose body is found unbound (the return value is then
-// false), drifts for no time on a stand-in bound orbit (alpha = 1): dM = 0,
-// x = 0, f = gdot = 1 and g = fdot = 0 exactly, so its state is left as it
-// was without any select on the result.
+// f, g, fdot and gdot of a planet's converged Kepler drift from r^2, v^2 and
+// r.v (a handful of lanes in one wavefront): Newton until every lane has made a
+// step whose correction is at most 2^-30 |x| (converged to rounding;
+// planet_newton), at most 40 steps.  A lane that holds no body, or whose body
+// is found unbound (the return value is then false), drifts for no time on a
+// stand-in bound orbit (alpha = 1): dM = 0, x = 0, f = gdot = 1 and
+// g = fdot = 0 exactly, so its state is left as it was without any select on
+// the result.
 // FAST: no wave-uniform branch; two Newton steps in the short sin/cos range
 // (planet_newton2).  `bad` is set on a lane where the general form would have
 // taken another path (the short range not allowed, or more Newton steps); the
 // results are the general form's bit for bit where no lane of the wavefront
 // is bad.  The general form leaves `bad` false.
-template <bool FAST>
-TPM_DEV bool drift_converged_t(const KepConst& K, double dt, bool lane_on,
-                               double& x, double& y, double& z,
-                               double& vx, double& vy, double& vz, bool& bad) {
-  double r2 = fma_(x, x, fma_(y, y, z * z));
-  double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
-  double u = fma_(x, vx, fma_(y, vy, z * vz));
+// STANDIN: lanes without a body already hold such a stand-in (r^2 = v^2 =
+// mu = 1, u = 0, dt = 0), so the fast form needs no selects for them; an
+// unbound body is then bad too.
+template <bool FAST, bool STANDIN = false>
+TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, double v2, double u,
+                       double& f, double& g, double& fd, double& gd, bool& bad) {
+  constexpr bool PLAIN = FAST && STANDIN;
   double r0, rinv;
-  sqrt_rsqrt(lane_on ? r2 : 1.0, r0, rinv);
+  sqrt_rsqrt(PLAIN || lane_on ? r2 : 1.0, r0, rinv);
   double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
   const bool bound = alpha > 0.0;
-  const bool idle = !(lane_on && bound);
+  const bool idle = PLAIN ? false : !(lane_on && bound);
   alpha = idle ? 1.0 : alpha;
   dt = idle ? 0.0 : dt;
   double sa, rsa;
@@ -319,6 +320,7 @@ TPM_DEV bool drift_converged_t(const KepConst& K, double dt, bool lane_on,
     bool conv;
     xk = planet_newton2(ec, es, om, dM, idle, xk, s, m, conv);
     bad = !(idle | short_args(dM, w)) | !conv;
+    if (PLAIN) bad = bad | !bound;
   } else {
     bad = false;
     if (wave_all(idle | short_args(dM, w)))
@@ -329,22 +331,28 @@ TPM_DEV bool drift_converged_t(const KepConst& K, double dt, bool lane_on,
   double Fp = fma_(-ec, m, fma_(es, s, om));
   double r1 = a * Fp;
   double r1inv = rcp(r1);
-  double f = fma_(a * rinv, m, 1.0);
-  double g = fma_(s - xk, ninv, dte);
-  double fd = -(a * a) * n * s * rinv * r1inv;
-  double gd = fma_(a * r1inv, m, 1.0);
+  f = fma_(a * rinv, m, 1.0);
+  g = fma_(s - xk, ninv, dte);
+  fd = -(a * a) * n * s * rinv * r1inv;
+  gd = fma_(a * r1inv, m, 1.0);
+  return bound;
+}
+
+// The converged drift of a planet held as three components on one lane.
+template <bool FAST>
+TPM_DEV bool drift_converged_t(const KepConst& K, double dt, bool lane_on,
+                               double& x, double& y, double& z,
+                               double& vx, double& vy, double& vz, bool& bad) {
+  double r2 = fma_(x, x, fma_(y, y, z * z));
+  double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
+  double u = fma_(x, vx, fma_(y, vy, z * vz));
+  double f, g, fd, gd;
+  const bool bound = planet_fg<FAST>(K, dt, lane_on, r2, v2, u, f, g, fd, gd, bad);
   double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
   double nvx = fma_(fd, x, gd * vx), nvy = fma_(fd, y, gd * vy), nvz = fma_(fd, z, gd * vz);
   x = nx; y = ny; z = nz;
   vx = nvx; vy = nvy; vz = nvz;
   return bound;
-}
-
-TPM_DEV bool drift_converged(const KepConst& K, double dt, bool lane_on,
-                             double& x, double& y, double& z,
-                             double& vx, double& vy, double& vz) {
-  bool bad;
-  return drift_converged_t<false>(K, dt, lane_on, x, y, z, vx, vy, vz, bad);
 }
 
 }  // namespace tpm

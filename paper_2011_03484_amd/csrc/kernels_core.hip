@@ -16,6 +16,7 @@
 //  * finalize        - scatter the active particles back to caller order.
 #include "internal.h"
 #include "particle.hpp"
+#include "planet_quad.hpp"
 #include "universal.hpp"
 
 namespace tpm {
@@ -1019,10 +1020,127 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
   return done;
 }
 
+template <bool FAST>
+struct FormTag { static constexpr bool value = FAST; };
+
+// ephemeris_body for one to four planets, in the layout of planet_quad.hpp
+// (same arguments and results to rounding; E is read per lane, once).  Blocks
+// as there: the fast form, or the general form from the first block a lane
+// could not take fast.  A body found unbound stays out of the fast form.
+template <int NP, bool VEL, typename EP, typename BlockEnd = EphNoBlockEnd>
+TPM_DEV int ephemeris_quad(EP E, double* __restrict__ rj, double* __restrict__ vj,
+                           double* __restrict__ rows, int nsteps, double dt, int64_t step0,
+                           int64_t* __restrict__ flag, double* __restrict__ vside = nullptr,
+                           double* __restrict__ vrows = nullptr, bool resumed = false,
+                           BlockEnd block_end = BlockEnd()) {
+  constexpr int ROW = 3 * NP + 3;
+  __builtin_amdgcn_s_setprio(3);   // a serial chain among particle wavefronts
+  const int lane = threadIdx.x & 63;
+  const EphQuad Q = eph_quad<NP>(E, dt, lane);
+  // block 0 holds the state and the heliocentric positions, component 3 none
+  const bool writer = Q.on && (lane & 12) == 0 && Q.col < 3;
+  const bool writer0 = lane < 3;
+  const int at = 3 * Q.body + Q.col;
+  double j = 0.0, w = 0.0;
+  if (Q.on && Q.col < 3) {
+    j = rj[at];
+    w = vj[at];
+  } else if (!Q.on) {
+    j = Q.col == 0 ? 1.0 : 0.0;      // the stand-in orbit of planet_fg
+    w = Q.col == 1 ? 1.0 : 0.0;
+  }
+  auto put_row = [&](double* row, double d, double h0) {
+    if (writer) row[at] = d;
+    if (writer0) row[3 * NP + lane] = h0;
+  };
+  auto put_velocities = [&](double* out) {
+    const double hv = mfma4(Q.pos, w);
+    if (writer) out[at] = hv;
+  };
+  double d, a, h0;
+  const bool close0 = quad_accel(Q, j, d, a, h0);
+  if (!resumed) {
+    put_row(rows, d, h0);
+    if (vside) put_velocities(vside);
+    if (VEL) put_velocities(vrows);
+  }
+  const double h = 0.5 * dt;
+  uint32_t first_ev = close0 ? 1u : UINT32_MAX;
+  auto step = [&](auto fast_c, int s) {
+    constexpr bool FAST = decltype(fast_c)::value;
+    bool bad;
+    w = fma_(h, a, w);
+    const bool bound = quad_drift<FAST>(Q, j, w, bad);
+    const bool close = quad_accel(Q, j, d, a, h0);
+    w = fma_(h, a, w);
+    put_row(rows + (size_t)s * ROW, d, h0);
+    if (VEL) put_velocities(vrows + (size_t)s * 3 * NP);
+    if (!FAST) {
+      const uint32_t key = 2u * (uint32_t)s;
+      first_ev = __builtin_elementwise_min(first_ev, Q.on && !bound ? key : UINT32_MAX);
+      first_ev = __builtin_elementwise_min(first_ev, close ? key + 1u : UINT32_MAX);
+    }
+    return FAST ? bad | (NP > 1 && close) : false;
+  };
+  // Once the run's first event is on record later ones cannot change it, but a
+  // close pair still ends the fast form: the general one is as right.
+  bool fast = true;
+  int done = 0;
+  while (done < nsteps) {
+    const int s0 = done;
+    const int nb = block_end.block(nsteps - s0);
+    done = s0 + nb;
+    if (fast) {
+      const double sj = j, sw = w, sa = a;
+      bool bad = false;
+      for (int t = 1; t <= nb; ++t) bad = bad | step(FormTag<true>{}, s0 + t);
+      if (wave_all(!bad)) {
+        if (!block_end(done)) break;
+        continue;
+      }
+      j = sj; w = sw; a = sa;
+      fast = false;
+    }
+    for (int t = 1; t <= nb; ++t) step(FormTag<false>{}, s0 + t);
+    if (!block_end(done)) break;
+  }
+  if (vside && done == nsteps) put_velocities(vside + 3 * NP);
+  if (writer) {
+    rj[at] = j;
+    vj[at] = w;
+  }
+  // earliest event over the wavefront: unbound -> -2, a close pair -> its step
+  uint32_t ev = first_ev;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    uint32_t o = __shfl_xor(ev, off, 64);
+    ev = o < ev ? o : ev;
+  }
+  if (lane == 0 && *flag == -1 && ev != UINT32_MAX)
+    *flag = (ev & 1u) ? step0 + (int64_t)(ev >> 1) : -2;
+  return done;
+}
+
+// The planet map of NP planets: one to four by matrix instructions.
+template <int NP, bool ROWB, bool VEL, typename EP, typename BlockEnd = EphNoBlockEnd>
+TPM_DEV int planet_map(EP E, double* rj, double* vj, double* rows, int nsteps, double dt,
+                       int64_t step0, int64_t* flag, double* vside = nullptr,
+                       double* vrows = nullptr, bool resumed = false,
+                       BlockEnd block_end = BlockEnd()) {
+  if constexpr (NP >= 1 && NP <= 4) {
+    return ephemeris_quad<NP, VEL>(E, rj, vj, rows, nsteps, dt, step0, flag, vside, vrows, resumed,
+                                   block_end);
+  } else {
+    const EphConst C = *E;
+    return ephemeris_body<NP, ROWB, VEL>(C, rj, vj, rows, nsteps, dt, step0, flag, vside, vrows,
+                                         resumed, block_end);
+  }
+}
+
 // The row stream's blocks: what the particles of the same launch follow the
 // map by, so they are short, a quarter of the steps to go but at least 8 and at
-// most 32 (publishing a block costs the map nothing that shows: 0.924 us per
-// step with blocks of 32 as with blocks of 128).  After each the count of
+// most 32 (publishing a block cost the map nothing that showed: the same time
+// per step with blocks of 32 as with blocks of 128).  After each the count of
 // published steps goes up; a map that runs ahead of its launch's chunk stops
 // once no other wavefront of the launch is at work.
 struct EphPublish {
@@ -1053,7 +1171,7 @@ static __device__ __attribute__((noinline)) TPM_PLANET_KERNEL void planet_rows(u
   constexpr int ROW = 3 * NP + 3;
   const KargPtr ka = (KargPtr)wave_uniform(ka_any);
   const RowStream R = karg_stream<RowStream>(ka, 0);
-  const EphConst E = karg_field<EphConst>(ka, offsetof(QueueKernelArgs<NP>, E));
+  const auto E = karg_pointer<EphConst>(ka, offsetof(QueueKernelArgs<NP>, E));
   const unsigned long long t0 = __builtin_readsteadycounter();
   int64_t done = (int64_t)wave_uniform((unsigned long long)__hip_atomic_load(
       R.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1067,7 +1185,7 @@ static __device__ __attribute__((noinline)) TPM_PLANET_KERNEL void planet_rows(u
     }
     const int s0 = (int)(done - b);
     const int64_t slot = (R.slot0 + j) % R.nslots;
-    const int n = ephemeris_body<NP, false, VEL>(
+    const int n = planet_map<NP, false, VEL>(
         E, R.rj, R.vj, R.ring + (size_t)(slot * R.slot_rows + s0) * ROW, len - s0, R.dt,
         R.step0 + (b - R.begin) + s0, R.flag,
         R.vside ? R.vside + (size_t)slot * 6 * NP : nullptr,
@@ -1093,7 +1211,10 @@ __global__ void __launch_bounds__(64) TPM_PLANET_KERNEL
 ephemeris_chunk(EphConst E, double* __restrict__ rj, double* __restrict__ vj,
                 double* __restrict__ rows, int nsteps, double dt, int64_t step0,
                 int64_t* __restrict__ flag, double* __restrict__ vside, double* __restrict__ vrows) {
-  ephemeris_body<NP, false, VEL>(E, rj, vj, rows, nsteps, dt, step0, flag, vside, vrows);
+  (void)E;                           // the first argument, read from the argument segment
+  planet_map<NP, false, VEL>(
+      karg_pointer<EphConst>((KargPtr)__builtin_amdgcn_kernarg_segment_ptr(), 0), rj, vj, rows,
+      nsteps, dt, step0, flag, vside, vrows);
 }
 
 // Many systems at once: workgroup b runs system b (its constants, Jacobi
@@ -1109,15 +1230,15 @@ ephemeris_batch(const EphConst* __restrict__ E, double* __restrict__ rj, double*
   double* r = rj + 3 * MAX_NP * b;
   double* v = vj + 3 * MAX_NP * b;
   switch (e.np) {
-    case 1: ephemeris_body<1, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 2: ephemeris_body<2, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 3: ephemeris_body<3, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 4: ephemeris_body<4, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 5: ephemeris_body<5, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 6: ephemeris_body<6, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 7: ephemeris_body<7, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    case 8: ephemeris_body<8, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
-    default: ephemeris_body<0, true>(e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 1: planet_map<1, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 2: planet_map<2, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 3: planet_map<3, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 4: planet_map<4, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 5: planet_map<5, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 6: planet_map<6, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 7: planet_map<7, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    case 8: planet_map<8, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
+    default: planet_map<0, true, false>(&e, r, v, rows, nsteps, dt[b], step0, flag + b); break;
   }
 }
 

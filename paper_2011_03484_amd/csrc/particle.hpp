@@ -67,6 +67,18 @@ TPM_DEV T karg_field(KargPtr p, size_t off) {
 #endif
 }
 
+// Pointer to a kernel argument in its segment (for reads with a lane's index).
+template <typename T>
+TPM_DEV auto karg_pointer(KargPtr p, size_t off) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return reinterpret_cast<const __attribute__((address_space(4))) T*>(karg_at_use(p) + off);
+#else
+  (void)p;
+  (void)off;
+  return static_cast<const T*>(nullptr);
+#endif
+}
+
 // Kick acceleration from one table row (sec. 2.2, kick equation):
 //   a = h0 - sum_j mu_j d_j / |d_j|^3,   d_j = r - r_j,
 // and the encounter test |d_j| < rcrit_j (lowest j wins; -1 if none).
