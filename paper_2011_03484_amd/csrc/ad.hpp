@@ -25,26 +25,20 @@ namespace tpm {
 struct DriftVals {
   double u, r0, rinv, alpha, sa, a, n, ec, es, dMr, q, x, s, c, m, Fp, r1, f, g, fd, gd;
   double rsa, ninv, r1inv;   // 1/sa, 1/n, 1/r1 (the derivatives multiply by these)
-  bool ok;
 };
 
-// Same arithmetic as drift_fixed (the particle kernel's drift), keeping the
-// intermediate values; writes the drifted state only where ok.  KNOWN: the
-// root of Kepler's equation and its sin and cos - 1 are given (kx, ks, km:
-// the values an earlier evaluation of the same drift found), so the solve is
-// skipped and every other value comes out bit for bit as that evaluation's.
-template <bool KNOWN>
-TPM_DEV void drift_vals_t(const KepConst& K, double dt, int kiters, double ftol, double x, double y,
-                          double z, double vx, double vy, double vz, DriftVals& D, double& nx,
-                          double& ny, double& nz, double& nvx, double& nvy, double& nvz,
-                          double kx, double ks, double km) {
+// The values of the drift whose Kepler root kx, with its sine ks and cosine
+// minus one km, an evaluation of the particles' drift found (drift_lanes; the
+// drifted state comes out as there, to rounding).
+TPM_DEV void drift_vals(const KepConst& K, double dt, double x, double y, double z, double vx,
+                        double vy, double vz, DriftVals& D, double& nx, double& ny, double& nz,
+                        double& nvx, double& nvy, double& nvz, double kx, double ks, double km) {
   double r2 = fma_(x, x, fma_(y, y, z * z));
   double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
   double u = fma_(x, vx, fma_(y, vy, z * vz));
   D.u = u;
   sqrt_rsqrt(r2, D.r0, D.rinv);
   D.alpha = fma_(-v2, K.inv_mu, 2.0 * D.rinv);
-  bool bound = D.alpha > 0.0;
   double rsa;
   sqrt_rsqrt(D.alpha, D.sa, rsa);
   D.rsa = rsa;
@@ -62,17 +56,8 @@ TPM_DEV void drift_vals_t(const KepConst& K, double dt, int kiters, double ftol,
   double dte = (D.q == 0.0) ? dt : D.dMr * ninv;
   dM = D.dMr;
   const double om = 1.0 - D.ec;
-  double xk, s, m, Fk;
-  if (KNOWN) {
-    xk = kx; s = ks; m = km; Fk = 0.0;
-  } else {
-    const double w = 2.0 * (__builtin_fabs(D.ec) + __builtin_fabs(D.es));
-    xk = kepler_starter(D.ec, D.es, om, dM, w);
-    xk = kepler_solve(D.ec, D.es, om, dM, kiters, w, xk, s, m, Fk);
-  }
-  double F = fma_(-D.ec, s, fma_(-D.es, m, xk - dM));
+  const double xk = kx, s = ks, m = km;
   D.Fp = fma_(-D.ec, m, fma_(D.es, s, om));
-  D.ok = bound && (__builtin_fmax(__builtin_fabs(F), __builtin_fabs(Fk)) <= ftol);
   D.x = xk; D.s = s; D.m = m; D.c = 1.0 + m;
   D.r1 = D.a * D.Fp;
   double r1inv = rcp(D.r1);
@@ -83,13 +68,6 @@ TPM_DEV void drift_vals_t(const KepConst& K, double dt, int kiters, double ftol,
   D.gd = fma_(D.a * r1inv, m, 1.0);
   nx = fma_(D.f, x, D.g * vx); ny = fma_(D.f, y, D.g * vy); nz = fma_(D.f, z, D.g * vz);
   nvx = fma_(D.fd, x, D.gd * vx); nvy = fma_(D.fd, y, D.gd * vy); nvz = fma_(D.fd, z, D.gd * vz);
-}
-
-TPM_DEV void drift_vals(const KepConst& K, double dt, int kiters, double ftol, double x, double y,
-                        double z, double vx, double vy, double vz, DriftVals& D, double& nx,
-                        double& ny, double& nz, double& nvx, double& nvy, double& nvz) {
-  drift_vals_t<false>(K, dt, kiters, ftol, x, y, z, vx, vy, vz, D, nx, ny, nz, nvx, nvy, nvz, 0.0,
-                      0.0, 0.0);
 }
 
 // Tangent of the drift: (dr, dv) at (r, v) -> (dr', dv').

@@ -52,13 +52,12 @@ template <int NP, typename RowT>
 TPM_DEV int32_t ad_step(const ADArgs<NP>& A, const RowT& row1, double r[3], double v[3],
                         double acc[3], int32_t& planet, double xsm[3]) {
   const double h = 0.5 * A.dt;
-  DriftVals D;
-  double nr[3], nv[3];
-  drift_vals(A.K, A.dt, A.kiters, A.ftol, r[0], r[1], r[2], fma_(h, acc[0], v[0]),
-             fma_(h, acc[1], v[1]), fma_(h, acc[2], v[2]), D, nr[0], nr[1], nr[2], nv[0], nv[1],
-             nv[2]);
-  xsm[0] = D.x; xsm[1] = D.s; xsm[2] = D.m;
-  if (!D.ok) return ST_KEPLER;
+  double nr[3] = {r[0], r[1], r[2]};
+  double nv[3] = {fma_(h, acc[0], v[0]), fma_(h, acc[1], v[1]), fma_(h, acc[2], v[2])};
+  const uint64_t bad =
+      drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), lanes(true), nr[0],
+                  nr[1], nr[2], nv[0], nv[1], nv[2], xsm[0], xsm[1], xsm[2]);
+  if (lane_in(bad)) return ST_KEPLER;
   double b[3];
   int hit = accel<NP>(row1, A.P, nr[0], nr[1], nr[2], b[0], b[1], b[2]);
   for (int k = 0; k < 3; ++k) {
@@ -178,8 +177,8 @@ ad_reverse(ADArgs<NP> A, const double* __restrict__ table, const double* __restr
     double vh[3] = {fma_(h, cur[6], v[0]), fma_(h, cur[7], v[1]), fma_(h, cur[8], v[2])};
     DriftVals D;
     double nr[3], nv[3];
-    drift_vals_t<true>(A.K, A.dt, A.kiters, A.ftol, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, nr[0],
-                       nr[1], nr[2], nv[0], nv[1], nv[2], cur[9], cur[10], cur[11]);
+    drift_vals(A.K, A.dt, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, nr[0], nr[1], nr[2], nv[0],
+               nv[1], nv[2], cur[9], cur[10], cur[11]);
     // closing kick: v_{s+1} = v' + h a(r_{s+1})
     double Al[3];
     accel_jac<NP>(row1, A.P, nr, lv, Al);
@@ -226,11 +225,17 @@ ad_tangent(ADArgs<NP> A, const double* __restrict__ table, double* __restrict__ 
     accel_jac<NP>(table + (size_t)s * ROW, A.P, r, dr, Ad);
     double vh[3] = {fma_(h, acc[0], v[0]), fma_(h, acc[1], v[1]), fma_(h, acc[2], v[2])};
     double dvh[3] = {dv[0] + h * Ad[0], dv[1] + h * Ad[1], dv[2] + h * Ad[2]};
+    // the state by the particles' drift, the values its derivative needs from
+    // the root that drift found
+    double nr[3] = {r[0], r[1], r[2]}, nv[3] = {vh[0], vh[1], vh[2]}, xk, sk, mk;
+    const uint64_t bad =
+        drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), lanes(true), nr[0],
+                    nr[1], nr[2], nv[0], nv[1], nv[2], xk, sk, mk);
+    if (lane_in(bad)) { why = ST_KEPLER; break; }
     DriftVals D;
-    double nr[3], nv[3];
-    drift_vals(A.K, A.dt, A.kiters, A.ftol, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, nr[0], nr[1],
-               nr[2], nv[0], nv[1], nv[2]);
-    if (!D.ok) { why = ST_KEPLER; break; }
+    double q[6];
+    drift_vals(A.K, A.dt, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, q[0], q[1], q[2], q[3], q[4],
+               q[5], xk, sk, mk);
     double ndr[3], ndv[3];
     drift_jvp(A.K, A.dt, D, r, vh, dr, dvh, ndr, ndv);
     double b[3];

@@ -161,7 +161,9 @@ template <int NP, int KIT>
 TPM_DEV bool enc_drift(const EncArgs<NP>& A, double dt, double& x, double& y, double& z,
                        double& vx, double& vy, double& vz) {
   double nx = x, ny = y, nz = z, nvx = vx, nvy = vy, nvz = vz;
-  bool ok = drift_fixed(A.K, dt, KIT > 0 ? KIT : A.kiters, A.ftol, nx, ny, nz, nvx, nvy, nvz);
+  double xk, sk, mk;
+  bool ok = !lane_in(drift_lanes(A.K, dt, KIT > 0 ? KIT : A.kiters, A.ftol, KIT == 5, lanes(true),
+                                 nx, ny, nz, nvx, nvy, nvz, xk, sk, mk));
   if (!ok && A.universal) {
     nx = x; ny = y; nz = z; nvx = vx; nvy = vy; nvz = vz;
     ok = drift_universal(A.K.mu, dt, nx, ny, nz, nvx, nvy, nvz);
@@ -369,7 +371,7 @@ static hipError_t enc_np(const SysConst& S, const double* rrem2, EncList L, cons
   A.universal = S.universal;
   A.target = target;
   A.budget = budget;
-  if (S.kiters == 5)
+  if (quick_serves(S.kiters, S.ftol))
     hipLaunchKernelGGL((encounter_run<NP, 5>), dim3((n_upper + 63) / 64), dim3(64), 0, st, A, L,
                        snap, R, out);
   else

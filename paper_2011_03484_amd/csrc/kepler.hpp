@@ -219,9 +219,10 @@ TPM_DEV double kepler_solve(double ec, double es, double om, double dM, int kite
 // drifted state into (x, v) on every lane; where the return value is false
 // (the drift is refused) that state is meaningless and the caller keeps its
 // own copy of the old one.
+// (xk, s, m) receive the root, its sine and its cosine minus one.
 TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
                          double& x, double& y, double& z,
-                         double& vx, double& vy, double& vz) {
+                         double& vx, double& vy, double& vz, double& xk, double& s, double& m) {
   double r2 = fma_(x, x, fma_(y, y, z * z));
   double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
   double u = fma_(x, vx, fma_(y, vy, z * vz));
@@ -246,8 +247,8 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
   dM = dMr;
   const double w = 2.0 * (__builtin_fabs(ec) + __builtin_fabs(es));
   const double om = 1.0 - ec;
-  double xk = kepler_starter(ec, es, om, dM, w);
-  double s, m, Fk;
+  xk = kepler_starter(ec, es, om, dM, w);
+  double Fk;
   xk = kepler_solve(ec, es, om, dM, kiters, w, xk, s, m, Fk);
   double F = fma_(-ec, s, fma_(-es, m, xk - dM));
   double Fp = fma_(-ec, m, fma_(es, s, om));
@@ -266,6 +267,139 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
   x = nx; y = ny; z = nz;
   vx = nvx; vy = nvy; vz = nvz;
   return ok;
+}
+
+// The short drift: the particle drift where the arc and the eccentricity are
+// moderate, |t| = |dM|/(1 - ec) <= 1/4 and eb = |ec| + |es| <= 3/4, in the
+// fewest instructions (a particle step is bound by their number).
+//  * No whole periods to remove and no bracket for the starter.  The failure
+//    rule of five Newton steps from the third-order starter always holds in
+//    these ranges (|F(x_5)| stays below 6e-17 over two million draws of them), so
+//    for thresholds from 1e-14 up it needs no evaluation.
+//  * 1/(1 - ec) = a/r0 is at hand, and the starter goes one order further
+//    (c4 = h (5 (h^2 - c3) + 1/12) by reversion of the series): one Newton step
+//    then is converged for arcs up to a hundredth of an orbit at
+//    eccentricities up to 0.5, where the third-order one left 2% of the lanes,
+//    and with them seven wavefronts in ten, to a second step.
+//  * |x| <= 0.3 leaves the last terms of the sine and cosine series below
+//    2^-55 of the sum.
+//  * gdot = 1 + m/F', fdot = -(n a)(sin x / r0)/F' and n a = sqrt(mu alpha), all
+//    without r1; 1/F' at the root continues the step's reciprocal (F' has moved
+//    by less than 2^-26).
+// A Newton step from x to x - d leaves an error of |F''| d^2 / (2 F'(x)) where d
+// is so small that F' hardly changes, and |F''| <= eb: a lane is `fine` with
+// |d| <= 2^-28 and eb d^2 / F'(x) <= 2^-54 |x - d|, half of which is left at
+// most.  The few that are not after one step take a second one, and a lane
+// still not fine (or out of the ranges, or unbound: NaN) is left to
+// drift_fixed.  All of it is the lane's own decision; the branches only skip
+// what no lane of act needs.  Lane predicates are kept as lane masks: as
+// booleans the compiler carries them through vector registers.
+// With it a lone wavefront's step of four planets takes less than the planet
+// map's 0.55 us (0.78 before); 10,000 steps of 13,313 particles 5.8 ms instead
+// of 9.5, of 200,000 15.9 instead of 22.1.  Rounding errors of one drift are the
+// same as drift_fixed's (5.7e-17 rms in position, 7.4e-17 to 8.5e-17 in velocity).
+constexpr double QUICK_FTOL = 1e-14;   // smallest failure threshold it may serve
+
+TPM_DEV uint64_t lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// Is this lane in the mask?  (A lane mask is what a select or a branch takes.)
+TPM_DEV bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
+// sin x and cos x - 1 for |x| <= 0.31.
+TPM_DEV void sincos_short(double x, double& s, double& m) {
+  const double z = x * x;
+  const double z2 = z * z;
+  const double z4 = z2 * z2;
+  const double s01 = fma_(S5, z, S3), s23 = fma_(S9, z, S7), s45 = fma_(S13, z, S11);
+  s = fma_(x * z, fma_(z4, s45, fma_(z2, s23, s01)), x);
+  const double c01 = fma_(C6, z, C4), c23 = fma_(C10, z, C8);
+  m = fma_(z2, fma_(z4, C12, fma_(z2, c23, c01)), -0.5 * z);
+}
+
+// Returns the fine lanes; the others' states mean nothing.
+TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double& x, double& y,
+                         double& z, double& vx, double& vy, double& vz, double& xk, double& s,
+                         double& m) {
+  const double r2 = fma_(x, x, fma_(y, y, z * z));
+  const double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
+  const double u = fma_(x, vx, fma_(y, vy, z * vz));
+  double r0, rinv;
+  sqrt_rsqrt(r2, r0, rinv);
+  const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
+  double sa, rsa;
+  sqrt_rsqrt(alpha, sa, rsa);             // NaN for unbound lanes, which are not fine
+  const double a = rsa * rsa;             // meets cos x - 1 and sin x - x only
+  const double ms = K.sqrt_mu * sa;       // n a
+  const double dM = ms * alpha * dt;
+  const double ninv = K.inv_sqrt_mu * rsa * a;
+  const double ec = fma_(-r0, alpha, 1.0);
+  const double es = u * sa * K.inv_sqrt_mu;
+  const double eb = __builtin_fabs(ec) + __builtin_fabs(es);
+  const double om = 1.0 - ec;
+  const double ar = a * rinv;             // 1/om
+  const double t = dM * ar;
+  const double h = (0.5 * es) * ar;
+  const double c3 = ar * fma_(es, h, ec * (-1.0 / 6.0));
+  const double c4 = h * fma_(5.0, fma_(h, h, -c3), 1.0 / 12.0);
+  xk = t * fma_(t, fma_(t, fma_(t, c4, c3), -h), 1.0);
+  const uint64_t range = lanes(__builtin_fabs(t) <= 0.25) & lanes(eb <= 0.75);
+  double iFp;
+  auto newton = [&](double x0, double& xn, double& sn, double& mn, double& yn) {
+    double sv, mv;
+    sincos_short(x0, sv, mv);
+    const double F = fma_(-ec, sv, fma_(-es, mv, x0 - dM));
+    yn = rcp_newton(fma_(-ec, mv, fma_(es, sv, om)));
+    xn = fma_(-F, yn, x0);
+    const double d = x0 - xn;
+    sn = fma_(-(1.0 + mv), d, sv);
+    mn = fma_(sv, d, mv);
+    const double ad = __builtin_fabs(d);
+    return range & lanes(ad <= 0x1p-28) &
+           lanes(eb * yn * (ad * ad) <= 0x1p-54 * __builtin_fabs(xn));
+  };
+  uint64_t fine = newton(xk, xk, s, m, iFp);
+  if (act & ~fine) {
+    double xn, sn, mn, yn;
+    const uint64_t f2 = newton(xk, xn, sn, mn, yn);
+    const bool mine = lane_in(fine);
+    xk = mine ? xk : xn;
+    s = mine ? s : sn;
+    m = mine ? m : mn;
+    iFp = mine ? iFp : yn;
+    fine |= f2;
+  }
+  {
+    const double e = fma_(-fma_(-ec, m, fma_(es, s, om)), iFp, 1.0);
+    iFp = fma_(iFp, fma_(e, e, e), iFp);
+  }
+  const double f = fma_(ar, m, 1.0);
+  const double g = fma_(s - xk, ninv, dt);
+  const double fd = -((ms * rinv) * (s * iFp));
+  const double gd = fma_(iFp, m, 1.0);
+  const double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
+  vx = fma_(fd, x, gd * vx); vy = fma_(fd, y, gd * vy); vz = fma_(fd, z, gd * vz);
+  x = nx; y = ny; z = nz;
+  return fine;
+}
+
+// The particles' drift of the lanes of act: drift_quick where `quick` is set and
+// it serves, drift_fixed elsewhere.  Returns the lanes of act whose drift is
+// refused (their state, and that of lanes outside act, means nothing).
+__host__ TPM_DEV bool quick_serves(int kiters, double ftol) { return kiters == 5 && ftol >= QUICK_FTOL; }
+
+TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ftol, bool quick,
+                             uint64_t act, double& x, double& y, double& z, double& vx, double& vy,
+                             double& vz, double& xk, double& s, double& m) {
+  double ox = x, oy = y, oz = z, ux = vx, uy = vy, uz = vz;
+  uint64_t rest = act;
+  if (quick) rest = act & ~drift_quick(K, dt, act, x, y, z, vx, vy, vz, xk, s, m);
+  if (rest == 0) return 0;
+  bool ok = true;
+  if (lane_in(rest)) {
+    ok = drift_fixed(K, dt, kiters, ftol, ox, oy, oz, ux, uy, uz, xk, s, m);
+    x = ox; y = oy; z = oz;
+    vx = ux; vy = uy; vz = uz;
+  }
+  return lanes(!ok);
 }
 
 // f, g, fdot and gdot of a planet's converged Kepler drift from r^2, v^2 and

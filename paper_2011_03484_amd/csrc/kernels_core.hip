@@ -7,8 +7,9 @@
 //    the planet map of the chunk run by one more wavefront of the same launch.
 //    Every lane reads the same planet-table row: broadcast vector loads into
 //    VGPRs, one step ahead of its use.
-//  * ephemeris_chunk (and planet_rows, inside particle_queue) - one wavefront; lane b holds Jacobi body b.  Wisdom-Holman
-//    kick-drift-kick of the planets (sec. 2.2, planet integration) writing the
+//  * ephemeris_chunk (and planet_rows, inside particle_queue) - one wavefront,
+//    each lane one component of one body (up to four planets, planet_quad.hpp)
+//    or lane b Jacobi body b.  Wisdom-Holman kick-drift-kick of the planets (sec. 2.2, planet integration) writing the
 //    heliocentric positions and the indirect term h0 per step.
 //  * compact_*       - stable partition of the working set so removed particles
 //    stop occupying lanes (sec. 2.2, resync interval), by wave ballots, an LDS
@@ -98,7 +99,8 @@ TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
 }
 
 // Advance particle i of the working set through steps [s_begin, s_end) of a
-// chunk whose rows start at `rows` (row k = step step0 + k).  The rows are
+// chunk whose rows start at `rows` (row k = step step0 + k).  KIT = 5 serves
+// failure thresholds from QUICK_FTOL up (drift_quick).  The rows are
 // written before the launch, or (KA with a row stream) by the launch's own
 // planet map as the particles follow: `have` counts the steps whose closing
 // rows are published, and the wavefront waits for more where it runs out
@@ -128,20 +130,20 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     vx = w.vx[i]; vy = w.vy[i]; vz = w.vz[i];
   }
   // A lane's removal record (the state it keeps, step, reason, planet) is
-  // written out in the step that removes it, so the state registers can be
-  // overwritten unconditionally; a removed lane takes no further part.  With
-  // the hand-off on, a lane within a planet's radius is handed off instead:
-  // its state stays in the working set, marked with its local step, for the
-  // encounter integrator.
-  int32_t reason = valid ? ST_ACTIVE : -1;
+  // written out in the step that removes it.  `act` holds the lanes still
+  // integrated: the others ride along, their states mean nothing and enter no
+  // test (masking them out of the step would cost every step an exec mask and
+  // a branch).  With the hand-off on, a lane within a planet's radius is
+  // handed off instead: its state stays in the working set, marked with its
+  // local step, for the encounter integrator.
+  uint64_t act = lanes(valid);
   auto record = [&](int32_t why, int64_t st, int32_t pl, double rx, double ry, double rz,
                     double ux, double uy, double uz) {
     const Work wr = KA ? karg_work(ka) : w;
     if (A.handoff && why == ST_ENCOUNTER) {
       wr.x[i] = rx; wr.y[i] = ry; wr.z[i] = rz;
       wr.vx[i] = ux; wr.vy[i] = uy; wr.vz[i] = uz;
-      reason = HANDOFF_BASE + (int32_t)(st - A.step0);
-      wr.status[i] = reason;
+      wr.status[i] = HANDOFF_BASE + (int32_t)(st - A.step0);
       return;
     }
     const Out o = KA ? karg_out(ka) : out;
@@ -152,52 +154,57 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     o.reason[k] = why;
     o.planet[k] = pl;
     wr.status[i] = why;
-    reason = why;
   };
   double ax, ay, az;
   if (KA && have <= s_begin) {
     have = wait_rows(ka, s_begin, A.nsteps);
     if (have <= s_begin) return;            // the wait gave up (flagged)
   }
-  int hit = accel<NP>(rows + (size_t)s_begin * ROW, A.P, x, y, z, ax, ay, az);
-  if (valid) {
-    if (hit >= 0) record(ST_ENCOUNTER, A.step0 + s_begin, hit, x, y, z, vx, vy, vz);
-    else if (fma_(x, x, fma_(y, y, z * z)) > A.rmax2)
-      record(ST_ESCAPE, A.step0 + s_begin, -1, x, y, z, vx, vy, vz);
+  {
+    const int hit = accel<NP>(rows + (size_t)s_begin * ROW, A.P, x, y, z, ax, ay, az);
+    const bool far = fma_(x, x, fma_(y, y, z * z)) > A.rmax2;
+    if (valid) {
+      if (hit >= 0) record(ST_ENCOUNTER, A.step0 + s_begin, hit, x, y, z, vx, vy, vz);
+      else if (far) record(ST_ESCAPE, A.step0 + s_begin, -1, x, y, z, vx, vy, vz);
+    }
+    act &= ~lanes((hit >= 0) | far);
   }
   const double h = 0.5 * A.dt;
   // one step s -> s + 1, with the row that ends it (row s + 1)
   auto step = [&](int s, const auto& row) {
-    if (reason == ST_ACTIVE) {
-      double nx = x, ny = y, nz = z;
-      double nvx = fma_(h, ax, vx), nvy = fma_(h, ay, vy), nvz = fma_(h, az, vz);
-      bool ok = drift_fixed(A.K, A.dt, kiters, A.ftol, nx, ny, nz, nvx, nvy, nvz);
-      if (UNIV && !wave_all(ok)) {
-        if (!ok) {
-          nx = x; ny = y; nz = z;
-          nvx = fma_(h, ax, vx); nvy = fma_(h, ay, vy); nvz = fma_(h, az, vz);
-          ok = drift_universal(A.K.mu, A.dt, nx, ny, nz, nvx, nvy, nvz);
-        }
+    double nx = x, ny = y, nz = z;
+    double nvx = fma_(h, ax, vx), nvy = fma_(h, ay, vy), nvz = fma_(h, az, vz);
+    double xk, sk, mk;
+    uint64_t bad = drift_lanes(A.K, A.dt, kiters, A.ftol, KIT == 5, act, nx, ny, nz, nvx, nvy, nvz,
+                               xk, sk, mk);
+    if (UNIV && bad) {
+      bool ok = true;
+      if (lane_in(bad)) {
+        nx = x; ny = y; nz = z;
+        nvx = fma_(h, ax, vx); nvy = fma_(h, ay, vy); nvz = fma_(h, az, vz);
+        ok = drift_universal(A.K.mu, A.dt, nx, ny, nz, nvx, nvy, nvz);
       }
-      double bx, by, bz;
-      const int hit1 = accel<NP>(row, A.P, nx, ny, nz, bx, by, bz);
-      const double r2 = fma_(nx, nx, fma_(ny, ny, nz * nz));
-      nvx = fma_(h, bx, nvx); nvy = fma_(h, by, nvy); nvz = fma_(h, bz, nvz);
-      if (!ok | (hit1 >= 0) | (r2 > A.rmax2)) {
+      bad = lanes(!ok);
+    }
+    double bx, by, bz;
+    uint64_t near;
+    const auto hit_of = accel_near<NP>(row, A.P, nx, ny, nz, bx, by, bz, near);
+    const uint64_t far = lanes(fma_(nx, nx, fma_(ny, ny, nz * nz)) > A.rmax2);
+    nvx = fma_(h, bx, nvx); nvy = fma_(h, by, nvy); nvz = fma_(h, bz, nvz);
+    const uint64_t gone = act & (bad | near | far);
+    if (gone) {
+      if (lane_in(gone)) {
         // a Kepler failure keeps the state at the start of the step
-        if (!ok) record(ST_KEPLER, A.step0 + s, -1, x, y, z, vx, vy, vz);
-        else if (hit1 >= 0) record(ST_ENCOUNTER, A.step0 + s + 1, hit1, nx, ny, nz, nvx, nvy, nvz);
+        if (lane_in(bad)) record(ST_KEPLER, A.step0 + s, -1, x, y, z, vx, vy, vz);
+        else if (lane_in(near))
+          record(ST_ENCOUNTER, A.step0 + s + 1, hit_of(), nx, ny, nz, nvx, nvy, nvz);
         else record(ST_ESCAPE, A.step0 + s + 1, -1, nx, ny, nz, nvx, nvy, nvz);
       }
-      x = nx; y = ny; z = nz;
-      vx = nvx; vy = nvy; vz = nvz;
-      ax = bx; ay = by; az = bz;
+      act &= ~gone;
     }
-  };
-  // leave once every lane is removed (checked every 8 steps: the check itself
-  // costs a vector-to-scalar round trip)
-  auto all_removed = [&](int s) {
-    return ((s - s_begin) & 7) == 0 && wave_all(reason != ST_ACTIVE);
+    x = nx; y = ny; z = nz;
+    vx = nvx; vy = nvy; vz = nvz;
+    ax = bx; ay = by; az = bz;
   };
   for (int s0 = s_begin;;) {
     if (KA && have <= s0) {
@@ -213,7 +220,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
       Row<NP> ra, rb;
       load_row<NP>(ra, rows + (size_t)(s0 + 1) * ROW, zero);
       for (int s = s0; s < lim; s += 2) {
-        if (all_removed(s)) break;
+        if (act == 0) break;
         load_row<NP>(rb, rows + (size_t)min(s + 2, lim) * ROW, zero);
         step(s, ra.v);
         if (s + 1 >= lim) break;
@@ -230,7 +237,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
       load_row<NP>(rb, rows + (size_t)min(s0 + 2, lim) * ROW, zero);
       load_row<NP>(rc, rows + (size_t)min(s0 + 3, lim) * ROW, zero);
       for (int s = s0; s < lim; s += 4) {
-        if (all_removed(s)) break;
+        if (act == 0) break;
         load_row<NP>(rd, rows + (size_t)min(s + 4, lim) * ROW, zero);
         step(s, ra.v);
         if (s + 1 >= lim) break;
@@ -246,14 +253,14 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     } else {
       // many wavefronts per SIMD: rows by scalar loads at their use
       for (int s = s0; s < lim; ++s) {
-        if (all_removed(s)) break;
+        if (act == 0) break;
         step(s, rows + (size_t)(s + 1) * ROW);
       }
     }
     s0 = lim;
-    if (!KA || s0 >= s_end || wave_all(reason != ST_ACTIVE)) break;
+    if (!KA || s0 >= s_end || act == 0) break;
   }
-  if (reason == ST_ACTIVE) {
+  if (lane_in(act)) {
     const Work we = KA ? karg_work(ka) : w;
     we.x[i] = x; we.y[i] = y; we.z[i] = z;
     we.vx[i] = vx; we.vy[i] = vy; we.vz[i] = vz;
@@ -367,7 +374,7 @@ TPM_DEV void batch_item(const SysDev& S, Work w, Out out, const double* __restri
   const int i = T.first + lane;
   const bool valid = lane < T.count;
   int have = s_end;                    // the rows are written before the launch
-  if (S.kiters == 5)
+  if (quick_serves(S.kiters, S.ftol))
     advance<NP, 5, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
   else
     advance<NP, 0, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
@@ -557,8 +564,9 @@ static hipError_t launch_np(const SysConst& S, Work w, const int32_t* d_nactive,
   hipLaunchKernelGGL((particle_queue<NP, KIT, UNIV, DEPTH>), dim3(nblocks), dim3(QL.block),     \
                      QL.lds(), st,                                                              \
                      w, d_nactive, out, R, rows, A, Q, E)
+  const bool quick = quick_serves(S.kiters, S.ftol);
   if (QL.deep) {
-    if (S.kiters == 5) {
+    if (quick) {
       if (S.universal) TPM_PQ(5, true, 3);
       else TPM_PQ(5, false, 3);
     } else {
@@ -566,7 +574,7 @@ static hipError_t launch_np(const SysConst& S, Work w, const int32_t* d_nactive,
       else TPM_PQ(0, false, 3);
     }
   } else {
-    if (S.kiters == 5) {
+    if (quick) {
       if (S.universal) TPM_PQ(5, true, 1);
       else TPM_PQ(5, false, 1);
     } else {
@@ -1601,7 +1609,12 @@ __global__ void drift_test_kernel(KepConst K, int kiters, double ftol, const dou
   double x = in[6 * i + 0], y = in[6 * i + 1], z = in[6 * i + 2];
   double vx = in[6 * i + 3], vy = in[6 * i + 4], vz = in[6 * i + 5];
   bool g = false;
-  if (mode != 2) g = drift_fixed(K, dt, kiters, ftol, x, y, z, vx, vy, vz);
+  double xk, sk, mk;
+  if (mode != 2) {
+    const uint64_t act = lanes(true);
+    g = !lane_in(drift_lanes(K, dt, kiters, ftol, quick_serves(kiters, ftol), act, x, y, z, vx, vy,
+                             vz, xk, sk, mk));
+  }
   if (mode != 0 && !g) {
     x = in[6 * i + 0]; y = in[6 * i + 1]; z = in[6 * i + 2];
     vx = in[6 * i + 3]; vy = in[6 * i + 4]; vz = in[6 * i + 5];

@@ -81,22 +81,37 @@ TPM_DEV auto karg_pointer(KargPtr p, size_t off) {
 
 // Kick acceleration from one table row (sec. 2.2, kick equation):
 //   a = h0 - sum_j mu_j d_j / |d_j|^3,   d_j = r - r_j,
-// and the encounter test |d_j| < rcrit_j (lowest j wins; -1 if none).
-// The row (3 NP + 3 doubles: r_1..r_NP, h0) is the same for every lane.
+// and the encounter test |d_j| < rcrit_j: `near` are the lanes where any holds,
+// the returned function gives the lowest such j (-1 if none), from the squared
+// distances.  The row (3 NP + 3 doubles: r_1..r_NP, h0) is the same for every
+// lane.
 template <int NP, typename RowT>
-TPM_DEV int accel(const RowT& row, const PlanetConst<NP>& P,
-                  double x, double y, double z, double& ax, double& ay, double& az) {
+TPM_DEV auto accel_near(const RowT& row, const PlanetConst<NP>& P, double x, double y, double z,
+                        double& ax, double& ay, double& az, uint64_t& near) {
+  struct Hit {
+    double d2[NP > 0 ? NP : 1];
+    const PlanetConst<NP>& P;
+    TPM_DEV int operator()() const {
+      // scanning downwards, the last hit wins
+      int hit = -1;
+#pragma unroll
+      for (int j = NP - 1; j >= 0; --j) hit = d2[j] < P.rcrit2[j] ? j : hit;
+      return hit;
+    }
+  };
+  Hit H{{}, P};
   ax = row[3 * NP + 0];
   ay = row[3 * NP + 1];
   az = row[3 * NP + 2];
-  double d2s[NP > 0 ? NP : 1];
+  near = 0;
 #pragma unroll
   for (int j = 0; j < NP; ++j) {
     double dx = x - row[3 * j + 0];
     double dy = y - row[3 * j + 1];
     double dz = z - row[3 * j + 2];
     double d2 = fma_(dx, dx, fma_(dy, dy, dz * dz));
-    d2s[j] = d2;
+    H.d2[j] = d2;
+    near |= lanes(d2 < P.rcrit2[j]);
     // to rounding (the first-order form, good to 2^-45, is always a little
     // low: a bias of the same sign in every kick)
     double k = mul_rsqrt3(P.mu[j], d2);
@@ -104,12 +119,15 @@ TPM_DEV int accel(const RowT& row, const PlanetConst<NP>& P,
     ay = fma_(-k, dy, ay);
     az = fma_(-k, dz, az);
   }
-  // lowest planet index inside its radius: scanning downwards, the last hit
-  // wins (one compare per planet, no combined lane predicates)
-  int hit = -1;
-#pragma unroll
-  for (int j = NP - 1; j >= 0; --j) hit = d2s[j] < P.rcrit2[j] ? j : hit;
-  return hit;
+  return H;
+}
+
+// The same, returning the lowest planet index at once.
+template <int NP, typename RowT>
+TPM_DEV int accel(const RowT& row, const PlanetConst<NP>& P,
+                  double x, double y, double z, double& ax, double& ay, double& az) {
+  uint64_t near;
+  return accel_near<NP>(row, P, x, y, z, ax, ay, az, near)();
 }
 
 }  // namespace tpm
