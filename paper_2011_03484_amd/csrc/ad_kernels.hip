@@ -55,7 +55,7 @@ TPM_DEV int32_t ad_step(const ADArgs<NP>& A, const RowT& row1, double r[3], doub
   double nr[3] = {r[0], r[1], r[2]};
   double nv[3] = {fma_(h, acc[0], v[0]), fma_(h, acc[1], v[1]), fma_(h, acc[2], v[2])};
   const uint64_t bad =
-      drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), lanes(true), nr[0],
+      drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), false, lanes(true), nr[0],
                   nr[1], nr[2], nv[0], nv[1], nv[2], xsm[0], xsm[1], xsm[2]);
   if (lane_in(bad)) return ST_KEPLER;
   double b[3];
@@ -229,7 +229,7 @@ ad_tangent(ADArgs<NP> A, const double* __restrict__ table, double* __restrict__ 
     // the root that drift found
     double nr[3] = {r[0], r[1], r[2]}, nv[3] = {vh[0], vh[1], vh[2]}, xk, sk, mk;
     const uint64_t bad =
-        drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), lanes(true), nr[0],
+        drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), false, lanes(true), nr[0],
                     nr[1], nr[2], nv[0], nv[1], nv[2], xk, sk, mk);
     if (lane_in(bad)) { why = ST_KEPLER; break; }
     DriftVals D;

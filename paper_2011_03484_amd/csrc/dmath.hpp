@@ -40,6 +40,11 @@ TPM_DEV bool wave_all(bool p) {
   return __builtin_amdgcn_ballot_w64(p) == __builtin_amdgcn_read_exec();
 }
 
+// The lanes where p holds, as a mask, and whether this lane is in a mask (what a
+// select or a branch takes: no round trip through a vector register).
+TPM_DEV uint64_t lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+TPM_DEV bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+
 // 1/x to rounding: y (1 + e + e^2), e = 1 - x y.
 TPM_DEV double rcp(double x) {
   double y = __builtin_amdgcn_rcp(x);

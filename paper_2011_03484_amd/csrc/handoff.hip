@@ -160,17 +160,9 @@ TPM_DEV int interp_accel(const EncArgs<NP>& A, double tau, const RowA& ra,
 template <int NP, int KIT>
 TPM_DEV bool enc_drift(const EncArgs<NP>& A, double dt, double& x, double& y, double& z,
                        double& vx, double& vy, double& vz) {
-  double nx = x, ny = y, nz = z, nvx = vx, nvy = vy, nvz = vz;
   double xk, sk, mk;
-  bool ok = !lane_in(drift_lanes(A.K, dt, KIT > 0 ? KIT : A.kiters, A.ftol, KIT == 5, lanes(true),
-                                 nx, ny, nz, nvx, nvy, nvz, xk, sk, mk));
-  if (!ok && A.universal) {
-    nx = x; ny = y; nz = z; nvx = vx; nvy = vy; nvz = vz;
-    ok = drift_universal(A.K.mu, dt, nx, ny, nz, nvx, nvy, nvz);
-  }
-  x = nx; y = ny; z = nz;
-  vx = nvx; vy = nvy; vz = nvz;
-  return ok;
+  return !lane_in(drift_lanes(A.K, dt, KIT > 0 ? KIT : A.kiters, A.ftol, KIT == 5,
+                              A.universal != 0, lanes(true), x, y, z, vx, vy, vz, xk, sk, mk));
 }
 
 // One lane per list entry.  Each lane runs its own sequence of micro-steps,

@@ -22,6 +22,7 @@
 #pragma once
 #include "dmath.hpp"
 #include "internal.h"
+#include "universal.hpp"
 
 namespace tpm {
 
@@ -300,10 +301,6 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
 // same as drift_fixed's (5.7e-17 rms in position, 7.4e-17 to 8.5e-17 in velocity).
 constexpr double QUICK_FTOL = 1e-14;   // smallest failure threshold it may serve
 
-TPM_DEV uint64_t lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
-// Is this lane in the mask?  (A lane mask is what a select or a branch takes.)
-TPM_DEV bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
-
 // sin x and cos x - 1 for |x| <= 0.31.
 TPM_DEV void sincos_short(double x, double& s, double& m) {
   const double z = x * x;
@@ -382,22 +379,43 @@ TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double&
 }
 
 // The particles' drift of the lanes of act: drift_quick where `quick` is set and
-// it serves, drift_fixed elsewhere.  Returns the lanes of act whose drift is
-// refused (their state, and that of lanes outside act, means nothing).
-__host__ TPM_DEV bool quick_serves(int kiters, double ftol) { return kiters == 5 && ftol >= QUICK_FTOL; }
+// it serves; with `univ` (a refused drift is then taken in universal variables,
+// so whether the fixed-count solve refuses does not matter)
+// drift_universal_quick where that serves; drift_fixed elsewhere, and with univ
+// drift_universal where it refuses.  Returns the lanes of act whose drift is
+// refused in the end (their state, and that of lanes outside act, means
+// nothing).
+__host__ TPM_DEV bool quick_serves(int kiters, double ftol) {
+  return kiters == 5 && ftol >= QUICK_FTOL;
+}
 
 TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ftol, bool quick,
-                             uint64_t act, double& x, double& y, double& z, double& vx, double& vy,
-                             double& vz, double& xk, double& s, double& m) {
-  double ox = x, oy = y, oz = z, ux = vx, uy = vy, uz = vz;
+                             bool univ, uint64_t act, double& x, double& y, double& z, double& vx,
+                             double& vy, double& vz, double& xk, double& s, double& m) {
+  const double ox = x, oy = y, oz = z, ux = vx, uy = vy, uz = vz;
   uint64_t rest = act;
   if (quick) rest = act & ~drift_quick(K, dt, act, x, y, z, vx, vy, vz, xk, s, m);
   if (rest == 0) return 0;
+  if (quick && univ) {
+    double px = ox, py = oy, pz = oz, qx = ux, qy = uy, qz = uz;
+    const uint64_t served = drift_universal_quick(K, dt, rest, px, py, pz, qx, qy, qz);
+    if (lane_in(served)) {
+      x = px; y = py; z = pz;
+      vx = qx; vy = qy; vz = qz;
+    }
+    rest &= ~served;
+    if (rest == 0) return 0;
+  }
   bool ok = true;
   if (lane_in(rest)) {
-    ok = drift_fixed(K, dt, kiters, ftol, ox, oy, oz, ux, uy, uz, xk, s, m);
     x = ox; y = oy; z = oz;
     vx = ux; vy = uy; vz = uz;
+    ok = drift_fixed(K, dt, kiters, ftol, x, y, z, vx, vy, vz, xk, s, m);
+    if (!ok && univ) {
+      x = ox; y = oy; z = oz;
+      vx = ux; vy = uy; vz = uz;
+      ok = drift_universal(K.mu, dt, x, y, z, vx, vy, vz);
+    }
   }
   return lanes(!ok);
 }

@@ -9,8 +9,9 @@
 //    VGPRs, one step ahead of its use.
 //  * ephemeris_chunk (and planet_rows, inside particle_queue) - one wavefront,
 //    each lane one component of one body (up to four planets, planet_quad.hpp)
-//    or lane b Jacobi body b.  Wisdom-Holman kick-drift-kick of the planets (sec. 2.2, planet integration) writing the
-//    heliocentric positions and the indirect term h0 per step.
+//    or lane b Jacobi body b.  Wisdom-Holman kick-drift-kick of the planets
+//    (sec. 2.2, planet integration) writing the heliocentric positions and the
+//    indirect term h0 per step.
 //  * compact_*       - stable partition of the working set so removed particles
 //    stop occupying lanes (sec. 2.2, resync interval), by wave ballots, an LDS
 //    scan and ordered block offsets.
@@ -112,8 +113,8 @@ TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
 // scalar loads at the point of use, for many).
 //
 // UNIV: a drift the fixed-iteration solve refuses is taken in universal
-// variables instead (drift_universal); the particle is removed as KEPLER only
-// if that gives no finite result either.
+// variables instead (drift_lanes); the particle is removed as KEPLER only if
+// that gives no finite result either.
 // KA: w and out are read from the work-queue kernel's argument segment ka
 // where they are used (the item's start and end, a record), which leaves the
 // step loop's scalar registers to its constants.
@@ -175,17 +176,8 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     double nx = x, ny = y, nz = z;
     double nvx = fma_(h, ax, vx), nvy = fma_(h, ay, vy), nvz = fma_(h, az, vz);
     double xk, sk, mk;
-    uint64_t bad = drift_lanes(A.K, A.dt, kiters, A.ftol, KIT == 5, act, nx, ny, nz, nvx, nvy, nvz,
-                               xk, sk, mk);
-    if (UNIV && bad) {
-      bool ok = true;
-      if (lane_in(bad)) {
-        nx = x; ny = y; nz = z;
-        nvx = fma_(h, ax, vx); nvy = fma_(h, ay, vy); nvz = fma_(h, az, vz);
-        ok = drift_universal(A.K.mu, A.dt, nx, ny, nz, nvx, nvy, nvz);
-      }
-      bad = lanes(!ok);
-    }
+    const uint64_t bad = drift_lanes(A.K, A.dt, kiters, A.ftol, KIT == 5, UNIV, act, nx, ny, nz,
+                                     nvx, nvy, nvz, xk, sk, mk);
     double bx, by, bz;
     uint64_t near;
     const auto hit_of = accel_near<NP>(row, A.P, nx, ny, nz, bx, by, bz, near);
@@ -1608,17 +1600,19 @@ __global__ void drift_test_kernel(KepConst K, int kiters, double ftol, const dou
   if (i >= n) return;
   double x = in[6 * i + 0], y = in[6 * i + 1], z = in[6 * i + 2];
   double vx = in[6 * i + 3], vy = in[6 * i + 4], vz = in[6 * i + 5];
-  bool g = false;
+  bool g;
   double xk, sk, mk;
-  if (mode != 2) {
-    const uint64_t act = lanes(true);
-    g = !lane_in(drift_lanes(K, dt, kiters, ftol, quick_serves(kiters, ftol), act, x, y, z, vx, vy,
-                             vz, xk, sk, mk));
-  }
-  if (mode != 0 && !g) {
-    x = in[6 * i + 0]; y = in[6 * i + 1]; z = in[6 * i + 2];
-    vx = in[6 * i + 3]; vy = in[6 * i + 4]; vz = in[6 * i + 5];
-    g = drift_universal(K.mu, dt, x, y, z, vx, vy, vz);
+  const uint64_t act = lanes(true);
+  if (mode == 2) {
+    g = lane_in(drift_universal_quick(K, dt, act, x, y, z, vx, vy, vz));
+    if (!g) {
+      x = in[6 * i + 0]; y = in[6 * i + 1]; z = in[6 * i + 2];
+      vx = in[6 * i + 3]; vy = in[6 * i + 4]; vz = in[6 * i + 5];
+      g = drift_universal(K.mu, dt, x, y, z, vx, vy, vz);
+    }
+  } else {
+    g = !lane_in(drift_lanes(K, dt, kiters, ftol, quick_serves(kiters, ftol), mode == 1, act, x, y,
+                             z, vx, vy, vz, xk, sk, mk));
   }
   // a refused drift leaves the state as it was
   out[6 * i + 0] = g ? x : in[6 * i + 0]; out[6 * i + 1] = g ? y : in[6 * i + 1];

@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include "dmath.hpp"
+#include "internal.h"
 
 namespace tpm {
 
@@ -51,6 +52,93 @@ TPM_DEV void stumpff_cs(double z, double& C, double& S) {
     C = (cosh(q) - 1.0) / (-z);
     S = (sinh(q) - q) / (-z * q);
   }
+}
+
+// C(z) and S(z) by their series through k = 8, for |z| <= 1 (the first term left
+// out is below 2/20! of the sum).
+TPM_DEV void stumpff_short(double z, double& C, double& S) {
+  double c = 1.0, s = 1.0;
+#pragma unroll
+  for (int k = 8; k >= 1; --k) {
+    c = fma_(z * (-1.0 / ((2.0 * k + 1.0) * (2.0 * k + 2.0))), c, 1.0);
+    s = fma_(z * (-1.0 / ((2.0 * k + 2.0) * (2.0 * k + 3.0))), s, 1.0);
+  }
+  C = 0.5 * c;
+  S = s * (1.0 / 6.0);
+}
+
+// The universal drift where |alpha| chi^2 <= 1 and few steps suffice, for the
+// lanes of act, in step with one another.  The root is sought from the
+// fourth-order series in tau = sqrt(mu) dt / r0 (with h = sigma0/(2 r0) and
+// beta = 1 - alpha r0 the equation divided by r0 is
+// chi + h chi^2 + (beta/(6 r0)) chi^3 - (h alpha/12) chi^4 + ... = tau) by
+// Laguerre steps of order five, which reach it from almost anywhere; a lane is
+// done once a Newton step chi -> chi - d leaves less than half of
+// 2^-54 |chi|: the error is |T''| d^2 / (2 T'), with |T''| at most
+// 1.13 (|sigma0| + |beta chi|).  Lanes that are not after eight steps, or leave
+// the range, are left to drift_universal, whose bracket always ends.  Returns
+// the lanes served (the others' states mean nothing).  drift_universal starts
+// from its bracket's midpoint and needs about nine evaluations of twice the
+// length, with IEEE divisions, where two or three do here.
+TPM_DEV uint64_t drift_universal_quick(const KepConst& K, double dt, uint64_t act, double& x,
+                                       double& y, double& z, double& vx, double& vy, double& vz) {
+  const double r2 = fma_(x, x, fma_(y, y, z * z));
+  const double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
+  const double u = fma_(x, vx, fma_(y, vy, z * vz));
+  double r0, rinv;
+  sqrt_rsqrt(r2, r0, rinv);
+  const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
+  const double sig = u * K.inv_sqrt_mu;
+  const double beta = fma_(-r0, alpha, 1.0);
+  const double target = K.sqrt_mu * dt;
+  const double tau = target * rinv;
+  const double h = 0.5 * sig * rinv;
+  const double c3 = fma_(2.0 * h, h, beta * rinv * (-1.0 / 6.0));
+  const double c4 = h * fma_(5.0, fma_(h, h, -c3), alpha * (1.0 / 12.0));
+  double chi = tau * fma_(tau, fma_(tau, fma_(tau, c4, c3), -h), 1.0);
+  // the series may be far off where it does not converge; tau itself is the
+  // root's order of magnitude there
+  if (!(__builtin_fabs(chi - tau) <= 0.5 * __builtin_fabs(tau))) chi = tau;
+  double C, S, zz, c2, w1, rr;
+  uint64_t done = 0, out = 0;
+  for (int it = 0;; ++it) {
+    c2 = chi * chi;
+    zz = alpha * c2;
+    stumpff_short(zz, C, S);
+    w1 = fma_(-zz, S, 1.0);                                // 1 - z S
+    const double w0 = fma_(-zz, C, 1.0);                   // 1 - z C
+    rr = fma_(c2, C, fma_(sig * chi, w1, r0 * w0));        // T'
+    out |= ~lanes(__builtin_fabs(zz) <= 1.0);              // (NaN too)
+    if ((act & ~(done | out)) == 0 || it == 8) break;
+    const double F = fma_(chi, fma_(chi, fma_(beta * chi, S, sig * C), r0), -target);
+    const double y1 = rcp_newton(rr);
+    const double d = F * y1;
+    const double ad = __builtin_fabs(d), ac = __builtin_fabs(chi);
+    const double curv = __builtin_fabs(sig) + __builtin_fabs(beta) * ac;
+    const uint64_t now = lanes(ad <= 0x1p-20 * ac) & lanes(curv * y1 * (ad * ad) <= 0x1p-54 * ac) &
+                         lanes(rr > 0.0);
+    double step = d;
+    if (act & ~(done | out | now)) {
+      const double T2 = fma_(sig, w0, beta * chi * w1);
+      const double q = __builtin_fabs(fma_(16.0 * rr, rr, -20.0 * (F * T2)));
+      const double den = fma_(q, rsqrt(__builtin_fmax(q, 1e-300)), rr);
+      step = lane_in(now) ? d : 5.0 * F * rcp_newton(den);
+    }
+    chi = lane_in(done) ? chi : chi - step;
+    done |= now & ~out;
+  }
+  const uint64_t served = act & done & ~out;
+  if (served == 0) return 0;
+  const double c2C = c2 * C;
+  const double rri = rcp(rr);
+  const double f = fma_(-c2C, rinv, 1.0);
+  const double g = fma_(r0 * chi, w1, sig * c2C) * K.inv_sqrt_mu;
+  const double fd = -(K.sqrt_mu * (chi * w1)) * (rinv * rri);
+  const double gd = fma_(-c2C, rri, 1.0);
+  const double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
+  vx = fma_(fd, x, gd * vx); vy = fma_(fd, y, gd * vy); vz = fma_(fd, z, gd * vz);
+  x = nx; y = ny; z = nz;
+  return served;
 }
 
 // Drift (x, v) by dt about mu in universal variables.  Returns false (state
