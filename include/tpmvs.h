@@ -364,7 +364,9 @@ int tpm_ad_tangent(tpm_sim* sim, const double* d_dR0, const double* d_dV0, doubl
  * any close pair; it wins a tie with a pair seen at the end of the same step).
  * Any flag makes the call return TPM_EPLANET; the run goes on and all results
  * are still written.  A system whose planets are not all bound at the start is
- * refused with TPM_EINVAL, as in tpm_set_planets. */
+ * refused with TPM_EINVAL, as in tpm_set_planets.  The call's device memory is
+ * kept for the next one on that device where it is at most 256 MiB, and freed
+ * when the call ends where it is more. */
 int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_t* planet_off,
                         const double* mu_p, const double* rp, const double* vp,
                         const double* rcrit, const int64_t* part_off, const double* r,

@@ -224,6 +224,29 @@ hipError_t launch_jacobi_to_helio(const EphConst& E, const double* rj, const dou
 
 hipError_t launch_helio_to_jacobi(const EphConst& E, const double* h, double* j, hipStream_t st);
 
+// Fill a new set of particles: the working set w (entry i: particle idx[i], or i
+// with idx null, na of them) from the states in out.r and out.v; the records not
+// supplied; the work queue's counters of `ntiles` tiles; the active count.
+hipError_t launch_load_particles(Out out, int n, Work w, const int32_t* idx, int na, bool step,
+                                 bool reason, bool planet, uint32_t* progress, int ntiles,
+                                 unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive,
+                                 hipStream_t st);
+
+// What the host reads at the end of an integrate call, written to pinned memory
+// by the call's last kernel.
+struct RunReport {
+  unsigned long long acc;   // active particle-steps (accumulated over calls)
+  int64_t flag;             // planet event
+  int64_t ticks;            // planet map time (accumulated, 10 ns)
+  int32_t qerr, nactive;
+};
+// Adds the steps spent active in [step_begin, step_end) to *acc and writes the
+// report; `done` counts its finished workgroups (zero before and after).
+hipError_t launch_run_report(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
+                             unsigned long long* acc, uint32_t* done, const int64_t* flag,
+                             const int64_t* ticks, const int32_t* qerr, const int32_t* nactive,
+                             RunReport* rep, hipStream_t st);
+
 // Steps spent active in [step_begin, step_end) summed over particles (for a
 // backward run the range is taken in absolute order).
 hipError_t launch_active_steps(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
@@ -273,6 +296,12 @@ hipError_t launch_particle_batch(const SysDev* sys, const TileDesc* tiles, Work 
 hipError_t launch_batch_retile(Work w, const int32_t* d_nactive, int n_upper, const int32_t* psys,
                                const int32_t* sorder, int nsys, int32_t* start, int32_t* end,
                                TileDesc* tiles, int32_t* ntiles_dev, hipStream_t st);
+// Start of a run: tiles (and their number) and planet states from their pristine
+// copies, each tile's system to its particles' psys, no planet events, *acc 0.
+hipError_t launch_batch_reset(const TileDesc* tiles0, TileDesc* tiles, int ntiles,
+                              int32_t* ntiles_dev, int32_t* psys, const double* rj0,
+                              const double* vj0, double* rj, double* vj, int64_t* flag, int nsys,
+                              unsigned long long* acc, hipStream_t st);
 // Zero a work-queue item counter (a kernel, so it can sit in a captured graph).
 hipError_t launch_queue_reset(unsigned long long* ctr, hipStream_t st);
 

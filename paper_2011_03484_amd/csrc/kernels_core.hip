@@ -16,6 +16,8 @@
 //    stop occupying lanes (sec. 2.2, resync interval), by wave ballots, an LDS
 //    scan and ordered block offsets.
 //  * finalize        - scatter the active particles back to caller order.
+#include <algorithm>
+
 #include "internal.h"
 #include "particle.hpp"
 #include "planet_quad.hpp"
@@ -491,6 +493,40 @@ batch_tiles(const int32_t* __restrict__ sorder, int nsys, const int32_t* __restr
     __syncthreads();
   }
   if (threadIdx.x == 0) *ntiles_dev = carry;
+}
+
+// Workgroup b: tile b, and system b.
+__global__ void __launch_bounds__(64)
+batch_reset(const TileDesc* __restrict__ tiles0, TileDesc* __restrict__ tiles, int ntiles,
+            int32_t* ntiles_dev, int32_t* __restrict__ psys, const double* __restrict__ rj0,
+            const double* __restrict__ vj0, double* __restrict__ rj, double* __restrict__ vj,
+            int64_t* __restrict__ flag, int nsys, unsigned long long* acc) {
+  const int b = blockIdx.x, lane = threadIdx.x;
+  if (b < ntiles) {
+    const TileDesc T = tiles0[b];
+    if (lane < T.count) psys[T.first + lane] = T.sys;
+    if (lane == 0) tiles[b] = T;
+  }
+  if (b < nsys) {
+    if (lane < 3 * MAX_NP) {
+      rj[3 * MAX_NP * b + lane] = rj0[3 * MAX_NP * b + lane];
+      vj[3 * MAX_NP * b + lane] = vj0[3 * MAX_NP * b + lane];
+    }
+    if (lane == 0) flag[b] = -1;
+  }
+  if (b == 0 && lane == 0) {
+    *ntiles_dev = ntiles;
+    *acc = 0;
+  }
+}
+
+hipError_t launch_batch_reset(const TileDesc* tiles0, TileDesc* tiles, int ntiles,
+                              int32_t* ntiles_dev, int32_t* psys, const double* rj0,
+                              const double* vj0, double* rj, double* vj, int64_t* flag, int nsys,
+                              unsigned long long* acc, hipStream_t st) {
+  hipLaunchKernelGGL(batch_reset, dim3(std::max(std::max(ntiles, nsys), 1)), dim3(64), 0, st,
+                     tiles0, tiles, ntiles, ntiles_dev, psys, rj0, vj0, rj, vj, flag, nsys, acc);
+  return hipGetLastError();
 }
 
 __global__ void __launch_bounds__(64) queue_reset(unsigned long long* ctr) {
@@ -1388,28 +1424,105 @@ hipError_t launch_helio_to_jacobi_batch(const EphConst* E, const double* h, doub
   return hipGetLastError();
 }
 
-// Sum over particles of the steps spent active in [step_begin, step_end).
+// Steps particle i spent active in [step_begin, step_end) (d: its removal step).
+TPM_DEV int64_t active_steps(int64_t d, int64_t step_begin, int64_t step_end) {
+  const int64_t lo = step_begin < step_end ? step_begin : step_end;
+  const int64_t hi = step_begin < step_end ? step_end : step_begin;
+  const int64_t e = (d < 0) ? hi : (d < lo ? lo : (d > hi ? hi : d));
+  return e - lo;
+}
+
+// Their sum, one addition to *acc per workgroup (a few of them, each over many
+// particles: the additions all go to one address).  Returns on thread 0.
+TPM_DEV void add_active_steps(const int64_t* __restrict__ dstep, int n, int64_t step_begin,
+                              int64_t step_end, unsigned long long* acc) {
+  __shared__ long long part[4];
+  long long v = 0;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+    v += active_steps(dstep[i], step_begin, step_end);
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    atomicAdd(acc, (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
+}
+static int active_grid(int n) { return std::max(1, std::min((n + 1023) / 1024, 128)); }
+
 __global__ void __launch_bounds__(256)
 active_steps_kernel(const int64_t* __restrict__ dstep, int n, int64_t step_begin, int64_t step_end,
                     unsigned long long* acc) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  long long v = 0;
-  if (i < n) {
-    int64_t d = dstep[i];
-    int64_t lo = step_begin < step_end ? step_begin : step_end;
-    int64_t hi = step_begin < step_end ? step_end : step_begin;
-    int64_t e = (d < 0) ? hi : (d < lo ? lo : (d > hi ? hi : d));
-    v = e - lo;
-  }
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(acc, (unsigned long long)v);
+  add_active_steps(dstep, n, step_begin, step_end, acc);
 }
 
 hipError_t launch_active_steps(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
                                unsigned long long* acc, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(active_steps_kernel, dim3((n + 255) / 256), dim3(256), 0, st, dstep, n,
+  hipLaunchKernelGGL(active_steps_kernel, dim3(active_grid(n)), dim3(256), 0, st, dstep, n,
                      step_begin, step_end, acc);
+  return hipGetLastError();
+}
+
+// The last workgroup to finish writes the report (its loads of the sum come
+// after every workgroup's addition: each adds, then counts itself done).
+__global__ void __launch_bounds__(256)
+run_report_kernel(const int64_t* __restrict__ dstep, int n, int64_t step_begin, int64_t step_end,
+                  unsigned long long* acc, uint32_t* done, const int64_t* flag,
+                  const int64_t* ticks, const int32_t* qerr, const int32_t* nactive,
+                  RunReport* rep) {
+  add_active_steps(dstep, n, step_begin, step_end, acc);
+  if (threadIdx.x != 0) return;
+  const uint32_t k = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  if (k + 1 != gridDim.x) return;
+  __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  rep->acc = __hip_atomic_load(acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  rep->flag = *flag;
+  rep->ticks = *ticks;
+  rep->qerr = *qerr;
+  rep->nactive = *nactive;
+}
+
+hipError_t launch_run_report(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
+                             unsigned long long* acc, uint32_t* done, const int64_t* flag,
+                             const int64_t* ticks, const int32_t* qerr, const int32_t* nactive,
+                             RunReport* rep, hipStream_t st) {
+  hipLaunchKernelGGL(run_report_kernel, dim3(active_grid(n)), dim3(256), 0, st, dstep, n,
+                     step_begin, step_end, acc, done, flag, ticks, qerr, nactive, rep);
+  return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- new particles
+__global__ void __launch_bounds__(256)
+load_particles_kernel(Out out, int n, Work w, const int32_t* __restrict__ idx, int na, bool step,
+                      bool reason, bool planet, uint32_t* progress, int ntiles,
+                      unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) {
+    if (step) out.step[i] = -1;
+    if (reason) out.reason[i] = ST_ACTIVE;
+    if (planet) out.planet[i] = -1;
+  }
+  if (i < na) {
+    const int64_t k = idx ? idx[i] : i;
+    w.x[i] = out.r[3 * k]; w.y[i] = out.r[3 * k + 1]; w.z[i] = out.r[3 * k + 2];
+    w.vx[i] = out.v[3 * k]; w.vy[i] = out.v[3 * k + 1]; w.vz[i] = out.v[3 * k + 2];
+    w.slot[i] = (int32_t)k;
+    w.status[i] = ST_ACTIVE;
+  }
+  if (i < ntiles) progress[i] = 0;
+  if (i == 0) {
+    *qctr = 0;
+    *qerr = 0;
+    *d_nactive = na;
+  }
+}
+
+hipError_t launch_load_particles(Out out, int n, Work w, const int32_t* idx, int na, bool step,
+                                 bool reason, bool planet, uint32_t* progress, int ntiles,
+                                 unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive,
+                                 hipStream_t st) {
+  const int m = std::max(std::max(n, ntiles), 1);
+  hipLaunchKernelGGL(load_particles_kernel, dim3((m + 255) / 256), dim3(256), 0, st, out, n, w, idx,
+                     na, step, reason, planet, progress, ntiles, qctr, qerr, d_nactive);
   return hipGetLastError();
 }
 

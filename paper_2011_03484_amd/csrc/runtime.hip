@@ -35,6 +35,8 @@
 
 using namespace tpm;
 
+struct tpm_sim;
+
 namespace {
 
 thread_local std::string g_err;
@@ -63,7 +65,14 @@ struct DeviceStreams {
   std::mutex lock;
   hipStream_t sP = nullptr, sE = nullptr;
   hipStream_t sH = nullptr;   // encounter integrator (close-encounter hand-off), on first use
+  // Kept for the many-system calls on this device, used under the lock: a
+  // context (events, pinned memory) and one device allocation, of which at most
+  // ARENA_KEEP bytes outlive a call.
+  struct ::tpm_sim* batch = nullptr;
+  char* arena = nullptr;
+  size_t arena_cap = 0;
 };
+constexpr size_t ARENA_KEEP = size_t(256) << 20;
 
 DeviceStreams& device_streams(int dev) {
   static std::mutex m;
@@ -108,6 +117,13 @@ int64_t handoff_ring_bytes() {
   return HANDOFF_RING_BYTES;
 }
 constexpr int NCNT = 8;    // in-flight active-count readbacks
+// A simulation's small device block: planet state, flags and counters in the
+// first 512 bytes, conversion scratch (12 MAX_NP doubles) behind them.
+constexpr size_t BASE_BYTES = 512 + sizeof(double) * 12 * MAX_NP;
+// Its pinned block: counts, the report of a call's end, and staging for results
+// that are smaller than the cost of copying them one by one.
+constexpr size_t STAGE_BYTES = size_t(1) << 20;
+constexpr size_t PIN_BYTES = 256 + STAGE_BYTES;
 
 template <class T>
 void dfree(T*& p) {
@@ -135,9 +151,18 @@ struct DevScope {
 };
 
 bool finite_all(const double* p, int64_t n) {
-  for (int64_t i = 0; i < n; ++i)
-    if (!std::isfinite(p[i])) return false;
-  return true;
+  // x - x is 0 for a finite x and NaN otherwise; four sums so that the
+  // additions do not wait for one another
+  double a = 0.0, b = 0.0, c = 0.0, d = 0.0;
+  int64_t i = 0;
+  for (; i + 4 <= n; i += 4) {
+    a += p[i] - p[i];
+    b += p[i + 1] - p[i + 1];
+    c += p[i + 2] - p[i + 2];
+    d += p[i + 3] - p[i + 3];
+  }
+  for (; i < n; ++i) a += p[i] - p[i];
+  return (a + b) + (c + d) == 0.0;
 }
 
 // Planet-map constants of one system from its sorted planets (mu, initial
@@ -196,27 +221,38 @@ struct tpm_sim {
   std::vector<int> perm;                 // internal planet index -> caller index
   std::vector<double> mu_s, rcrit_s;     // internal (sorted) order
   std::vector<double> a_s;               // initial osculating semi-major axes, sorted
+  // One small device block of the simulation, allocated once (BASE_BYTES): the
+  // planets' state, the counters and the flags.
+  char* d_base = nullptr;
   double* d_rj = nullptr;                // Jacobi planet state [np][3]
   double* d_vj = nullptr;
   double* d_tmp = nullptr;               // [4][np][3] scratch for conversions
-  int64_t* d_flag = nullptr;
+  int64_t* d_flag = nullptr;             // first planet event (follows the planets' state)
   int64_t* d_stream = nullptr;           // row stream: [0] steps published, [1] map time (10 ns)
   int64_t rows_done = 0;                 // host copy of d_stream[0] between calls
   int64_t map_ticks = 0;                 // d_stream[1] at the end of the last integrate
   int64_t n = 0;
   Work work[2]{};
   int cur = 0;
+  // The particle arrays are parts of one allocation, kept from one set of
+  // particles to the next (see load_particles); the results lie together and in
+  // order (r, v, step, reason, planet).
+  char* d_part = nullptr;
+  size_t part_cap = 0;
   int32_t* d_nactive = nullptr;
   int32_t* d_scratch = nullptr;
   Out out{};
   int32_t* h_pin = nullptr;             // [0..NCNT) active counts, [16..] scratch
+  RunReport* h_rep = nullptr;           // pinned: what the device reports at a call's end
+  char* h_stage = nullptr;              // pinned: small results on their way to the caller
   hipEvent_t ev_cnt[NCNT]{};             // one per in-flight count readback
   int64_t cnt_issued = 0, cnt_seen = 0;  // readbacks issued / consumed
   unsigned long long* d_acc = nullptr;
   int n_active = 0;                      // host copy (upper bound between compactions)
   double* d_ring = nullptr;
-  int64_t ring_rows = 0;                 // rows per slot allocated
-  int64_t ring_slots = 0;                // slots allocated (NSLOT; with the hand-off, a call's chunks)
+  size_t ring_cap = 0;                   // bytes allocated (kept across calls)
+  int64_t ring_rows = 0;                 // rows per slot
+  int64_t ring_slots = 0;                // slots (NSLOT; with the hand-off, a call's chunks)
   double* d_table = nullptr;             // caller-supplied table (optional)
   int64_t table_rows = 0;
   // planet history (tpm_set_planet_history): t[nrec], r, v [nrec][np][3]
@@ -232,6 +268,8 @@ struct tpm_sim {
   unsigned long long* d_qctr = nullptr;  // work-queue item counter
   uint32_t* d_progress = nullptr;        // per-tile progress counters
   int32_t* d_qerr = nullptr;             // work-queue error flag
+  uint32_t* d_done = nullptr;            // workgroups of the closing kernel that are done
+  unsigned long long acc_seen = 0;       // *d_acc at the end of the last call
   unsigned long long q_base = 0;         // host copy of the item counter
   uint32_t q_epoch = 0;                  // host copy of the tiles' progress
   tpm_stats stats{};
@@ -279,11 +317,13 @@ struct tpm_sim {
   // the encounter stream
   std::vector<double> rrem_s;
   bool rrem_set = false;
-  EncList enc{};
+  EncList enc{};                         // parts of d_enc
+  char* d_enc = nullptr;
+  size_t enc_cap = 0;
   int32_t* d_snap = nullptr;             // [chunks of the call]
   double* d_vring = nullptr;             // [slots][vring_rows][np][3]
-  int64_t vring_rows = 0, vring_slots = 0;
-  int vring_np = -1;                     // planets the velocity ring was sized for
+  size_t vring_cap = 0;                  // bytes allocated
+  int64_t vring_rows = 0;
   int64_t snap_slots = 0;                // entries of d_snap
   hipEvent_t ev_gath[NSLOT]{}, ev_hdone[NSLOT]{};
 
@@ -294,7 +334,6 @@ struct tpm_sim {
       if (ev_hdone[k]) (void)hipEventDestroy(ev_hdone[k]);
     }
     release_ad();
-    release_diag();
     release_particles();
     release_planets();
     release_ring();
@@ -325,38 +364,24 @@ struct tpm_sim {
   }
 
   void release_handoff() {
-    dfree(enc.x); dfree(enc.y); dfree(enc.z); dfree(enc.vx); dfree(enc.vy); dfree(enc.vz);
-    dfree(enc.slot); dfree(enc.status); dfree(enc.step); dfree(enc.m); dfree(enc.Ml);
-    dfree(enc.count);
+    dfree(d_enc);
+    enc_cap = 0;
     enc = EncList{};
     dfree(d_snap);
     dfree(d_vring);
+    vring_cap = 0;
     vring_rows = 0;
-    vring_slots = 0;
-    vring_np = -1;
     snap_slots = 0;
   }
   void release_particles() {
-    release_handoff();
-    release_diag();
-    for (auto& w : work) {
-      dfree(w.x); dfree(w.y); dfree(w.z); dfree(w.vx); dfree(w.vy); dfree(w.vz);
-      dfree(w.slot); dfree(w.status);
-      w = Work{};
-    }
-    dfree(out.r); dfree(out.v); dfree(out.step); dfree(out.reason); dfree(out.planet);
-    out = Out{};
-    dfree(d_scratch); d_scratch = nullptr;
-    dfree(d_qctr); dfree(d_progress); dfree(d_qerr);
-    q_base = 0;
-    q_epoch = 0;
+    dfree(d_part);
+    part_cap = 0;
     n = 0;
     particles_set = false;
   }
   void release_planets() {
     release_diag();
-    dfree(d_rj); dfree(d_vj); dfree(d_tmp); dfree(d_table);
-    d_rj = d_vj = d_tmp = d_table = nullptr;
+    dfree(d_table);
     table_rows = 0;
     release_history();
   }
@@ -380,7 +405,7 @@ struct tpm_sim {
     const double a = hist_t0 + (double)step * dt, b = hist_t0 + (double)(step + nsteps) * dt;
     return std::min(a, b) >= hist_tmin && std::max(a, b) <= hist_tmax;
   }
-  void release_ring() { dfree(d_ring); d_ring = nullptr; ring_rows = 0; ring_slots = 0; }
+  void release_ring() { dfree(d_ring); ring_cap = 0; ring_rows = 0; ring_slots = 0; }
   void release_base() {
     // the streams belong to the device (shared); only wait for them
     if (sP) (void)hipStreamSynchronize(sP);
@@ -392,7 +417,7 @@ struct tpm_sim {
     for (auto e : {t0P, t1P, t0E, t1E}) if (e) (void)hipEventDestroy(e);
     for (auto e : kev) (void)hipEventDestroy(e);
     for (auto e : ev_cnt) if (e) (void)hipEventDestroy(e);
-    dfree(d_flag); dfree(d_stream); dfree(d_nactive); dfree(d_acc);
+    dfree(d_base);
     if (h_pin) (void)hipHostFree(h_pin);
   }
 
@@ -433,42 +458,60 @@ int ensure_handoff(tpm_sim* s, int64_t rows, int64_t slots) {
       TPM_HIP(hipEventCreateWithFlags(&s->ev_hdone[k], hipEventDisableTiming));
     }
   const size_t n = std::max<int64_t>(s->n, 1);
-  if (!s->enc.count) {
-    EncList& L = s->enc;
-    for (double** p : {&L.x, &L.y, &L.z, &L.vx, &L.vy, &L.vz})
-      TPM_HIP(hipMalloc(p, sizeof(double) * n));
-    TPM_HIP(hipMalloc(&L.slot, sizeof(int32_t) * n));
-    TPM_HIP(hipMalloc(&L.status, sizeof(int32_t) * n));
-    TPM_HIP(hipMalloc(&L.step, sizeof(int64_t) * n));
-    TPM_HIP(hipMalloc(&L.m, sizeof(int32_t) * n));
-    TPM_HIP(hipMalloc(&L.Ml, sizeof(int32_t) * n));
-    TPM_HIP(hipMalloc(&L.count, sizeof(int32_t)));
-    TPM_HIP(hipMemset(L.count, 0, sizeof(int32_t)));
-  }
-  if (s->vring_rows < rows || s->vring_slots < slots || s->vring_np != s->np || !s->d_vring ||
-      s->snap_slots < slots) {
+  auto idle = [&]() -> int {
     TPM_HIP(hipStreamSynchronize(s->sE));
     TPM_HIP(hipStreamSynchronize(s->sP));
     TPM_HIP(hipStreamSynchronize(D.sH));
+    return TPM_OK;
+  };
+  const size_t enc_bytes = 256 + (6 * 8 + 8 + 4 * 4) * n;
+  if (s->enc_cap < enc_bytes) {
+    if (int rc = idle()) return rc;
+    dfree(s->d_enc);
+    s->enc_cap = 0;
+    TPM_HIP(hipMalloc(&s->d_enc, enc_bytes));
+    s->enc_cap = enc_bytes;
+    s->enc.count = (int32_t*)s->d_enc;
+    TPM_HIP(hipMemset(s->enc.count, 0, sizeof(int32_t)));   // each call ends with it empty
+    TPM_HIP(hipDeviceSynchronize());
+  }
+  {
+    EncList& L = s->enc;
+    double* d = (double*)(s->d_enc + 256);
+    for (double** p : {&L.x, &L.y, &L.z, &L.vx, &L.vy, &L.vz}) { *p = d; d += n; }
+    L.step = (int64_t*)d;
+    int32_t* k = (int32_t*)(L.step + n);
+    for (int32_t** p : {&L.slot, &L.status, &L.m, &L.Ml}) { *p = k; k += n; }
+  }
+  const size_t vbytes = sizeof(double) * slots * rows * 3 * std::max(s->np, 1);
+  if (s->vring_cap < vbytes) {
+    if (int rc = idle()) return rc;
     dfree(s->d_vring);
+    s->vring_cap = 0;
+    TPM_HIP(hipMalloc(&s->d_vring, vbytes));
+    s->vring_cap = vbytes;
+  }
+  s->vring_rows = rows;
+  if (s->snap_slots < slots) {
+    if (int rc = idle()) return rc;
     dfree(s->d_snap);
-    TPM_HIP(hipMalloc(&s->d_vring, sizeof(double) * slots * rows * 3 * std::max(s->np, 1)));
+    s->snap_slots = 0;
     TPM_HIP(hipMalloc(&s->d_snap, sizeof(int32_t) * slots));
-    s->vring_rows = rows;
-    s->vring_slots = slots;
-    s->vring_np = s->np;
     s->snap_slots = slots;
   }
   return TPM_OK;
 }
 
+// Planet-table ring of `slots` slots of `rows` rows for the current planets.
 int ensure_ring(tpm_sim* s, int64_t rows, int64_t slots = NSLOT) {
-  if (s->ring_rows >= rows && s->ring_slots >= slots && s->d_ring) return TPM_OK;
-  TPM_HIP(hipStreamSynchronize(s->sE));
-  TPM_HIP(hipStreamSynchronize(s->sP));
-  s->release_ring();
-  size_t bytes = sizeof(double) * (size_t)slots * rows * (3 * s->np + 3);
-  TPM_HIP(hipMalloc(&s->d_ring, bytes));
+  const size_t bytes = sizeof(double) * (size_t)slots * rows * (3 * s->np + 3);
+  if (s->ring_cap < bytes) {
+    TPM_HIP(hipStreamSynchronize(s->sE));
+    TPM_HIP(hipStreamSynchronize(s->sP));
+    s->release_ring();
+    TPM_HIP(hipMalloc(&s->d_ring, bytes));
+    s->ring_cap = bytes;
+  }
   s->ring_rows = rows;
   s->ring_slots = slots;
   return TPM_OK;
@@ -497,31 +540,51 @@ void permute_table(const tpm_sim* s, const double* src, double* dst, int64_t row
 int load_particles(tpm_sim* s, int64_t n, const double* r, const double* v, const int64_t* step,
                    const int32_t* reason, const int32_t* planet) {
   TPM_HIP(hipStreamSynchronize(s->sP));
-  s->release_particles();
-  const size_t nn = (size_t)std::max<int64_t>(n, 1);
-  for (auto& w : s->work) {
-    TPM_HIP(hipMalloc(&w.x, nn * 8)); TPM_HIP(hipMalloc(&w.y, nn * 8)); TPM_HIP(hipMalloc(&w.z, nn * 8));
-    TPM_HIP(hipMalloc(&w.vx, nn * 8)); TPM_HIP(hipMalloc(&w.vy, nn * 8)); TPM_HIP(hipMalloc(&w.vz, nn * 8));
-    TPM_HIP(hipMalloc(&w.slot, nn * 4)); TPM_HIP(hipMalloc(&w.status, nn * 4));
+  s->release_diag();
+  s->particles_set = false;
+  s->n = 0;
+  const size_t nn = (size_t)std::max<int64_t>(n, 1), ntiles = (nn + 63) / 64;
+  // one allocation for all of them, kept while it fits and is not far too large
+  size_t at = 0;
+  auto part = [&](size_t bytes) {
+    const size_t o = at;
+    at += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t o_out = part(nn * 64), o_w0 = part(nn * 56), o_w1 = part(nn * 56);
+  const size_t o_idx = part(nn * 4), o_prog = part(ntiles * 4);
+  const size_t o_scr = part(sizeof(int32_t) * compact_scratch_ints((int)nn));
+  if (s->part_cap < at || s->part_cap > 8 * at + (size_t(64) << 20)) {
+    s->release_particles();
+    TPM_HIP(hipMalloc(&s->d_part, at));
+    s->part_cap = at;
   }
-  TPM_HIP(hipMalloc(&s->out.r, nn * 24)); TPM_HIP(hipMalloc(&s->out.v, nn * 24));
-  TPM_HIP(hipMalloc(&s->out.step, nn * 8)); TPM_HIP(hipMalloc(&s->out.reason, nn * 4));
-  TPM_HIP(hipMalloc(&s->out.planet, nn * 4));
-  TPM_HIP(hipMalloc(&s->d_scratch, sizeof(int32_t) * compact_scratch_ints((int)nn)));
-  const size_t ntiles = (nn + 63) / 64;
-  TPM_HIP(hipMalloc(&s->d_qctr, sizeof(unsigned long long)));
-  TPM_HIP(hipMalloc(&s->d_progress, sizeof(uint32_t) * ntiles));
-  TPM_HIP(hipMalloc(&s->d_qerr, sizeof(int32_t)));
-  TPM_HIP(hipMemset(s->d_qctr, 0, sizeof(unsigned long long)));
-  TPM_HIP(hipMemset(s->d_progress, 0, sizeof(uint32_t) * ntiles));
-  TPM_HIP(hipMemset(s->d_qerr, 0, sizeof(int32_t)));
-  TPM_HIP(hipDeviceSynchronize());   // null-stream set-up before work on the non-blocking streams
+  char* base = s->d_part;
+  s->out.r = (double*)(base + o_out);
+  s->out.v = s->out.r + 3 * nn;
+  s->out.step = (int64_t*)(s->out.v + 3 * nn);
+  s->out.reason = (int32_t*)(s->out.step + nn);
+  s->out.planet = s->out.reason + nn;
+  for (int k = 0; k < 2; ++k) {
+    double* d = (double*)(base + (k ? o_w1 : o_w0));
+    Work& w = s->work[k];
+    for (double** p : {&w.x, &w.y, &w.z, &w.vx, &w.vy, &w.vz}) { *p = d; d += nn; }
+    w.slot = (int32_t*)d;
+    w.status = w.slot + nn;
+  }
+  s->d_progress = (uint32_t*)(base + o_prog);
+  s->d_scratch = (int32_t*)(base + o_scr);
+  int32_t* d_idx = (int32_t*)(base + o_idx);
   // the working set: active particles in caller order, structure of arrays
+  // (its index list is only made where it is not simply 0, 1, ...)
+  const bool by_e = s->opt.sort_by_e && s->central_set;
   std::vector<int32_t> idx;
-  idx.reserve(n);
-  for (int64_t i = 0; i < n; ++i)
-    if (!reason || reason[i] == TPM_ACTIVE) idx.push_back((int32_t)i);
-  if (s->opt.sort_by_e && s->central_set) {
+  if (reason || by_e) {
+    idx.reserve(n);
+    for (int64_t i = 0; i < n; ++i)
+      if (!reason || reason[i] == TPM_ACTIVE) idx.push_back((int32_t)i);
+  }
+  if (by_e) {
     // Expected Newton count grows with eccentricity: bins of 0.1 in the
     // osculating e about mu0 (unbound orbits in the last bin), most eccentric
     // first, caller order within a bin.  The compaction is a stable
@@ -543,30 +606,23 @@ int load_particles(tpm_sim* s, int64_t n, const double* r, const double* v, cons
     for (int32_t i : idx) bin[i] = ebin(i);
     std::stable_sort(idx.begin(), idx.end(), [&](int32_t a, int32_t b) { return bin[a] > bin[b]; });
   }
-  const int64_t na = (int64_t)idx.size();
-  std::vector<double> col(na);
-  Work& w = s->work[0];
-  double* dst[6] = {w.x, w.y, w.z, w.vx, w.vy, w.vz};
-  for (int c = 0; c < 6; ++c) {
-    const double* src = c < 3 ? r : v;
-    for (int64_t k = 0; k < na; ++k) col[k] = src[3 * (int64_t)idx[k] + (c % 3)];
-    if (na) TPM_HIP(hipMemcpy(dst[c], col.data(), na * 8, hipMemcpyHostToDevice));
-  }
-  std::vector<int32_t> zero(n, 0), m1(n, -1);
-  std::vector<int64_t> m1l(n, -1);
-  if (na) {
-    TPM_HIP(hipMemcpy(w.slot, idx.data(), na * 4, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(w.status, zero.data(), na * 4, hipMemcpyHostToDevice));
-  }
+  const bool listed = reason || by_e;
+  const int64_t na = listed ? (int64_t)idx.size() : n;
   if (n) {
-    TPM_HIP(hipMemcpy(s->out.step, step ? step : m1l.data(), n * 8, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->out.reason, reason ? reason : zero.data(), n * 4, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->out.planet, planet ? planet : m1.data(), n * 4, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->out.r, r, n * 24, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->out.v, v, n * 24, hipMemcpyHostToDevice));
+    TPM_HIP(hipMemcpyAsync(s->out.r, r, n * 24, hipMemcpyHostToDevice, s->sP));
+    TPM_HIP(hipMemcpyAsync(s->out.v, v, n * 24, hipMemcpyHostToDevice, s->sP));
+    if (step) TPM_HIP(hipMemcpyAsync(s->out.step, step, n * 8, hipMemcpyHostToDevice, s->sP));
+    if (reason) TPM_HIP(hipMemcpyAsync(s->out.reason, reason, n * 4, hipMemcpyHostToDevice, s->sP));
+    if (planet) TPM_HIP(hipMemcpyAsync(s->out.planet, planet, n * 4, hipMemcpyHostToDevice, s->sP));
+    if (listed && na)
+      TPM_HIP(hipMemcpyAsync(d_idx, idx.data(), na * 4, hipMemcpyHostToDevice, s->sP));
   }
-  int32_t na32 = (int32_t)na;
-  TPM_HIP(hipMemcpy(s->d_nactive, &na32, 4, hipMemcpyHostToDevice));
+  TPM_HIP(launch_load_particles(s->out, (int)n, s->work[0], listed ? d_idx : nullptr, (int)na,
+                                !step, !reason, !planet, s->d_progress, (int)ntiles, s->d_qctr,
+                                s->d_qerr, s->d_nactive, s->sP));
+  TPM_HIP(hipStreamSynchronize(s->sP));       // the caller's arrays are read
+  s->q_base = 0;
+  s->q_epoch = 0;
   s->cur = 0;
   s->n = n;
   s->n_active = (int)na;
@@ -574,14 +630,122 @@ int load_particles(tpm_sim* s, int64_t n, const double* r, const double* v, cons
   return TPM_OK;
 }
 
-int check_eplanet(tpm_sim* s, int rc) {
-  if (rc != TPM_OK) return rc;
-  int64_t flag = -1;
-  TPM_HIP(hipMemcpy(&flag, s->d_flag, sizeof(flag), hipMemcpyDeviceToHost));
+int eplanet(int64_t flag) {
   if (flag == -2) return fail(TPM_EPLANET, "a planet orbit became unbound");
   if (flag >= 0)
     return fail(TPM_EPLANET, "two planets came within a mutual Hill radius at step " +
                                  std::to_string(flag));
+  return TPM_OK;
+}
+
+// The planets' Jacobi state from their heliocentric one (sorted order), with
+// the arithmetic of the device's conversion (helio_to_jacobi_batch):
+// r'_b = r_b - (sum_{k<b} mu_k r_k)/eta_{b-1}.
+void to_jacobi(const EphConst& E, const double* h, double* j) {
+  for (int b = 1; b <= E.np; ++b)
+    for (int c = 0; c < 3; ++c) {
+      double s = 0.0;
+      for (int k = 1; k < b; ++k) s = std::fma(E.mu[k], h[3 * (k - 1) + c], s);
+      j[3 * (b - 1) + c] = std::fma(-s, E.inv_eta[b - 1], h[3 * (b - 1) + c]);
+    }
+}
+
+// The planets' Jacobi state and the planet event to the device, in one copy.
+int put_planets(tpm_sim* s, const double* rj, const double* vj, int64_t flag) {
+  double block[6 * MAX_NP + 1] = {};
+  std::memcpy(block, rj, sizeof(double) * 3 * s->np);
+  std::memcpy(block + 3 * MAX_NP, vj, sizeof(double) * 3 * s->np);
+  std::memcpy(block + 6 * MAX_NP, &flag, sizeof(flag));
+  TPM_HIP(hipMemcpy(s->d_rj, block, sizeof(block), hipMemcpyHostToDevice));
+  return TPM_OK;
+}
+
+// The options of a simulation with their defaults filled in, or the reason to
+// refuse them; the device's properties.
+int check_options(tpm_options& o, bool& auto_sub, hipDeviceProp_t& prop) {
+  if (o.kepler_iters <= 0) o.kepler_iters = 5;
+  if (o.kepler_iters > 64) return fail(TPM_EINVAL, "kepler_iters > 64");
+  if (o.chunk_steps < 0 || o.resync_chunks < 0 || o.block_threads < 0 || o.sub_chunks < 0 ||
+      o.waves_per_simd < 0)
+    return fail(TPM_EINVAL, "negative option");
+  auto_sub = o.sub_chunks == 0;
+  if (auto_sub) o.sub_chunks = 64;
+  if (o.waves_per_simd > 8) return fail(TPM_EINVAL, "waves_per_simd > 8");
+  if (o.chunk_steps == 0) o.chunk_steps = 8192;
+  if (o.chunk_steps > (1 << 30)) return fail(TPM_EINVAL, "chunk_steps > 2^30");
+  if (o.resync_chunks == 0) o.resync_chunks = 1;
+  if (o.block_threads == 0) o.block_threads = 64;
+  if (o.block_threads % 64 || o.block_threads > 256)
+    return fail(TPM_EINVAL, "block_threads must be 64, 128, 192 or 256");
+  if (!(o.kepler_ftol > 0.0)) o.kepler_ftol = 1e-13;
+  if (!std::isfinite(o.r_escape)) return fail(TPM_EINVAL, "r_escape not finite");
+  if (o.handoff_substeps < 0 || o.handoff_substeps > 4096)
+    return fail(TPM_EINVAL, "handoff_substeps must be 0..4096");
+  int ndev = 0;
+  if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0)
+    return fail(TPM_EDEVICE, "no HIP device");
+  if (o.device < 0 || o.device >= ndev) return fail(TPM_EINVAL, "device ordinal out of range");
+  if (hipGetDeviceProperties(&prop, o.device) != hipSuccess)
+    return fail(TPM_EDEVICE, "hipGetDeviceProperties failed");
+  if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
+    return fail(TPM_EDEVICE, std::string("device is ") + prop.gcnArchName + ", library is built for gfx950");
+  return TPM_OK;
+}
+
+// A simulation with checked options.
+int new_sim(const tpm_options& o, bool auto_sub, const hipDeviceProp_t& prop, tpm_sim** out) {
+  TPM_HIP(hipSetDevice(o.device));
+  tpm_sim* s = new tpm_sim();
+  s->opt = o;
+  s->auto_sub = auto_sub;
+  s->ncu = prop.multiProcessorCount;
+  auto bad = [&](hipError_t e, const char* what) {
+    if (e == hipSuccess) return false;
+    fail(TPM_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+    return true;
+  };
+  {
+    DeviceStreams& D = device_streams(o.device);
+    if (bad(ensure_device_streams(D), "stream")) {
+      delete s;
+      return TPM_EDEVICE;
+    }
+    s->sP = D.sP;
+    s->sE = D.sE;
+  }
+  for (int i = 0; i < NSLOT; ++i)
+    if (bad(hipEventCreateWithFlags(&s->ev_eph[i], hipEventDisableTiming), "event") ||
+        bad(hipEventCreateWithFlags(&s->ev_done[i], hipEventDisableTiming), "event")) {
+      delete s;
+      return TPM_EDEVICE;
+    }
+  if (bad(hipEventCreate(&s->t0P), "event") || bad(hipEventCreate(&s->t1P), "event") ||
+      bad(hipEventCreate(&s->t0E), "event") || bad(hipEventCreate(&s->t1E), "event") ||
+      bad(hipMalloc(&s->d_base, BASE_BYTES), "alloc") ||
+      bad(hipMemset(s->d_base, 0, BASE_BYTES), "memset") ||
+      bad(hipStreamSynchronize(nullptr), "memset") ||
+      bad(hipHostMalloc(&s->h_pin, PIN_BYTES, hipHostMallocDefault), "pinned alloc")) {
+    delete s;
+    return TPM_EDEVICE;
+  }
+  s->h_rep = (RunReport*)((char*)s->h_pin + 128);
+  s->h_stage = (char*)s->h_pin + 256;
+  s->d_rj = (double*)s->d_base;
+  s->d_vj = s->d_rj + 3 * MAX_NP;
+  s->d_flag = (int64_t*)(s->d_vj + 3 * MAX_NP);
+  s->d_stream = s->d_flag + 1;
+  s->d_acc = (unsigned long long*)(s->d_stream + 2);
+  s->d_qctr = s->d_acc + 1;
+  s->d_nactive = (int32_t*)(s->d_qctr + 1);
+  s->d_qerr = s->d_nactive + 1;
+  s->d_done = (uint32_t*)(s->d_qerr + 1);
+  s->d_tmp = (double*)(s->d_base + 512);
+  for (int i = 0; i < NCNT; ++i)
+    if (bad(hipEventCreateWithFlags(&s->ev_cnt[i], hipEventDisableTiming), "event")) {
+    delete s;
+    return TPM_EDEVICE;
+  }
+  *out = s;
   return TPM_OK;
 }
 
@@ -618,81 +782,10 @@ int tpm_create(const tpm_options* opt, tpm_sim** out) {
   tpm_options o;
   tpm_default_options(&o);
   if (opt) o = *opt;
-  if (o.kepler_iters <= 0) o.kepler_iters = 5;
-  if (o.kepler_iters > 64) return fail(TPM_EINVAL, "kepler_iters > 64");
-  if (o.chunk_steps < 0 || o.resync_chunks < 0 || o.block_threads < 0 || o.sub_chunks < 0 ||
-      o.waves_per_simd < 0)
-    return fail(TPM_EINVAL, "negative option");
-  const bool auto_sub = o.sub_chunks == 0;
-  if (auto_sub) o.sub_chunks = 64;
-  if (o.waves_per_simd > 8) return fail(TPM_EINVAL, "waves_per_simd > 8");
-  if (o.chunk_steps == 0) o.chunk_steps = 8192;
-  if (o.chunk_steps > (1 << 30)) return fail(TPM_EINVAL, "chunk_steps > 2^30");
-  if (o.resync_chunks == 0) o.resync_chunks = 1;
-  if (o.block_threads == 0) o.block_threads = 64;
-  if (o.block_threads % 64 || o.block_threads > 256)
-    return fail(TPM_EINVAL, "block_threads must be 64, 128, 192 or 256");
-  if (!(o.kepler_ftol > 0.0)) o.kepler_ftol = 1e-13;
-  if (!std::isfinite(o.r_escape)) return fail(TPM_EINVAL, "r_escape not finite");
-  if (o.handoff_substeps < 0 || o.handoff_substeps > 4096)
-    return fail(TPM_EINVAL, "handoff_substeps must be 0..4096");
-  int ndev = 0;
-  if (hipGetDeviceCount(&ndev) != hipSuccess || ndev <= 0)
-    return fail(TPM_EDEVICE, "no HIP device");
-  if (o.device < 0 || o.device >= ndev) return fail(TPM_EINVAL, "device ordinal out of range");
+  bool auto_sub = false;
   hipDeviceProp_t prop;
-  if (hipGetDeviceProperties(&prop, o.device) != hipSuccess)
-    return fail(TPM_EDEVICE, "hipGetDeviceProperties failed");
-  if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0)
-    return fail(TPM_EDEVICE, std::string("device is ") + prop.gcnArchName + ", library is built for gfx950");
-  TPM_HIP(hipSetDevice(o.device));
-  tpm_sim* s = new tpm_sim();
-  s->opt = o;
-  s->auto_sub = auto_sub;
-  s->ncu = prop.multiProcessorCount;
-  auto bad = [&](hipError_t e, const char* what) {
-    if (e == hipSuccess) return false;
-    fail(TPM_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
-    return true;
-  };
-  {
-    DeviceStreams& D = device_streams(o.device);
-    if (bad(ensure_device_streams(D), "stream")) {
-      delete s;
-      return TPM_EDEVICE;
-    }
-    s->sP = D.sP;
-    s->sE = D.sE;
-  }
-  for (int i = 0; i < NSLOT; ++i)
-    if (bad(hipEventCreateWithFlags(&s->ev_eph[i], hipEventDisableTiming), "event") ||
-        bad(hipEventCreateWithFlags(&s->ev_done[i], hipEventDisableTiming), "event")) {
-      delete s;
-      return TPM_EDEVICE;
-    }
-  if (bad(hipEventCreate(&s->t0P), "event") || bad(hipEventCreate(&s->t1P), "event") ||
-      bad(hipEventCreate(&s->t0E), "event") || bad(hipEventCreate(&s->t1E), "event") ||
-      bad(hipMalloc(&s->d_flag, sizeof(int64_t)), "alloc") ||
-      bad(hipMalloc(&s->d_stream, 2 * sizeof(int64_t)), "alloc") ||
-      bad(hipMemset(s->d_stream, 0, 2 * sizeof(int64_t)), "memset") ||
-      bad(hipMalloc(&s->d_nactive, sizeof(int32_t)), "alloc") ||
-      bad(hipMalloc(&s->d_acc, sizeof(unsigned long long)), "alloc") ||
-      bad(hipHostMalloc(&s->h_pin, 256, hipHostMallocDefault), "pinned alloc")) {
-    delete s;
-    return TPM_EDEVICE;
-  }
-  for (int i = 0; i < NCNT; ++i)
-    if (bad(hipEventCreateWithFlags(&s->ev_cnt[i], hipEventDisableTiming), "event")) {
-    delete s;
-    return TPM_EDEVICE;
-  }
-  int64_t m1 = -1;
-  if (bad(hipMemcpy(s->d_flag, &m1, sizeof(m1), hipMemcpyHostToDevice), "memcpy")) {
-    delete s;
-    return TPM_EDEVICE;
-  }
-  *out = s;
-  return TPM_OK;
+  if (int rc = check_options(o, auto_sub, prop)) return rc;
+  return new_sim(o, auto_sub, prop, out);
 }
 
 void tpm_destroy(tpm_sim* s) {
@@ -734,7 +827,6 @@ int tpm_set_planets(tpm_sim* s, int32_t np, const double* mu, const double* r, c
   TPM_HIP(hipStreamSynchronize(s->sP));
   TPM_HIP(hipStreamSynchronize(s->sE));
   s->release_planets();
-  s->release_ring();
   s->np = np;
   s->perm.resize(np);
   std::iota(s->perm.begin(), s->perm.end(), 0);
@@ -750,20 +842,11 @@ int tpm_set_planets(tpm_sim* s, int32_t np, const double* mu, const double* r, c
     s->a_s[j] = a[c];
     for (int k = 0; k < 3; ++k) { rs[3 * j + k] = r[3 * c + k]; vs[3 * j + k] = v[3 * c + k]; }
   }
-  size_t b = sizeof(double) * 3 * std::max(np, 1);
-  TPM_HIP(hipMalloc(&s->d_rj, b));
-  TPM_HIP(hipMalloc(&s->d_vj, b));
-  TPM_HIP(hipMalloc(&s->d_tmp, 4 * b));
-  if (np > 0) {
-    TPM_HIP(hipMemcpy(s->d_tmp, rs.data(), b, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->d_tmp + 3 * np, vs.data(), b, hipMemcpyHostToDevice));
-    EphConst E = s->eph();
-    TPM_HIP(launch_helio_to_jacobi(E, s->d_tmp, s->d_rj, s->sE));
-    TPM_HIP(launch_helio_to_jacobi(E, s->d_tmp + 3 * np, s->d_vj, s->sE));
-    TPM_HIP(hipStreamSynchronize(s->sE));
-  }
-  int64_t m1 = -1;
-  TPM_HIP(hipMemcpy(s->d_flag, &m1, sizeof(m1), hipMemcpyHostToDevice));
+  double rj[3 * MAX_NP] = {}, vj[3 * MAX_NP] = {};
+  const EphConst E = s->eph();
+  to_jacobi(E, rs.data(), rj);
+  to_jacobi(E, vs.data(), vj);
+  if (int rc = put_planets(s, rj, vj, -1)) return rc;
   s->step = 0;
   s->planets_set = true;
   s->rrem_set = false;
@@ -968,7 +1051,7 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   s->stats.chunks = 0;
   s->stats.compactions = 0;
   TPM_HIP(hipEventRecord(s->t0P, s->sP));
-  TPM_HIP(hipEventRecord(s->t0E, s->sE));
+  if (!live) TPM_HIP(hipEventRecord(s->t0E, s->sE));
   // A history's rows are enqueued up to NSLOT-1 chunks ahead of the particles.
   int64_t hist_next = 0;
   auto enqueue_hist = [&](int64_t upto) -> int {
@@ -1205,49 +1288,37 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
     TPM_HIP(hipMemcpyAsync(s->h_pin + 18, s->enc.count, sizeof(int32_t), hipMemcpyDeviceToHost,
                            s->sP));
     TPM_HIP(launch_handoff_merge(s->enc, (int)s->n, s->work[s->cur], s->d_nactive, s->sP));
-    TPM_HIP(hipMemcpyAsync(s->h_pin + 19, s->d_nactive, sizeof(int32_t), hipMemcpyDeviceToHost,
-                           s->sP));
   }
   TPM_HIP(hipEventRecord(s->t1P, s->sP));
-  TPM_HIP(hipEventRecord(s->t1E, s->sE));
-  TPM_HIP(hipStreamSynchronize(s->sE));
+  if (!live) TPM_HIP(hipEventRecord(s->t1E, s->sE));
+  // active particle-steps of this call, and everything the host wants to know
+  TPM_HIP(launch_run_report(s->out.step, (int)s->n, step_begin, step_begin + nsteps, s->d_acc,
+                            s->d_done, s->d_flag, s->d_stream + 1, s->d_qerr, s->d_nactive,
+                            s->h_rep, s->sP));
+  if (!live) TPM_HIP(hipStreamSynchronize(s->sE));
   TPM_HIP(hipStreamSynchronize(s->sP));
   {
-    int rc = poll_counts();
-    if (rc) return rc;
-    rc = fire(true, SIZE_MAX);
+    int rc = fire(true, SIZE_MAX);
     if (rc) return rc;
   }
-  s->stats.handoffs = 0;
-  if (ho && nchunks > 0) {
-    s->stats.handoffs = s->h_pin[18];
-    s->n_active = s->h_pin[19];
-  }
-  {
-    int32_t qerr = 0;
-    TPM_HIP(hipMemcpy(&qerr, s->d_qerr, sizeof(qerr), hipMemcpyDeviceToHost));
-    if (qerr) return fail(TPM_EDEVICE, "particle work queue: a wait exceeded its limit");
-  }
+  const RunReport rep = *s->h_rep;
+  s->cnt_seen = s->cnt_issued;
+  s->n_active = rep.nactive;
+  s->stats.handoffs = ho && nchunks > 0 ? s->h_pin[18] : 0;
+  if (rep.qerr) return fail(TPM_EDEVICE, "particle work queue: a wait exceeded its limit");
   s->step += nsteps;
   s->hist_dt = dt;
   float msP = 0.f, msE = 0.f;
   TPM_HIP(hipEventElapsedTime(&msP, s->t0P, s->t1P));
   if (live) {
     s->rows_done += nsteps;
-    int64_t ticks = 0;
-    TPM_HIP(hipMemcpy(&ticks, s->d_stream + 1, sizeof(ticks), hipMemcpyDeviceToHost));
-    msE = (float)((double)(ticks - s->map_ticks) * 1e-5);
-    s->map_ticks = ticks;
+    msE = (float)((double)(rep.ticks - s->map_ticks) * 1e-5);
+    s->map_ticks = rep.ticks;
   } else {
     TPM_HIP(hipEventElapsedTime(&msE, s->t0E, s->t1E));
   }
-  // active particle-steps of this call
-  TPM_HIP(hipMemsetAsync(s->d_acc, 0, sizeof(unsigned long long), s->sP));
-  TPM_HIP(launch_active_steps(s->out.step, (int)s->n, step_begin, s->step, s->d_acc, s->sP));
-  unsigned long long acc = 0;
-  TPM_HIP(hipMemcpyAsync(s->h_pin + 16, s->d_acc, sizeof(acc), hipMemcpyDeviceToHost, s->sP));
-  TPM_HIP(hipStreamSynchronize(s->sP));
-  std::memcpy(&acc, s->h_pin + 16, sizeof(acc));
+  const unsigned long long acc = rep.acc - s->acc_seen;
+  s->acc_seen = rep.acc;
   auto w1 = std::chrono::steady_clock::now();
   double kms = 0.0;
   if (timed)
@@ -1261,7 +1332,7 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   s->stats.ephemeris_ms = msE;
   s->stats.wall_ms = std::chrono::duration<double, std::milli>(w1 - w0).count();
   s->stats.active_particle_steps = (int64_t)acc;
-  return check_eplanet(s, TPM_OK);
+  return eplanet(rep.flag);
 }
 
 int tpm_get_particles(tpm_sim* s, double* r, double* v, int64_t* deact_step, int32_t* reason,
@@ -1273,16 +1344,27 @@ int tpm_get_particles(tpm_sim* s, double* r, double* v, int64_t* deact_step, int
   const int64_t n = s->n;
   if (n == 0) return TPM_OK;
   TPM_HIP(launch_finalize(s->work[s->cur], s->d_nactive, s->n_active, s->out, s->sP));
-  TPM_HIP(hipStreamSynchronize(s->sP));
-  if (r) TPM_HIP(hipMemcpy(r, s->out.r, n * 24, hipMemcpyDeviceToHost));
-  if (v) TPM_HIP(hipMemcpy(v, s->out.v, n * 24, hipMemcpyDeviceToHost));
-  if (deact_step) TPM_HIP(hipMemcpy(deact_step, s->out.step, n * 8, hipMemcpyDeviceToHost));
-  if (reason) TPM_HIP(hipMemcpy(reason, s->out.reason, n * 4, hipMemcpyDeviceToHost));
-  if (planet) {
-    TPM_HIP(hipMemcpy(planet, s->out.planet, n * 4, hipMemcpyDeviceToHost));
+  if ((size_t)n * 64 <= STAGE_BYTES) {
+    // all of it in one copy (the results lie together), then to the caller
+    TPM_HIP(hipMemcpyAsync(s->h_stage, s->out.r, n * 64, hipMemcpyDeviceToHost, s->sP));
+    TPM_HIP(hipStreamSynchronize(s->sP));
+    const char* h = s->h_stage;
+    if (r) std::memcpy(r, h, n * 24);
+    if (v) std::memcpy(v, h + n * 24, n * 24);
+    if (deact_step) std::memcpy(deact_step, h + n * 48, n * 8);
+    if (reason) std::memcpy(reason, h + n * 56, n * 4);
+    if (planet) std::memcpy(planet, h + n * 60, n * 4);
+  } else {
+    TPM_HIP(hipStreamSynchronize(s->sP));
+    if (r) TPM_HIP(hipMemcpy(r, s->out.r, n * 24, hipMemcpyDeviceToHost));
+    if (v) TPM_HIP(hipMemcpy(v, s->out.v, n * 24, hipMemcpyDeviceToHost));
+    if (deact_step) TPM_HIP(hipMemcpy(deact_step, s->out.step, n * 8, hipMemcpyDeviceToHost));
+    if (reason) TPM_HIP(hipMemcpy(reason, s->out.reason, n * 4, hipMemcpyDeviceToHost));
+    if (planet) TPM_HIP(hipMemcpy(planet, s->out.planet, n * 4, hipMemcpyDeviceToHost));
+  }
+  if (planet)
     for (int64_t i = 0; i < n; ++i)
       if (planet[i] >= 0) planet[i] = s->perm[planet[i]];
-  }
   return TPM_OK;
 }
 
@@ -1517,7 +1599,6 @@ int tpm_set_state(tpm_sim* s, const void* buf, int64_t size) {
   TPM_HIP(hipStreamSynchronize(s->sP));
   TPM_HIP(hipStreamSynchronize(s->sE));
   s->release_planets();
-  s->release_ring();
   s->ad.valid = false;
   s->mu0 = h.mu0;
   s->central_set = true;
@@ -1528,15 +1609,7 @@ int tpm_set_state(tpm_sim* s, const void* buf, int64_t size) {
   s->mu_s.assign(h.mu, h.mu + np);
   s->rcrit_s.assign(h.rcrit, h.rcrit + np);
   s->a_s.assign(h.a, h.a + np);
-  const size_t b = sizeof(double) * 3 * std::max(np, 1);
-  TPM_HIP(hipMalloc(&s->d_rj, b));
-  TPM_HIP(hipMalloc(&s->d_vj, b));
-  TPM_HIP(hipMalloc(&s->d_tmp, 4 * b));
-  if (np > 0) {
-    TPM_HIP(hipMemcpy(s->d_rj, h.rj, sizeof(double) * 3 * np, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(s->d_vj, h.vj, sizeof(double) * 3 * np, hipMemcpyHostToDevice));
-  }
-  TPM_HIP(hipMemcpy(s->d_flag, &h.flag, sizeof(int64_t), hipMemcpyHostToDevice));
+  if (int rc = put_planets(s, h.rj, h.vj, h.flag)) return rc;
   s->step = h.step;
   s->planets_set = true;
   s->rrem_set = false;
@@ -1912,6 +1985,7 @@ int tpm_ad_tangent(tpm_sim* s, const double* d_dR0, const double* d_dV0, double*
 // particles, planet-count histogram, fixed options).
 namespace {
 
+// Device arrays of one many-system call: parts of the device's arena.
 struct BatchBuffers {
   EphConst* E = nullptr;
   SysDev* sys = nullptr;
@@ -1936,22 +2010,12 @@ struct BatchBuffers {
   uint32_t* progress = nullptr;
   int32_t* qerr = nullptr;
   unsigned long long* acc = nullptr;
-  // pristine copies for the autotuner's trial runs
+  // pristine copies, from which every trial run and the run itself start
   double* rj0 = nullptr;
   double* vj0 = nullptr;
-  double* st0 = nullptr;
-  ~BatchBuffers() {
-    dfree(E); dfree(sys); dfree(tiles); dfree(rj); dfree(vj); dfree(dt); dfree(ring_off);
-    dfree(flag); dfree(ring);
-    for (Work* p : {&w, &w2}) {
-      dfree(p->x); dfree(p->y); dfree(p->z); dfree(p->vx); dfree(p->vy); dfree(p->vz);
-      dfree(p->slot); dfree(p->status);
-    }
-    dfree(psys); dfree(sorder); dfree(sbeg); dfree(send); dfree(ntiles_dev); dfree(cscratch);
-    dfree(out.r); dfree(out.v); dfree(out.step); dfree(out.reason); dfree(out.planet);
-    dfree(nall); dfree(ctr); dfree(progress); dfree(qerr); dfree(acc);
-    dfree(rj0); dfree(vj0); dfree(st0);
-  }
+  TileDesc* tiles0 = nullptr;
+  double* r0 = nullptr;       // [n][3]
+  double* v0 = nullptr;
 };
 
 struct TuneChoice {
@@ -2011,20 +2075,26 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
   static const int kBlocks[] = {64, 256};
   const int Kmax = o.chunk_steps > 0 ? o.chunk_steps : 2048;
 
-  // a device context via the single-system object (streams, events, device)
+  // the device's context for these calls (streams, events, pinned memory)
   tpm_options so = o;
   so.chunk_steps = Kmax;
   so.block_threads = 64;
   so.resync_chunks = 1;
-  tpm_sim* ctx = nullptr;
-  {
-    int rc = tpm_create(&so, &ctx);
-    if (rc) return rc;
-  }
-  std::unique_ptr<tpm_sim, void (*)(tpm_sim*)> guard(ctx, tpm_destroy);
-  std::lock_guard<std::mutex> dev_lock(device_streams(o.device).lock);
+  bool auto_sub = false;
+  hipDeviceProp_t prop;
+  if (int rc = check_options(so, auto_sub, prop)) return rc;
+  TPM_HIP(hipSetDevice(o.device));
+  DeviceStreams& D = device_streams(o.device);
+  std::lock_guard<std::mutex> dev_lock(D.lock);
+  if (!D.batch)
+    if (int rc = new_sim(so, auto_sub, prop, &D.batch)) return rc;
+  tpm_sim* const ctx = D.batch;
   BatchBuffers B;
-  const int64_t slot_rows = Kmax + 1;   // ring rows per slot (the longest candidate chunk)
+  // ring: rows per slot of the longest candidate chunk, slots for the chunks in
+  // flight (the shortest candidate's number of chunks, if that is fewer)
+  const int Kmin = o.chunk_steps > 0 ? o.chunk_steps : kChunks[0];
+  const int64_t slot_rows = std::min<int64_t>(Kmax, nsteps) + 1;
+  const int nslot = (int)std::max<int64_t>(1, std::min<int64_t>(NSLOT, (nsteps + Kmin - 1) / Kmin));
 
   // ---- per-system set-up (host: ordering and constants; device: Jacobi)
   std::vector<EphConst> E(nsys);
@@ -2064,7 +2134,7 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
     E[s] = make_eph(mu0[s], np, ms.data(), as.data());
     ring_off[s] = ring_total;
     d.ring_off = ring_total;
-    ring_total += (int64_t)NSLOT * slot_rows * (3 * np + 3);
+    ring_total += (int64_t)nslot * slot_rows * (3 * np + 3);
     hist[np]++;
   }
   // tiles of 64 particles of one system, largest planet count first
@@ -2075,115 +2145,121 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
   std::stable_sort(tiles.begin(), tiles.end(),
                    [&](const TileDesc& x, const TileDesc& y) { return S[x.sys].np > S[y.sys].np; });
   const int ntiles = (int)tiles.size();
-  std::vector<int32_t> sorder(nsys), psys(std::max<int64_t>(n, 1), 0);
+  std::vector<int32_t> sorder(nsys);
   std::iota(sorder.begin(), sorder.end(), 0);
   std::stable_sort(sorder.begin(), sorder.end(), [&](int x, int y) { return S[x].np > S[y].np; });
-  for (int s = 0; s < nsys; ++s)
-    for (int64_t i = part_off[s]; i < part_off[s + 1]; ++i) psys[i] = s;
 
-  // ---- device buffers
+  // ---- device arrays, laid out in the arena; what the host fills first, in one
+  // block that goes over in one copy
   const size_t nn = (size_t)std::max<int64_t>(n, 1);
   const size_t ps = (size_t)3 * MAX_NP * nsys;
-  TPM_HIP(hipMalloc(&B.E, sizeof(EphConst) * nsys));
-  TPM_HIP(hipMalloc(&B.sys, sizeof(SysDev) * nsys));
-  TPM_HIP(hipMalloc(&B.tiles, sizeof(TileDesc) * std::max(ntiles, 1)));
-  TPM_HIP(hipMalloc(&B.rj, sizeof(double) * ps));
-  TPM_HIP(hipMalloc(&B.vj, sizeof(double) * ps));
-  TPM_HIP(hipMalloc(&B.rj0, sizeof(double) * ps));
-  TPM_HIP(hipMalloc(&B.vj0, sizeof(double) * ps));
-  TPM_HIP(hipMalloc(&B.dt, sizeof(double) * nsys));
-  TPM_HIP(hipMalloc(&B.ring_off, sizeof(int64_t) * nsys));
-  TPM_HIP(hipMalloc(&B.flag, sizeof(int64_t) * nsys));
-  TPM_HIP(hipMalloc(&B.ring, sizeof(double) * std::max<int64_t>(ring_total, 1)));
-  for (Work* W : {&B.w, &B.w2}) {
-    for (double** p : {&W->x, &W->y, &W->z, &W->vx, &W->vy, &W->vz}) TPM_HIP(hipMalloc(p, nn * 8));
-    TPM_HIP(hipMalloc(&W->slot, nn * 4));
-    TPM_HIP(hipMalloc(&W->status, nn * 4));
+  const size_t nt = (size_t)std::max(ntiles, 1);
+  size_t at = 0;
+  auto part = [&](size_t bytes) {
+    const size_t o_ = at;
+    at += (bytes + 255) / 256 * 256;
+    return o_;
+  };
+  const size_t o_E = part(sizeof(EphConst) * nsys), o_sys = part(sizeof(SysDev) * nsys);
+  const size_t o_t0 = part(sizeof(TileDesc) * nt), o_so = part(4 * (size_t)nsys);
+  const size_t o_dt = part(8 * (size_t)nsys), o_ro = part(8 * (size_t)nsys);
+  const size_t o_h = part(8 * ps), o_hv = part(8 * ps);
+  const size_t filled = at;
+  const size_t o_rj0 = part(8 * ps), o_vj0 = part(8 * ps), o_rj = part(8 * ps), o_vj = part(8 * ps);
+  const size_t o_t = part(sizeof(TileDesc) * nt), o_flag = part(8 * (size_t)nsys);
+  const size_t o_sb = part(4 * (size_t)nsys), o_se = part(4 * (size_t)nsys);
+  const size_t o_r0 = part(nn * 48), o_out = part(nn * 64), o_w = part(nn * 56), o_w2 = part(nn * 56);
+  const size_t o_psys = part(nn * 4), o_prog = part(4 * nt);
+  const size_t o_scr = part(sizeof(int32_t) * compact_scratch_ints((int)nn)), o_misc = part(256);
+  const size_t o_ring = part(8 * (size_t)std::max<int64_t>(ring_total, 1));
+  if (D.arena_cap < at) {
+    TPM_HIP(hipStreamSynchronize(ctx->sP));
+    TPM_HIP(hipStreamSynchronize(ctx->sE));
+    dfree(D.arena);
+    D.arena_cap = 0;
+    TPM_HIP(hipMalloc(&D.arena, at));
+    D.arena_cap = at;
   }
-  TPM_HIP(hipMalloc(&B.psys, nn * 4));
-  TPM_HIP(hipMalloc(&B.sorder, sizeof(int32_t) * nsys));
-  TPM_HIP(hipMalloc(&B.sbeg, sizeof(int32_t) * nsys));
-  TPM_HIP(hipMalloc(&B.send, sizeof(int32_t) * nsys));
-  TPM_HIP(hipMalloc(&B.ntiles_dev, sizeof(int32_t)));
-  TPM_HIP(hipMalloc(&B.cscratch, sizeof(int32_t) * compact_scratch_ints((int)nn)));
-  TPM_HIP(hipMemcpy(B.psys, psys.data(), nn * 4, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemcpy(B.sorder, sorder.data(), sizeof(int32_t) * nsys, hipMemcpyHostToDevice));
-  TPM_HIP(hipMalloc(&B.out.r, nn * 24));
-  TPM_HIP(hipMalloc(&B.out.v, nn * 24));
-  TPM_HIP(hipMalloc(&B.out.step, nn * 8));
-  TPM_HIP(hipMalloc(&B.out.reason, nn * 4));
-  TPM_HIP(hipMalloc(&B.out.planet, nn * 4));
-  TPM_HIP(hipMalloc(&B.st0, nn * 6 * 8));
-  TPM_HIP(hipMalloc(&B.nall, sizeof(int32_t)));
-  TPM_HIP(hipMalloc(&B.ctr, sizeof(unsigned long long)));
-  TPM_HIP(hipMalloc(&B.progress, sizeof(uint32_t) * std::max(ntiles, 1)));
-  TPM_HIP(hipMalloc(&B.qerr, sizeof(int32_t)));
-  TPM_HIP(hipMalloc(&B.acc, sizeof(unsigned long long)));
-  TPM_HIP(hipMemcpy(B.E, E.data(), sizeof(EphConst) * nsys, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemcpy(B.sys, S.data(), sizeof(SysDev) * nsys, hipMemcpyHostToDevice));
-  if (ntiles) TPM_HIP(hipMemcpy(B.tiles, tiles.data(), sizeof(TileDesc) * ntiles, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemcpy(B.dt, dts.data(), sizeof(double) * nsys, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemcpy(B.ring_off, ring_off.data(), sizeof(int64_t) * nsys, hipMemcpyHostToDevice));
-  {
-    std::vector<int64_t> m1(nsys, -1);
-    TPM_HIP(hipMemcpy(B.flag, m1.data(), sizeof(int64_t) * nsys, hipMemcpyHostToDevice));
-  }
-  // planets: heliocentric -> Jacobi on the device (staged through rj0 / vj0)
-  TPM_HIP(hipMemcpy(B.rj0, hpos.data(), sizeof(double) * ps, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemcpy(B.vj0, hvel.data(), sizeof(double) * ps, hipMemcpyHostToDevice));
-  TPM_HIP(hipMemset(B.rj, 0, sizeof(double) * ps));
-  TPM_HIP(hipMemset(B.vj, 0, sizeof(double) * ps));
-  TPM_HIP(hipDeviceSynchronize());   // null-stream set-up before work on the non-blocking streams
-  TPM_HIP(launch_helio_to_jacobi_batch(B.E, B.rj0, B.rj, nsys, ctx->sP));
-  TPM_HIP(launch_helio_to_jacobi_batch(B.E, B.vj0, B.vj, nsys, ctx->sP));
-  TPM_HIP(hipStreamSynchronize(ctx->sP));
-  TPM_HIP(hipMemcpy(B.rj0, B.rj, sizeof(double) * ps, hipMemcpyDeviceToDevice));
-  TPM_HIP(hipMemcpy(B.vj0, B.vj, sizeof(double) * ps, hipMemcpyDeviceToDevice));
-  // particles: caller AoS -> SoA (global order = caller order)
-  {
-    std::vector<double> col(n);
-    double* dst[6] = {B.w.x, B.w.y, B.w.z, B.w.vx, B.w.vy, B.w.vz};
-    for (int c = 0; c < 6; ++c) {
-      const double* src = c < 3 ? r : v;
-      for (int64_t i = 0; i < n; ++i) col[i] = src[3 * i + (c % 3)];
-      if (n) {
-        TPM_HIP(hipMemcpy(dst[c], col.data(), n * 8, hipMemcpyHostToDevice));
-        TPM_HIP(hipMemcpy(B.st0 + (size_t)c * n, col.data(), n * 8, hipMemcpyHostToDevice));
-      }
+  struct Keep {          // an arena above the bound goes back when the call ends
+    DeviceStreams& D;
+    ~Keep() {
+      if (D.arena_cap <= ARENA_KEEP) return;
+      (void)hipStreamSynchronize(D.sP);
+      (void)hipStreamSynchronize(D.sE);
+      dfree(D.arena);
+      D.arena_cap = 0;
     }
-    std::vector<int32_t> idx(n), zero(n, 0);
-    std::iota(idx.begin(), idx.end(), 0);
+  } keep{D};
+  char* const base = D.arena;
+  B.E = (EphConst*)(base + o_E);
+  B.sys = (SysDev*)(base + o_sys);
+  B.tiles0 = (TileDesc*)(base + o_t0);
+  B.tiles = (TileDesc*)(base + o_t);
+  B.sorder = (int32_t*)(base + o_so);
+  B.dt = (double*)(base + o_dt);
+  B.ring_off = (int64_t*)(base + o_ro);
+  B.rj0 = (double*)(base + o_rj0);
+  B.vj0 = (double*)(base + o_vj0);
+  B.rj = (double*)(base + o_rj);
+  B.vj = (double*)(base + o_vj);
+  B.flag = (int64_t*)(base + o_flag);
+  B.sbeg = (int32_t*)(base + o_sb);
+  B.send = (int32_t*)(base + o_se);
+  B.r0 = (double*)(base + o_r0);
+  B.v0 = B.r0 + 3 * nn;
+  B.out.r = (double*)(base + o_out);
+  B.out.v = B.out.r + 3 * nn;
+  B.out.step = (int64_t*)(B.out.v + 3 * nn);
+  B.out.reason = (int32_t*)(B.out.step + nn);
+  B.out.planet = B.out.reason + nn;
+  for (int k = 0; k < 2; ++k) {
+    Work& W = k ? B.w2 : B.w;
+    double* d = (double*)(base + (k ? o_w2 : o_w));
+    for (double** p : {&W.x, &W.y, &W.z, &W.vx, &W.vy, &W.vz}) { *p = d; d += nn; }
+    W.slot = (int32_t*)d;
+    W.status = W.slot + nn;
+  }
+  B.psys = (int32_t*)(base + o_psys);
+  B.progress = (uint32_t*)(base + o_prog);
+  B.cscratch = (int32_t*)(base + o_scr);
+  B.ring = (double*)(base + o_ring);
+  B.ctr = (unsigned long long*)(base + o_misc);
+  B.acc = B.ctr + 1;
+  B.nall = (int32_t*)(B.acc + 1);
+  B.ntiles_dev = B.nall + 1;
+  B.qerr = B.nall + 2;
+  {
+    std::vector<char> block(filled);
+    auto fill = [&](size_t o_, const void* src, size_t bytes) {
+      if (bytes) std::memcpy(block.data() + o_, src, bytes);
+    };
+    fill(o_E, E.data(), sizeof(EphConst) * nsys);
+    fill(o_sys, S.data(), sizeof(SysDev) * nsys);
+    fill(o_t0, tiles.data(), sizeof(TileDesc) * ntiles);
+    fill(o_so, sorder.data(), 4 * (size_t)nsys);
+    fill(o_dt, dts.data(), 8 * (size_t)nsys);
+    fill(o_ro, ring_off.data(), 8 * (size_t)nsys);
+    fill(o_h, hpos.data(), 8 * ps);
+    fill(o_hv, hvel.data(), 8 * ps);
+    TPM_HIP(hipMemcpyAsync(base, block.data(), filled, hipMemcpyHostToDevice, ctx->sP));
     if (n) {
-      TPM_HIP(hipMemcpy(B.w.slot, idx.data(), n * 4, hipMemcpyHostToDevice));
-      TPM_HIP(hipMemcpy(B.w.status, zero.data(), n * 4, hipMemcpyHostToDevice));
+      TPM_HIP(hipMemcpyAsync(B.r0, r, n * 24, hipMemcpyHostToDevice, ctx->sP));
+      TPM_HIP(hipMemcpyAsync(B.v0, v, n * 24, hipMemcpyHostToDevice, ctx->sP));
     }
+    // planets: heliocentric -> Jacobi on the device
+    TPM_HIP(launch_helio_to_jacobi_batch(B.E, (double*)(base + o_h), B.rj0, nsys, ctx->sP));
+    TPM_HIP(launch_helio_to_jacobi_batch(B.E, (double*)(base + o_hv), B.vj0, nsys, ctx->sP));
+    TPM_HIP(hipStreamSynchronize(ctx->sP));
   }
-  const int32_t n32 = (int32_t)n;
-  TPM_HIP(hipMemcpy(B.nall, &n32, 4, hipMemcpyHostToDevice));
-  std::vector<int32_t> slot0(std::max<int64_t>(n, 1));
-  std::iota(slot0.begin(), slot0.end(), 0);
+  // initial particle, planet and queue state (outside any captured graph)
   auto reset_run = [&]() -> int {
-    // initial particle, planet and queue state (outside any captured graph)
-    double* dst[6] = {B.w.x, B.w.y, B.w.z, B.w.vx, B.w.vy, B.w.vz};
-    for (int c = 0; c < 6; ++c)
-      if (n) TPM_HIP(hipMemcpy(dst[c], B.st0 + (size_t)c * n, n * 8, hipMemcpyDeviceToDevice));
-    if (n) TPM_HIP(hipMemset(B.w.status, 0, n * 4));
-    if (n) TPM_HIP(hipMemcpy(B.w.slot, slot0.data(), n * 4, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(B.nall, &n32, 4, hipMemcpyHostToDevice));
-    if (ntiles) TPM_HIP(hipMemcpy(B.tiles, tiles.data(), sizeof(TileDesc) * ntiles, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(B.ntiles_dev, &ntiles, 4, hipMemcpyHostToDevice));
-    TPM_HIP(hipMemcpy(B.rj, B.rj0, sizeof(double) * ps, hipMemcpyDeviceToDevice));
-    TPM_HIP(hipMemcpy(B.vj, B.vj0, sizeof(double) * ps, hipMemcpyDeviceToDevice));
-    TPM_HIP(hipMemset(B.ctr, 0, sizeof(unsigned long long)));
-    TPM_HIP(hipMemset(B.progress, 0, sizeof(uint32_t) * std::max(ntiles, 1)));
-    TPM_HIP(hipMemset(B.qerr, 0, sizeof(int32_t)));
-    std::vector<int64_t> m1(std::max<int64_t>(n, nsys), -1);
-    TPM_HIP(hipMemcpy(B.flag, m1.data(), sizeof(int64_t) * nsys, hipMemcpyHostToDevice));
-    if (n) {
-      TPM_HIP(hipMemcpy(B.out.step, m1.data(), sizeof(int64_t) * n, hipMemcpyHostToDevice));
-      TPM_HIP(hipMemset(B.out.reason, 0, n * 4));
-    }
-    TPM_HIP(hipDeviceSynchronize());
+    Out in = B.out;
+    in.r = B.r0;
+    in.v = B.v0;
+    TPM_HIP(launch_load_particles(in, (int)n, B.w, nullptr, (int)n, true, true, true, B.progress,
+                                  (int)nt, B.ctr, B.qerr, B.nall, ctx->sP));
+    TPM_HIP(launch_batch_reset(B.tiles0, B.tiles, ntiles, B.ntiles_dev, B.psys, B.rj0, B.vj0, B.rj,
+                               B.vj, B.flag, nsys, B.acc, ctx->sP));
     return TPM_OK;
   };
 
@@ -2206,8 +2282,8 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
     TPM_HIP(hipStreamWaitEvent(ctx->sE, ctx->ev_cnt[0], 0));
     for (int64_t c = 0; c < chunks; ++c) {
       const int ks = (int)std::min<int64_t>(K, nsteps - c * K);
-      const int slot = (int)(c % NSLOT);
-      if (c >= NSLOT) TPM_HIP(hipStreamWaitEvent(ctx->sE, ctx->ev_done[slot], 0));
+      const int slot = (int)(c % nslot);
+      if (c >= nslot) TPM_HIP(hipStreamWaitEvent(ctx->sE, ctx->ev_done[slot], 0));
       TPM_HIP(launch_ephemeris_batch(B.E, B.rj, B.vj, B.ring, B.ring_off, slot, slot_rows, nsys, ks,
                                      B.dt, c * K, B.flag, ctx->sE));
       TPM_HIP(hipEventRecord(ctx->ev_eph[slot], ctx->sE));
@@ -2256,8 +2332,6 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
                     o.resync_chunks > 0 ? o.resync_chunks : 1};
   int cur = 0;
   if (autotune && nsteps > 0 && ntiles > 0) {
-    hipDeviceProp_t prop;
-    TPM_HIP(hipGetDeviceProperties(&prop, o.device));
     std::string key = std::string(prop.gcnArchName) + "/" + std::to_string(nsys) + "/" +
                       std::to_string(n) + "/" + std::to_string(nsteps) + "/" +
                       std::to_string(o.block_threads) + "/" + std::to_string(o.chunk_steps) + "/" +
@@ -2386,21 +2460,27 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
   auto w1 = std::chrono::steady_clock::now();
   float run_ms = 0.f;
   TPM_HIP(hipEventElapsedTime(&run_ms, ctx->t0P, ctx->t1P));
-  {
-    int32_t qerr = 0;
-    TPM_HIP(hipMemcpy(&qerr, B.qerr, sizeof(qerr), hipMemcpyDeviceToHost));
-    if (qerr) return fail(TPM_EDEVICE, "particle work queue: a wait exceeded its limit");
-  }
   // ---- results
   TPM_HIP(launch_finalize(cur ? B.w2 : B.w, B.nall, (int)n, B.out, ctx->sP));
-  TPM_HIP(hipMemsetAsync(B.acc, 0, sizeof(unsigned long long), ctx->sP));
-  TPM_HIP(launch_active_steps(B.out.step, (int)n, 0, nsteps, B.acc, ctx->sP));
+  TPM_HIP(launch_run_report(B.out.step, (int)n, 0, nsteps, B.acc, ctx->d_done, ctx->d_flag,
+                            ctx->d_stream + 1, B.qerr, B.nall, ctx->h_rep, ctx->sP));
+  std::vector<int64_t> flags(nsys);
+  TPM_HIP(hipMemcpyAsync(flags.data(), B.flag, sizeof(int64_t) * nsys, hipMemcpyDeviceToHost,
+                         ctx->sP));
   TPM_HIP(hipStreamSynchronize(ctx->sP));
+  if (ctx->h_rep->qerr)
+    return fail(TPM_EDEVICE, "particle work queue: a wait exceeded its limit");
+  const unsigned long long acc = ctx->h_rep->acc;
+  std::vector<int32_t> rs;            // reasons, where the caller does not take them
   if (n) {
     TPM_HIP(hipMemcpy(r_out, B.out.r, n * 24, hipMemcpyDeviceToHost));
     TPM_HIP(hipMemcpy(v_out, B.out.v, n * 24, hipMemcpyDeviceToHost));
     if (step_out) TPM_HIP(hipMemcpy(step_out, B.out.step, n * 8, hipMemcpyDeviceToHost));
     if (reason_out) TPM_HIP(hipMemcpy(reason_out, B.out.reason, n * 4, hipMemcpyDeviceToHost));
+    else if (stats_out) {
+      rs.resize(n);
+      TPM_HIP(hipMemcpy(rs.data(), B.out.reason, n * 4, hipMemcpyDeviceToHost));
+    }
     if (planet_out) {
       TPM_HIP(hipMemcpy(planet_out, B.out.planet, n * 4, hipMemcpyDeviceToHost));
       for (int s = 0; s < nsys; ++s)
@@ -2408,10 +2488,6 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
           if (planet_out[i] >= 0) planet_out[i] = perm[s][planet_out[i]];
     }
   }
-  unsigned long long acc = 0;
-  TPM_HIP(hipMemcpy(&acc, B.acc, sizeof(acc), hipMemcpyDeviceToHost));
-  std::vector<int64_t> flags(nsys);
-  TPM_HIP(hipMemcpy(flags.data(), B.flag, sizeof(int64_t) * nsys, hipMemcpyDeviceToHost));
   if (stats_out) {
     tpm_stats st{};
     st.step = nsteps;
@@ -2427,13 +2503,10 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
     st.chunk_steps = choice.chunk;
     st.resync_chunks = choice.resync;
     st.compactions = choice.resync > 0 ? (nchunks - 1) / choice.resync : 0;
-    if (n) {
-      std::vector<int32_t> rs(n);
-      TPM_HIP(hipMemcpy(rs.data(), B.out.reason, n * 4, hipMemcpyDeviceToHost));
-      for (auto x : rs)
-        if (x >= 0 && x < 4) st.count_by_reason[x]++;
-      st.n_active = st.count_by_reason[0];
-    }
+    const int32_t* why = reason_out ? reason_out : rs.data();
+    for (int64_t i = 0; i < n; ++i)
+      if (why[i] >= 0 && why[i] < 4) st.count_by_reason[why[i]]++;
+    st.n_active = st.count_by_reason[0];
     *stats_out = st;
   }
   if (planet_flag) std::copy(flags.begin(), flags.end(), planet_flag);
