@@ -28,6 +28,13 @@ hipError_t launch_ad_reverse(const SysConst& S, double dt, int64_t n, int s0, in
                              const double* table, const double* tape, double* lam,
                              const int64_t* dstep, hipStream_t st);
 
+// The same, and beside it the recomputation of steps [r0, s0) from the checkpoint
+// `in` into the tape `tape_next`.
+hipError_t launch_ad_reverse_pair(const SysConst& S, double dt, int64_t n, int r0, int s0, int s1,
+                                  const double* table, const double* tape, double* lam,
+                                  const double* in, double* tape_next, int64_t* dstep,
+                                  hipStream_t st);
+
 // Tangent of steps [s0, s1): state and tangent ([6][n] each) in/out.
 hipError_t launch_ad_tangent(const SysConst& S, double dt, int64_t n, int s0, int s1,
                              const double* table, double* st_, double* tg, int32_t* reason,

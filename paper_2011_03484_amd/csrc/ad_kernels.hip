@@ -75,12 +75,10 @@ TPM_DEV int32_t ad_step(const ADArgs<NP>& A, const RowT& row1, double r[3], doub
 // mode 2: recompute for the adjoint - a particle advances exactly through the
 //         steps s < dstep[i] of the recorded run and no record is written.
 template <int NP>
-__global__ void __launch_bounds__(256)
-ad_segment(ADArgs<NP> A, const double* __restrict__ table, const double* __restrict__ in,
-           double* __restrict__ out, double* __restrict__ tape, int64_t* __restrict__ dstep,
-           int32_t* __restrict__ reason, int32_t* __restrict__ planet, int mode) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.n) return;
+TPM_DEV void segment_body(const ADArgs<NP>& A, int64_t i, const double* __restrict__ table,
+                          const double* __restrict__ in, double* __restrict__ out,
+                          double* __restrict__ tape, int64_t* __restrict__ dstep,
+                          int32_t* __restrict__ reason, int32_t* __restrict__ planet, int mode) {
   constexpr int ROW = 3 * NP + 3;
   const int64_t n = A.n;
   double r[3] = {in[i], in[n + i], in[2 * n + i]};
@@ -100,20 +98,17 @@ ad_segment(ADArgs<NP> A, const double* __restrict__ table, const double* __restr
     if (hit >= 0) { why = ST_ENCOUNTER; pl = hit; ds = A.s0; }
     else if (fma_(r[0], r[0], fma_(r[1], r[1], r[2] * r[2])) > A.rmax2) { why = ST_ESCAPE; ds = A.s0; }
   }
-  // the row that ends step s is fetched into registers during step s - 1
+  // the row that ends step s is fetched during step s - 1, into one of two
+  // buffers in turn
   const int zero = opaque_zero_vgpr();
-  Row<NP> R1, Rn;
-  if (A.s0 < A.s1) load_row<NP>(R1, table + (size_t)(A.s0 + 1) * ROW, zero);
-  for (int s = A.s0; s < A.s1; ++s) {
-    if (s + 1 < A.s1) load_row<NP>(Rn, table + (size_t)(s + 2) * ROW, zero);
-    const Row<NP> Rs = R1;
-    R1 = Rn;
-    if (mode == 2 ? (s >= stop) : (why != ST_ACTIVE)) continue;
+  Row<NP> ra, rb;
+  auto step = [&](int s, const Row<NP>& row) {
+    if (mode == 2 ? (s >= stop) : (why != ST_ACTIVE)) return;
     double r1[3] = {r[0], r[1], r[2]}, v1[3] = {v[0], v[1], v[2]}, a1[3] = {acc[0], acc[1], acc[2]};
     int32_t p1 = -1;
     double xsm[3];
-    int32_t w = ad_step<NP>(A, Rs.v, r1, v1, a1, p1, xsm);
-    if (w == ST_KEPLER) { why = w; ds = s; continue; }
+    int32_t w = ad_step<NP>(A, row.v, r1, v1, a1, p1, xsm);
+    if (w == ST_KEPLER) { why = w; ds = s; return; }
     if (tape) {
       double* t = tape + (size_t)(s - A.s0) * AD_TAPE_FIELDS * n + i;
       const double f[AD_TAPE_FIELDS] = {r[0], r[1], r[2], v[0], v[1], v[2], acc[0], acc[1], acc[2],
@@ -123,6 +118,15 @@ ad_segment(ADArgs<NP> A, const double* __restrict__ table, const double* __restr
     }
     for (int k = 0; k < 3; ++k) { r[k] = r1[k]; v[k] = v1[k]; acc[k] = a1[k]; }
     if (w != ST_ACTIVE) { why = w; pl = p1; ds = s + 1; }
+  };
+  auto row_at = [&](int s) { return table + (size_t)min(s, A.s1) * ROW; };
+  if (A.s0 < A.s1) load_row<NP>(ra, row_at(A.s0 + 1), zero);
+  for (int s = A.s0; s < A.s1; s += 2) {
+    load_row<NP>(rb, row_at(s + 2), zero);
+    step(s, ra);
+    if (s + 1 >= A.s1) break;
+    load_row<NP>(ra, row_at(s + 3), zero);
+    step(s + 1, rb);
   }
   if (out) {
     out[i] = r[0]; out[n + i] = r[1]; out[2 * n + i] = r[2];
@@ -135,70 +139,118 @@ ad_segment(ADArgs<NP> A, const double* __restrict__ table, const double* __restr
   }
 }
 
+// A particle's steps of one segment, last to first.  Both kicks at a boundary
+// have the same Jacobian and meet the same dL/dv, so A(r_s) lv is evaluated
+// once for the closing kick of step s - 1 and the opening one of step s.  Bound
+// by the instructions of a lone wavefront; with that, derivative expressions
+// written as FMAs and two fetch buffers in turn, 0.97 us a step at four planets
+// (1.8 before).
 template <int NP>
-__global__ void __launch_bounds__(256)
-ad_reverse(ADArgs<NP> A, const double* __restrict__ table, const double* __restrict__ tape,
-           double* __restrict__ lam, const int64_t* __restrict__ dstep) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= A.n) return;
+TPM_DEV void reverse_body(const ADArgs<NP>& A, int64_t i, const double* __restrict__ table,
+                          const double* __restrict__ tape, double* __restrict__ lam,
+                          const int64_t* __restrict__ dstep) {
   constexpr int ROW = 3 * NP + 3;
   const int64_t n = A.n;
   const double h = 0.5 * A.dt;
-  double lr[3] = {lam[i], lam[n + i], lam[2 * n + i]};
-  double lv[3] = {lam[3 * n + i], lam[4 * n + i], lam[5 * n + i]};
   const int64_t ds = dstep[i];
   // steps s with s < ds (or all steps if never removed) were carried out
   int s_top = A.s1;
   if (ds >= 0 && ds < (int64_t)s_top) s_top = (int)(ds > A.s0 ? ds : A.s0);
-  // the tape entry of step s is fetched during step s + 1 (its loads do not
-  // depend on the adjoint)
-  auto fetch = [&](int s, double (&f)[AD_TAPE_FIELDS]) {
+  if (s_top <= A.s0) return;
+  double lr[3] = {lam[i], lam[n + i], lam[2 * n + i]};
+  double lv[3] = {lam[3 * n + i], lam[4 * n + i], lam[5 * n + i]};
+  // The tape entry of step s and row s are fetched during step s + 1 (they do
+  // not depend on the adjoint), into one of two buffers in turn.
+  struct Buf {
+    double f[AD_TAPE_FIELDS];
+    Row<NP> row;
+  };
+  const int zero = opaque_zero_vgpr();
+  auto fetch = [&](int s, Buf& b) {
     const double* t = tape + (size_t)(s - A.s0) * AD_TAPE_FIELDS * n + i;
 #pragma unroll
-    for (int k = 0; k < AD_TAPE_FIELDS; ++k) f[k] = t[(size_t)k * n];
+    for (int k = 0; k < AD_TAPE_FIELDS; ++k) b.f[k] = t[(size_t)k * n];
+    load_row<NP>(b.row, table + (size_t)s * ROW, zero);
   };
-  // and so is row s - 1 (rows s and s + 1 are in registers already)
-  double cur[AD_TAPE_FIELDS], nxt[AD_TAPE_FIELDS];
-  Row<NP> R0, R1, Rn;
-  if (s_top - 1 >= A.s0) {
-    fetch(s_top - 1, cur);
-    load_row<NP>(R0, table + (size_t)(s_top - 1) * ROW, 0);
-    load_row<NP>(R1, table + (size_t)s_top * ROW, 0);
-  }
-  for (int s = s_top - 1; s >= A.s0; --s) {
-    if (s - 1 >= A.s0) {
-      fetch(s - 1, nxt);
-      load_row<NP>(Rn, table + (size_t)(s - 1) * ROW, 0);
-    }
-    double r[3] = {cur[0], cur[1], cur[2]};
-    double v[3] = {cur[3], cur[4], cur[5]};
-    const auto& row0 = R0.v;
-    const auto& row1 = R1.v;
-    double vh[3] = {fma_(h, cur[6], v[0]), fma_(h, cur[7], v[1]), fma_(h, cur[8], v[2])};
-    DriftVals D;
-    double nr[3], nv[3];
-    drift_vals(A.K, A.dt, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, nr[0], nr[1], nr[2], nv[0],
-               nv[1], nv[2], cur[9], cur[10], cur[11]);
-    // closing kick: v_{s+1} = v' + h a(r_{s+1})
-    double Al[3];
-    accel_jac<NP>(row1, A.P, nr, lv, Al);
-    double lr1[3] = {lr[0] + h * Al[0], lr[1] + h * Al[1], lr[2] + h * Al[2]};
-    // drift
-    double lr0[3], lvh[3];
-    drift_vjp(A.K, A.dt, D, r, vh, lr1, lv, lr0, lvh);
-    // opening kick: vh = v_s + h a(r_s)
-    accel_jac<NP>(row0, A.P, r, lvh, Al);
+  auto values = [&](const Buf& b, double vh[3]) {
+    const double* f = b.f;
+    for (int k = 0; k < 3; ++k) vh[k] = fma_(h, f[6 + k], f[3 + k]);
+    return drift_vals(A.K, A.dt, f, vh, f[9], f[10], f[11]);
+  };
+  auto step = [&](int s, const Buf& b) {
+    double vh[3], lr0[3], lvh[3], Al[3];
+    const DriftVals D = values(b, vh);
+    drift_vjp(A.K, A.dt, D, b.f, vh, lr, lv, lr0, lvh);
+    accel_jac<NP>(b.row.v, A.P, b.f, lvh, Al);
+    // the opening kick of this step and the closing one of the step before
+    // (the segment before adds its own last step's)
+    const double h1 = s > A.s0 ? h : 0.0;
     for (int k = 0; k < 3; ++k) {
-      lr[k] = lr0[k] + h * Al[k];
+      lr[k] = fma_(h1, Al[k], fma_(h, Al[k], lr0[k]));
       lv[k] = lvh[k];
     }
-#pragma unroll
-    for (int k = 0; k < AD_TAPE_FIELDS; ++k) cur[k] = nxt[k];
-    R1 = R0;
-    R0 = Rn;
+  };
+  Buf a, b;
+  fetch(s_top - 1, a);
+  // the closing kick of the last step, at the state it ended in
+  {
+    double vh[3], nr[3], Al[3];
+    const DriftVals D = values(a, vh);
+    for (int k = 0; k < 3; ++k) nr[k] = fma_(D.f, a.f[k], D.g * vh[k]);
+    accel_jac<NP>(table + (size_t)s_top * ROW, A.P, nr, lv, Al);
+    for (int k = 0; k < 3; ++k) lr[k] = fma_(h, Al[k], lr[k]);
+  }
+  for (int s = s_top - 1;;) {
+    if (s > A.s0) fetch(s - 1, b);
+    step(s, a);
+    if (--s < A.s0) break;
+    if (s > A.s0) fetch(s - 1, a);
+    step(s, b);
+    if (--s < A.s0) break;
   }
   lam[i] = lr[0]; lam[n + i] = lr[1]; lam[2 * n + i] = lr[2];
   lam[3 * n + i] = lv[0]; lam[4 * n + i] = lv[1]; lam[5 * n + i] = lv[2];
+}
+
+template <int NP>
+__global__ void __launch_bounds__(64)
+ad_segment(ADArgs<NP> A, const double* __restrict__ table, const double* __restrict__ in,
+           double* __restrict__ out, double* __restrict__ tape, int64_t* __restrict__ dstep,
+           int32_t* __restrict__ reason, int32_t* __restrict__ planet, int mode) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < A.n) segment_body<NP>(A, i, table, in, out, tape, dstep, reason, planet, mode);
+}
+
+template <int NP>
+__global__ void __launch_bounds__(64)
+ad_reverse(ADArgs<NP> A, const double* __restrict__ table, const double* __restrict__ tape,
+           double* __restrict__ lam, const int64_t* __restrict__ dstep) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < A.n) reverse_body<NP>(A, i, table, tape, lam, dstep);
+}
+
+// The reverse sweep of one segment (A) and the recomputation of the one before
+// it (steps [r0, A.s0), from its checkpoint `in` into the other tape) side by
+// side: a workgroup is one wavefront of each, so that they lie on two SIMDs of
+// one compute unit.  As two launches on two streams their lone wavefronts
+// shared SIMDs and slowed each other to 290 us a segment of 125 steps, where
+// alone they took 222 and 156 (16,384 particles).
+template <int NP>
+__global__ void __launch_bounds__(128)
+ad_reverse_pair(ADArgs<NP> A, int r0, const double* __restrict__ table,
+                const double* __restrict__ tape, double* __restrict__ lam,
+                const double* __restrict__ in, double* __restrict__ tape_next,
+                int64_t* __restrict__ dstep) {
+  const int64_t i = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  if (i >= A.n) return;
+  if (threadIdx.x < 64) {
+    reverse_body<NP>(A, i, table, tape, lam, dstep);
+  } else {
+    ADArgs<NP> R = A;
+    R.s0 = r0;
+    R.s1 = A.s0;
+    segment_body<NP>(R, i, table, in, nullptr, tape_next, dstep, nullptr, nullptr, 2);
+  }
 }
 
 template <int NP>
@@ -215,41 +267,57 @@ ad_tangent(ADArgs<NP> A, const double* __restrict__ table, double* __restrict__ 
   double dr[3] = {tg[i], tg[n + i], tg[2 * n + i]};
   double dv[3] = {tg[3 * n + i], tg[4 * n + i], tg[5 * n + i]};
   int32_t why = first ? ST_ACTIVE : reason[i];
-  double acc[3];
+  // A(r) dr at a step boundary serves the closing kick of one step and the
+  // opening kick of the next (position and tangent are the same)
+  double acc[3], Ad[3];
   int hit = accel<NP>(table + (size_t)A.s0 * ROW, A.P, r[0], r[1], r[2], acc[0], acc[1], acc[2]);
   if (first && (hit >= 0 || fma_(r[0], r[0], fma_(r[1], r[1], r[2] * r[2])) > A.rmax2))
     why = hit >= 0 ? ST_ENCOUNTER : ST_ESCAPE;
-  for (int s = A.s0; s < A.s1 && why == ST_ACTIVE; ++s) {
-    const double* row1 = table + (size_t)(s + 1) * ROW;
-    double Ad[3];
-    accel_jac<NP>(table + (size_t)s * ROW, A.P, r, dr, Ad);
-    double vh[3] = {fma_(h, acc[0], v[0]), fma_(h, acc[1], v[1]), fma_(h, acc[2], v[2])};
-    double dvh[3] = {dv[0] + h * Ad[0], dv[1] + h * Ad[1], dv[2] + h * Ad[2]};
+  accel_jac<NP>(table + (size_t)A.s0 * ROW, A.P, r, dr, Ad);
+  // the row that ends step s is fetched during step s - 1
+  const int zero = opaque_zero_vgpr();
+  Row<NP> ra, rb;
+  auto step = [&](int s, const Row<NP>& row) {
+    if (why != ST_ACTIVE) return;
+    double vh[3], dvh[3];
+    for (int k = 0; k < 3; ++k) {
+      vh[k] = fma_(h, acc[k], v[k]);
+      dvh[k] = fma_(h, Ad[k], dv[k]);
+    }
     // the state by the particles' drift, the values its derivative needs from
     // the root that drift found
     double nr[3] = {r[0], r[1], r[2]}, nv[3] = {vh[0], vh[1], vh[2]}, xk, sk, mk;
     const uint64_t bad =
-        drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), false, lanes(true), nr[0],
-                    nr[1], nr[2], nv[0], nv[1], nv[2], xk, sk, mk);
-    if (lane_in(bad)) { why = ST_KEPLER; break; }
-    DriftVals D;
-    double q[6];
-    drift_vals(A.K, A.dt, r[0], r[1], r[2], vh[0], vh[1], vh[2], D, q[0], q[1], q[2], q[3], q[4],
-               q[5], xk, sk, mk);
+        drift_lanes(A.K, A.dt, A.kiters, A.ftol, quick_serves(A.kiters, A.ftol), false, lanes(true),
+                    nr[0], nr[1], nr[2], nv[0], nv[1], nv[2], xk, sk, mk);
+    if (lane_in(bad)) {
+      why = ST_KEPLER;
+      return;
+    }
+    const DriftVals D = drift_vals(A.K, A.dt, r, vh, xk, sk, mk);
     double ndr[3], ndv[3];
     drift_jvp(A.K, A.dt, D, r, vh, dr, dvh, ndr, ndv);
     double b[3];
-    int h1 = accel<NP>(row1, A.P, nr[0], nr[1], nr[2], b[0], b[1], b[2]);
-    accel_jac<NP>(row1, A.P, nr, ndr, Ad);
+    const int h1 = accel<NP>(row.v, A.P, nr[0], nr[1], nr[2], b[0], b[1], b[2]);
+    accel_jac<NP>(row.v, A.P, nr, ndr, Ad);
     for (int k = 0; k < 3; ++k) {
       r[k] = nr[k];
       acc[k] = b[k];
       v[k] = fma_(h, b[k], nv[k]);
       dr[k] = ndr[k];
-      dv[k] = ndv[k] + h * Ad[k];
+      dv[k] = fma_(h, Ad[k], ndv[k]);
     }
     if (h1 >= 0) why = ST_ENCOUNTER;
     else if (fma_(r[0], r[0], fma_(r[1], r[1], r[2] * r[2])) > A.rmax2) why = ST_ESCAPE;
+  };
+  auto row_at = [&](int s) { return table + (size_t)min(s, A.s1) * ROW; };
+  load_row<NP>(ra, row_at(A.s0 + 1), zero);
+  for (int s = A.s0; s < A.s1; s += 2) {
+    load_row<NP>(rb, row_at(s + 2), zero);
+    step(s, ra);
+    if (s + 1 >= A.s1) break;
+    load_row<NP>(ra, row_at(s + 3), zero);
+    step(s + 1, rb);
   }
   st[i] = r[0]; st[n + i] = r[1]; st[2 * n + i] = r[2];
   st[3 * n + i] = v[0]; st[4 * n + i] = v[1]; st[5 * n + i] = v[2];
@@ -340,6 +408,19 @@ hipError_t launch_ad_reverse(const SysConst& S, double dt, int64_t n, int s0, in
                      make_args<N>(S, dt, n, s0, s1), table, tape, lam, dstep)
   TPM_NP_SWITCH(S.np, TPM_REV)
 #undef TPM_REV
+  return hipGetLastError();
+}
+
+hipError_t launch_ad_reverse_pair(const SysConst& S, double dt, int64_t n, int r0, int s0, int s1,
+                                  const double* table, const double* tape, double* lam,
+                                  const double* in, double* tape_next, int64_t* dstep,
+                                  hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+#define TPM_PAIR(N)                                                                           \
+  hipLaunchKernelGGL(ad_reverse_pair<N>, dim3(ad_grid(n)), dim3(2 * AD_BLOCK), 0, st,         \
+                     make_args<N>(S, dt, n, s0, s1), r0, table, tape, lam, in, tape_next, dstep)
+  TPM_NP_SWITCH(S.np, TPM_PAIR)
+#undef TPM_PAIR
   return hipGetLastError();
 }
 

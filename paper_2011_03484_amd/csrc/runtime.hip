@@ -288,8 +288,11 @@ struct tpm_sim {
     int32_t* treason = nullptr;   // tangent's own removal flags
     size_t cap_table = 0, cap_ckpts = 0, cap_tape = 0, cap_n = 0;
     bool valid = false;
-    // ordering events between the caller's stream and the library's streams
-    hipEvent_t ev_tab[2]{}, ev_rec[2]{}, ev_rev[2]{}, ev_in = nullptr;
+    // ordering events between the caller's stream and the library's streams;
+    // ev_end: the planet-map stream is done with the last forward (reading the
+    // planets' state and the planet event), which an integrate call waits for
+    hipEvent_t ev_tab[2]{}, ev_end = nullptr;
+    bool reading = false;
   } ad;
   std::vector<hipEvent_t> kev;           // per-launch timing events (time_kernels)
   // sampled diagnostics and snapshots (tpm_set_diagnostics)
@@ -344,10 +347,8 @@ struct tpm_sim {
     dfree(ad.dstep); dfree(ad.reason); dfree(ad.planet); dfree(ad.treason);
     for (int k = 0; k < 2; ++k) {
       if (ad.ev_tab[k]) (void)hipEventDestroy(ad.ev_tab[k]);
-      if (ad.ev_rec[k]) (void)hipEventDestroy(ad.ev_rec[k]);
-      if (ad.ev_rev[k]) (void)hipEventDestroy(ad.ev_rev[k]);
     }
-    if (ad.ev_in) (void)hipEventDestroy(ad.ev_in);
+    if (ad.ev_end) (void)hipEventDestroy(ad.ev_end);
     ad = AD{};
   }
 
@@ -1050,6 +1051,10 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   }
   s->stats.chunks = 0;
   s->stats.compactions = 0;
+  if (s->ad.reading) {                    // a forward may still read the planets
+    TPM_HIP(hipStreamWaitEvent(s->sP, s->ad.ev_end, 0));
+    s->ad.reading = false;
+  }
   TPM_HIP(hipEventRecord(s->t0P, s->sP));
   if (!live) TPM_HIP(hipEventRecord(s->t0E, s->sE));
   // A history's rows are enqueued up to NSLOT-1 chunks ahead of the particles.
@@ -1829,21 +1834,16 @@ int tpm_ad_forward(tpm_sim* s, int64_t n, const double* d_r0, const double* d_v0
   A.ckpt = ckpt_every;
   A.nseg = nseg;
   A.dt = dt;
-  if (!A.ev_in) {
-    for (int k = 0; k < 2; ++k) {
-      TPM_HIP(hipEventCreateWithFlags(&A.ev_tab[k], hipEventDisableTiming));
-      TPM_HIP(hipEventCreateWithFlags(&A.ev_rec[k], hipEventDisableTiming));
-      TPM_HIP(hipEventCreateWithFlags(&A.ev_rev[k], hipEventDisableTiming));
-    }
-    TPM_HIP(hipEventCreateWithFlags(&A.ev_in, hipEventDisableTiming));
-  }
+  for (int k = 0; k < 2; ++k)
+    if (!A.ev_tab[k]) TPM_HIP(hipEventCreateWithFlags(&A.ev_tab[k], hipEventDisableTiming));
+  if (!A.ev_end) TPM_HIP(hipEventCreateWithFlags(&A.ev_end, hipEventDisableTiming));
   // The planet table of the whole run, from the current planet state (not
   // advanced), is computed on the library's planet-map stream in pieces of
-  // whole segments (at least 1,024 steps), after whatever that stream already
+  // whole segments (at least 96 steps), after whatever that stream already
   // holds (an earlier integrate); the caller's stream runs each segment once
   // the piece holding its last row is written, so the planet map and the
-  // particle segments overlap.  A later tpm_integrate is ordered after these
-  // pieces by the same stream.
+  // particle segments overlap.  A later tpm_integrate waits for these pieces
+  // (ev_end).
   const SysConst S = s->sys();
   const EphConst E = s->eph();
   const size_t pb = sizeof(double) * 3 * std::max(s->np, 1);
@@ -1852,7 +1852,7 @@ int tpm_ad_forward(tpm_sim* s, int64_t n, const double* d_r0, const double* d_v0
   TPM_HIP(hipMemcpyAsync(rj, s->d_rj, pb, hipMemcpyDeviceToDevice, s->sE));
   TPM_HIP(hipMemcpyAsync(vj, s->d_vj, pb, hipMemcpyDeviceToDevice, s->sE));
   TPM_HIP(launch_aos_to_soa(d_r0, d_v0, A.ckpts, n, st));
-  const int64_t piece = (int64_t)ckpt_every * std::max<int64_t>(1, (1024 + ckpt_every - 1) / ckpt_every);
+  const int64_t piece = (int64_t)ckpt_every * std::max<int64_t>(1, (96 + ckpt_every - 1) / ckpt_every);
   int k = 0;   // next segment
   for (int64_t p0 = 0, j = 0;; p0 += piece, ++j) {
     const int64_t p1 = std::min<int64_t>(nsteps, p0 + piece);
@@ -1873,6 +1873,8 @@ int tpm_ad_forward(tpm_sim* s, int64_t n, const double* d_r0, const double* d_v0
     }
     if (p1 >= nsteps) break;
   }
+  TPM_HIP(hipEventRecord(A.ev_end, s->sE));
+  A.reading = true;
   if (nseg == 0) {
     // no step: only the checks at step 0
     TPM_HIP(launch_ad_segment(S, dt, n, 0, 0, A.table, A.ckpts, nullptr, nullptr, A.dstep,
@@ -1902,44 +1904,22 @@ int tpm_ad_backward(tpm_sim* s, const double* d_gRT, const double* d_gVT, double
   const SysConst S = s->sys();
   double* lam = A.work;
   double* tape[2] = {A.tape, A.tape + (size_t)A.ckpt * AD_TAPE_FIELDS * n};
-  // Segment k's states are recomputed from its checkpoint into tape k % 2 on
-  // the library's particle stream while the caller's stream sweeps segment
-  // k + 1 backwards through the other tape: the recomputation does not depend
-  // on the adjoint, so the two overlap (each fills only part of the device at
-  // these particle counts).  A recomputation waits until the sweep that last
-  // read its tape is done; a sweep waits for its tape.
-  const hipStream_t sR = s->sP;
-  TPM_HIP(hipEventRecord(A.ev_in, st));
-  TPM_HIP(hipStreamWaitEvent(sR, A.ev_in, 0));
-  auto recompute = [&](int k) -> int {
-    const int s0 = k * A.ckpt;
-    const int s1 = (int)std::min<int64_t>(A.nsteps, (int64_t)s0 + A.ckpt);
-    TPM_HIP(launch_ad_segment(S, A.dt, n, s0, s1, A.table, A.ckpts + (size_t)k * 6 * n, nullptr,
-                              tape[k % 2], A.dstep, nullptr, nullptr, 2, sR));
-    TPM_HIP(hipEventRecord(A.ev_rec[k % 2], sR));
-    return TPM_OK;
-  };
+  // Segment k's states are recomputed from its checkpoint into tape k % 2 while
+  // segment k + 1 is swept backwards through the other tape (the recomputation
+  // does not depend on the adjoint): one launch for both, all on the caller's
+  // stream.
+  auto first = [&](int k) { return k * A.ckpt; };
+  auto last = [&](int k) { return (int)std::min<int64_t>(A.nsteps, (int64_t)first(k) + A.ckpt); };
+  auto from = [&](int k) { return A.ckpts + (size_t)k * 6 * n; };
   TPM_HIP(launch_aos_to_soa(d_gRT, d_gVT, lam, n, st));
-  for (int k = A.nseg - 1; k >= 0 && k >= A.nseg - 2; --k) {
-    int rc = recompute(k);
-    if (rc) return rc;
-  }
-  for (int k = A.nseg - 1; k >= 0; --k) {
-    const int s0 = k * A.ckpt;
-    const int s1 = (int)std::min<int64_t>(A.nsteps, (int64_t)s0 + A.ckpt);
-    TPM_HIP(hipStreamWaitEvent(st, A.ev_rec[k % 2], 0));
-    TPM_HIP(launch_ad_reverse(S, A.dt, n, s0, s1, A.table, tape[k % 2], lam, A.dstep, st));
-    if (k >= 2) {
-      TPM_HIP(hipEventRecord(A.ev_rev[k % 2], st));
-      TPM_HIP(hipStreamWaitEvent(sR, A.ev_rev[k % 2], 0));
-      int rc = recompute(k - 2);
-      if (rc) return rc;
-    }
-  }
-  // the library's stream is done with this call's tapes before anything else
-  // runs on it
-  TPM_HIP(hipEventRecord(A.ev_in, st));
-  TPM_HIP(hipStreamWaitEvent(sR, A.ev_in, 0));
+  if (const int k = A.nseg - 1; k >= 0)
+    TPM_HIP(launch_ad_segment(S, A.dt, n, first(k), last(k), A.table, from(k), nullptr, tape[k % 2],
+                              A.dstep, nullptr, nullptr, 2, st));
+  for (int k = A.nseg - 1; k > 0; --k)
+    TPM_HIP(launch_ad_reverse_pair(S, A.dt, n, first(k - 1), first(k), last(k), A.table,
+                                   tape[k % 2], lam, from(k - 1), tape[(k - 1) % 2], A.dstep, st));
+  if (A.nseg > 0)
+    TPM_HIP(launch_ad_reverse(S, A.dt, n, first(0), last(0), A.table, tape[0], lam, A.dstep, st));
   TPM_HIP(launch_soa_to_aos(lam, d_gR0, d_gV0, n, st));
   return TPM_OK;
 }
