@@ -209,9 +209,11 @@ hipError_t launch_handoff_merge(EncList L, int n_upper, Work w, int32_t* d_nacti
                                 hipStream_t st);
 
 // Stable partition of the working set: active entries of src (in order) go to
-// dst; d_nactive is updated in place.  scratch holds >= 2 * nblocks + 1 ints.
+// dst; d_nactive is updated in place and, where host_count is given, the new
+// count is written there too (pinned memory).  scratch: compact_scratch_ints
+// ints, 8-byte aligned and zero; each launch leaves them zero.
 hipError_t launch_compact(Work src, Work dst, int32_t* d_nactive, int n_upper, int32_t* scratch,
-                          hipStream_t st);
+                          int32_t* host_count, hipStream_t st);
 int compact_scratch_ints(int n_upper);
 
 // Write the still-active particles of the working set into out (by slot).
@@ -226,9 +228,10 @@ hipError_t launch_helio_to_jacobi(const EphConst& E, const double* h, double* j,
 
 // Fill a new set of particles: the working set w (entry i: particle idx[i], or i
 // with idx null, na of them) from the states in out.r and out.v; the records not
-// supplied; the work queue's counters of `ntiles` tiles; the active count.
+// supplied; nclear words from `progress` on zero (the work queue's progress
+// words and what lies behind them); the queue's counters; the active count.
 hipError_t launch_load_particles(Out out, int n, Work w, const int32_t* idx, int na, bool step,
-                                 bool reason, bool planet, uint32_t* progress, int ntiles,
+                                 bool reason, bool planet, uint32_t* progress, int nclear,
                                  unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive,
                                  hipStream_t st);
 
@@ -297,11 +300,13 @@ hipError_t launch_batch_retile(Work w, const int32_t* d_nactive, int n_upper, co
                                const int32_t* sorder, int nsys, int32_t* start, int32_t* end,
                                TileDesc* tiles, int32_t* ntiles_dev, hipStream_t st);
 // Start of a run: tiles (and their number) and planet states from their pristine
-// copies, each tile's system to its particles' psys, no planet events, *acc 0.
+// copies, each tile's system to its particles' psys, no planet events, *acc 0,
+// the compaction's scratch zero.
 hipError_t launch_batch_reset(const TileDesc* tiles0, TileDesc* tiles, int ntiles,
                               int32_t* ntiles_dev, int32_t* psys, const double* rj0,
                               const double* vj0, double* rj, double* vj, int64_t* flag, int nsys,
-                              unsigned long long* acc, hipStream_t st);
+                              unsigned long long* acc, int32_t* scratch, int nscratch,
+                              hipStream_t st);
 // Zero a work-queue item counter (a kernel, so it can sit in a captured graph).
 hipError_t launch_queue_reset(unsigned long long* ctr, hipStream_t st);
 

@@ -500,8 +500,10 @@ __global__ void __launch_bounds__(64)
 batch_reset(const TileDesc* __restrict__ tiles0, TileDesc* __restrict__ tiles, int ntiles,
             int32_t* ntiles_dev, int32_t* __restrict__ psys, const double* __restrict__ rj0,
             const double* __restrict__ vj0, double* __restrict__ rj, double* __restrict__ vj,
-            int64_t* __restrict__ flag, int nsys, unsigned long long* acc) {
+            int64_t* __restrict__ flag, int nsys, unsigned long long* acc, int32_t* scratch,
+            int nscratch) {
   const int b = blockIdx.x, lane = threadIdx.x;
+  for (int k = b * 64 + lane; k < nscratch; k += 64 * gridDim.x) scratch[k] = 0;
   if (b < ntiles) {
     const TileDesc T = tiles0[b];
     if (lane < T.count) psys[T.first + lane] = T.sys;
@@ -523,9 +525,11 @@ batch_reset(const TileDesc* __restrict__ tiles0, TileDesc* __restrict__ tiles, i
 hipError_t launch_batch_reset(const TileDesc* tiles0, TileDesc* tiles, int ntiles,
                               int32_t* ntiles_dev, int32_t* psys, const double* rj0,
                               const double* vj0, double* rj, double* vj, int64_t* flag, int nsys,
-                              unsigned long long* acc, hipStream_t st) {
+                              unsigned long long* acc, int32_t* scratch, int nscratch,
+                              hipStream_t st) {
   hipLaunchKernelGGL(batch_reset, dim3(std::max(std::max(ntiles, nsys), 1)), dim3(64), 0, st,
-                     tiles0, tiles, ntiles, ntiles_dev, psys, rj0, vj0, rj, vj, flag, nsys, acc);
+                     tiles0, tiles, ntiles, ntiles_dev, psys, rj0, vj0, rj, vj, flag, nsys, acc,
+                     scratch, nscratch);
   return hipGetLastError();
 }
 
@@ -1493,7 +1497,7 @@ hipError_t launch_run_report(const int64_t* dstep, int n, int64_t step_begin, in
 // ---------------------------------------------------------------- new particles
 __global__ void __launch_bounds__(256)
 load_particles_kernel(Out out, int n, Work w, const int32_t* __restrict__ idx, int na, bool step,
-                      bool reason, bool planet, uint32_t* progress, int ntiles,
+                      bool reason, bool planet, uint32_t* progress, int nclear,
                       unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
@@ -1508,7 +1512,7 @@ load_particles_kernel(Out out, int n, Work w, const int32_t* __restrict__ idx, i
     w.slot[i] = (int32_t)k;
     w.status[i] = ST_ACTIVE;
   }
-  if (i < ntiles) progress[i] = 0;
+  if (i < nclear) progress[i] = 0;
   if (i == 0) {
     *qctr = 0;
     *qerr = 0;
@@ -1517,12 +1521,12 @@ load_particles_kernel(Out out, int n, Work w, const int32_t* __restrict__ idx, i
 }
 
 hipError_t launch_load_particles(Out out, int n, Work w, const int32_t* idx, int na, bool step,
-                                 bool reason, bool planet, uint32_t* progress, int ntiles,
+                                 bool reason, bool planet, uint32_t* progress, int nclear,
                                  unsigned long long* qctr, int32_t* qerr, int32_t* d_nactive,
                                  hipStream_t st) {
-  const int m = std::max(std::max(n, ntiles), 1);
+  const int m = std::max(std::max(n, nclear), 1);
   hipLaunchKernelGGL(load_particles_kernel, dim3((m + 255) / 256), dim3(256), 0, st, out, n, w, idx,
-                     na, step, reason, planet, progress, ntiles, qctr, qerr, d_nactive);
+                     na, step, reason, planet, progress, nclear, qctr, qerr, d_nactive);
   return hipGetLastError();
 }
 
@@ -1542,109 +1546,141 @@ TPM_DEV int lane_prefix(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
 }
 
-__global__ void __launch_bounds__(CB)
-compact_count(const int32_t* __restrict__ status, const int32_t* __restrict__ d_nactive,
-              int32_t* __restrict__ block_count) {
-  const int n = *d_nactive;
-  const int base = blockIdx.x * CTILE;
-  int c = 0;
-#pragma unroll
-  for (int e = 0; e < CE; ++e) {
-    int i = base + e * CB + threadIdx.x;
-    c += (i < n && status[i] == ST_ACTIVE) ? 1 : 0;
-  }
-  // wave sum by ballots of each bit would be overkill; use a small LDS reduction
-  __shared__ int part[CB / 64];
-  int wsum = c;
-  for (int off = 32; off > 0; off >>= 1) wsum += __shfl_down(wsum, off, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = wsum;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int k = 0; k < CB / 64; ++k) t += part[k];
-    block_count[blockIdx.x] = t;
-  }
-}
-
-// Exclusive scan of block counts by one workgroup; writes the new n_active.
-__global__ void __launch_bounds__(1024)
-compact_scan(const int32_t* __restrict__ block_count, int32_t* __restrict__ block_off, int nb,
-             int32_t* __restrict__ d_nactive) {
-  __shared__ int buf[1024];
-  __shared__ int carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < nb; base += 1024) {
-    int i = base + threadIdx.x;
-    int v = i < nb ? block_count[i] : 0;
-    buf[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-      int t = threadIdx.x >= off ? buf[threadIdx.x - off] : 0;
-      __syncthreads();
-      buf[threadIdx.x] += t;
-      __syncthreads();
-    }
-    if (i < nb) block_off[i] = carry + buf[threadIdx.x] - v;
-    __syncthreads();
-    if (threadIdx.x == 1023) carry += buf[1023];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *d_nactive = carry;
-}
+// Stable partition in one launch.  A block takes the next tile of CTILE entries
+// (in the order blocks start, so the tiles before it are in hand), counts its
+// active ones, publishes the count, adds up what the tiles before it have
+// published (wave 0, 64 tiles at a time, back to the nearest one whose sum is
+// complete), publishes its own sum and writes its entries.  A tile's word is
+// 0, or 4 * count + 1 (its count alone) or 4 * sum + 2 (with all before it).
+// The last block to finish clears the words and the counters for the next
+// launch, so they need no host value and a captured launch can be replayed.
+// Bound by launches and latency: counting, scanning and moving in launches of
+// their own, and a copy of the count to the host, took 28 us for 25,000 entries
+// with the gaps between them, and made a call of 64 particles and 256 steps
+// 323 us instead of 299.
+constexpr uint64_t COMPACT_COUNT = 1, COMPACT_SUM = 2;
 
 __global__ void __launch_bounds__(CB)
-compact_scatter(Work src, Work dst, const int32_t* __restrict__ block_off,
-                const int32_t* __restrict__ d_nold) {
-  const int n_old = *d_nold;
-  __shared__ int wcount[CB / 64];
-  __shared__ int running;
+compact_kernel(Work src, Work dst, int32_t* d_nactive, int32_t* scratch,
+               int32_t* __restrict__ host_count) {
+  uint32_t* ticket = reinterpret_cast<uint32_t*>(scratch);
+  uint32_t* done = ticket + 1;
+  uint64_t* word = reinterpret_cast<uint64_t*>(scratch + 2);
+  __shared__ int s_tile, s_n, s_off;
+  __shared__ int wcount[CE][CB / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (threadIdx.x == 0) running = block_off[blockIdx.x];
+  if (threadIdx.x == 0) {
+    s_tile = (int)__hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // (the last tile's block writes the new count only after every block with a
+    // tile has published, hence read the old one)
+    s_n = __hip_atomic_load(d_nactive, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   __syncthreads();
-  const int base = blockIdx.x * CTILE;
+  const int tile = s_tile, n = s_n;
+  const int tiles = (n + CTILE - 1) / CTILE;
+  if (tile < tiles) {
+    const int64_t base = (int64_t)tile * CTILE + threadIdx.x;
+    bool keep[CE];
+    int pos[CE];
 #pragma unroll
-  for (int e = 0; e < CE; ++e) {
-    int i = base + e * CB + threadIdx.x;
-    bool keep = i < n_old && src.status[i] == ST_ACTIVE;
-    uint64_t m = __ballot(keep);
-    int before = lane_prefix(m);
-    if (lane == 0) wcount[wid] = __popcll(m);
+    for (int e = 0; e < CE; ++e) {
+      const int64_t i = base + e * CB;
+      keep[e] = i < n && src.status[i] == ST_ACTIVE;
+      const uint64_t m = lanes(keep[e]);
+      pos[e] = lane_prefix(m);
+      if (lane == 0) wcount[e][wid] = __popcll(m);
+    }
     __syncthreads();
-    int off = running;
-    for (int k = 0; k < wid; ++k) off += wcount[k];
-    if (keep) {
-      int d = off + before;
-      dst.x[d] = src.x[i]; dst.y[d] = src.y[i]; dst.z[d] = src.z[i];
-      dst.vx[d] = src.vx[i]; dst.vy[d] = src.vy[i]; dst.vz[d] = src.vz[i];
-      dst.slot[d] = src.slot[i];
+    int total = 0;
+#pragma unroll
+    for (int e = 0; e < CE; ++e)
+#pragma unroll
+      for (int k = 0; k < CB / 64; ++k) {
+        pos[e] += k < wid ? wcount[e][k] : 0;
+        total += wcount[e][k];
+      }
+    // the entries of the rounds before
+    int before = 0;
+#pragma unroll
+    for (int e = 0; e < CE; ++e) {
+      pos[e] += before;
+#pragma unroll
+      for (int k = 0; k < CB / 64; ++k) before += wcount[e][k];
+    }
+    if (threadIdx.x == 0)
+      __hip_atomic_store(word + tile, ((uint64_t)total << 2) | (tile ? COMPACT_COUNT : COMPACT_SUM),
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    double v[CE][6];
+    int32_t slot[CE];
+#pragma unroll
+    for (int e = 0; e < CE; ++e) {
+      if (!keep[e]) continue;
+      const int64_t i = base + e * CB;
+      v[e][0] = src.x[i]; v[e][1] = src.y[i]; v[e][2] = src.z[i];
+      v[e][3] = src.vx[i]; v[e][4] = src.vy[i]; v[e][5] = src.vz[i];
+      slot[e] = src.slot[i];
+    }
+    if (wid == 0) {
+      int off = 0;
+      for (int j = tile - 1; j >= 0; j -= 64) {
+        // lane l reads tile j - l; every word up to the nearest complete sum is
+        // published by a block that is running or has ended
+        const int k = j - lane;
+        uint64_t u, need;
+        for (;;) {
+          u = k >= 0 ? __hip_atomic_load(word + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                     : COMPACT_SUM;
+          const uint64_t sums = lanes((u & 3) == COMPACT_SUM);
+          need = sums ? sums ^ (sums - 1) : ~0ull;   // lanes up to the first sum
+          if ((need & lanes(u == 0)) == 0) break;
+          __builtin_amdgcn_s_sleep(1);
+        }
+        int c = lane_in(need) ? (int)(u >> 2) : 0;
+        for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
+        off += c;
+        if (need != ~0ull || lanes((u & 3) == COMPACT_SUM)) break;
+      }
+      if (lane == 0) {
+        s_off = off;
+        if (tile)
+          __hip_atomic_store(word + tile, ((uint64_t)(off + total) << 2) | COMPACT_SUM,
+                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tile == tiles - 1) {
+          __hip_atomic_store(d_nactive, off + total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (host_count) *host_count = off + total;
+        }
+      }
+    }
+    __syncthreads();
+    const int off = s_off;
+#pragma unroll
+    for (int e = 0; e < CE; ++e) {
+      if (!keep[e]) continue;
+      const int d = off + pos[e];
+      dst.x[d] = v[e][0]; dst.y[d] = v[e][1]; dst.z[d] = v[e][2];
+      dst.vx[d] = v[e][3]; dst.vy[d] = v[e][4]; dst.vz[d] = v[e][5];
+      dst.slot[d] = slot[e];
       dst.status[d] = ST_ACTIVE;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int t = 0;
-      for (int k = 0; k < CB / 64; ++k) t += wcount[k];
-      running += t;
-    }
-    __syncthreads();
+  } else if (tile == 0 && threadIdx.x == 0 && host_count) {
+    *host_count = 0;                           // nothing was active
   }
-}
-
-__global__ void __launch_bounds__(256) copy_count(const int32_t* a, int32_t* b) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *b = *a;
+  // the last block: every look-back is over
+  if (threadIdx.x == 0)
+    s_tile = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+             gridDim.x;
+  __syncthreads();
+  if (!s_tile) return;
+  for (unsigned k = threadIdx.x; k < gridDim.x; k += CB) word[k] = 0;
+  if (threadIdx.x < 2) scratch[threadIdx.x] = 0;
 }
 
 hipError_t launch_compact(Work src, Work dst, int32_t* d_nactive, int n_upper, int32_t* scratch,
-                          hipStream_t st) {
-  int nb = (n_upper + CTILE - 1) / CTILE;
+                          int32_t* host_count, hipStream_t st) {
+  const int nb = (n_upper + CTILE - 1) / CTILE;
   if (nb <= 0) return hipSuccess;
-  int32_t* counts = scratch;
-  int32_t* offs = scratch + nb;
-  int32_t* n_old = scratch + 2 * nb;
-  hipLaunchKernelGGL(copy_count, dim3(1), dim3(64), 0, st, d_nactive, n_old);
-  hipLaunchKernelGGL(compact_count, dim3(nb), dim3(CB), 0, st, src.status, d_nactive, counts);
-  hipLaunchKernelGGL(compact_scan, dim3(1), dim3(1024), 0, st, counts, offs, nb, d_nactive);
-  hipLaunchKernelGGL(compact_scatter, dim3(nb), dim3(CB), 0, st, src, dst, offs, n_old);
+  hipLaunchKernelGGL(compact_kernel, dim3(nb), dim3(CB), 0, st, src, dst, d_nactive, scratch,
+                     host_count);
   return hipGetLastError();
 }
 

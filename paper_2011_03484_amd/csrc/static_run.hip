@@ -78,9 +78,9 @@ struct PlanetsIn {
 
 // Initial state of one run: working set 0's slots (caller index) and status
 // (all active), the planets' heliocentric state, the progress words of the
-// tiles, and the counters and flags.
+// tiles, the compaction's scratch, and the counters and flags.
 __global__ void __launch_bounds__(256)
-static_setup_kernel(unsigned char* base, PlanetsIn P, int np, int n, int ntiles) {
+static_setup_kernel(unsigned char* base, PlanetsIn P, int np, int n, int ntiles, int ncscr) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   int32_t* slot = reinterpret_cast<int32_t*>(base + OFF_WORK0 + 48 * (int64_t)n);
   if (i < n) {
@@ -88,6 +88,7 @@ static_setup_kernel(unsigned char* base, PlanetsIn P, int np, int n, int ntiles)
     slot[n + i] = 0;      // the status array follows the slots
   }
   if (i < ntiles) reinterpret_cast<uint32_t*>(base + OFF_PROG)[i] = 0u;
+  if (i < ncscr) reinterpret_cast<int32_t*>(base + OFF_CSCR)[i] = 0;
   if (i < 3 * np) {
     double* h = reinterpret_cast<double*>(base + OFF_PLAN) + 2 * 3 * MAX_NP;
     h[i] = P.r[i];
@@ -282,9 +283,10 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
   double* ring = reinterpret_cast<double*>(base + OFF_RING);
   int32_t* cscr = reinterpret_cast<int32_t*>(base + OFF_CSCR);
   {
-    const int m = std::max(std::max(nn, ntiles), std::max(3 * np, 1));
+    const int ncscr = compact_scratch_ints(nn);
+    const int m = std::max(std::max(nn, ncscr), std::max(3 * np, 1));
     hipLaunchKernelGGL(static_setup_kernel, dim3((m + 255) / 256), dim3(256), 0, st, base, P, np, nn,
-                       ntiles);
+                       ntiles, ncscr);
     S_HIP(hipGetLastError());
   }
   if (np > 0) {
@@ -338,7 +340,7 @@ extern "C" int tpm_integrate_static(const tpm_options* opt_in, double mu0, int32
       q_base += QL.grabs(ntiles);
       q_epoch += (uint32_t)QL.nsub;
       if (nn > 0 && (((c + 1) % resync == 0) || c == nchunks - 1)) {
-        S_HIP(launch_compact(w[cur], w[1 - cur], &misc->nactive, nn, cscr, st));
+        S_HIP(launch_compact(w[cur], w[1 - cur], &misc->nactive, nn, cscr, nullptr, st));
         cur = 1 - cur;
       }
     }
