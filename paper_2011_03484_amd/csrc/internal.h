@@ -8,10 +8,15 @@ namespace tpm {
 // Wavefronts per SIMD for a particle launch when the caller leaves it to the
 // library: as many as the working set's tiles fill on every SIMD alike (at
 // least one, at most four).  An uneven split, some SIMDs holding one more
-// wavefront than others, lets the tiles on the shared SIMDs fall behind.
+// wavefront than others, lets the tiles on the shared SIMDs fall behind, but two
+// wavefronts take 15% fewer cycles a step than one alone: 20,000 steps of 1,563
+// tiles on 1,024 SIMDs 16.6 ms with one and 17.5 with two, of 2,032 tiles 21.4
+// and 19.3; the line is where they cross.
 inline int auto_waves_per_simd(int ntiles, int ncu) {
-  const int per = ntiles / (4 * (ncu > 0 ? ncu : 1));
-  return per < 1 ? 1 : (per > 4 ? 4 : per);
+  const int simds = 4 * (ncu > 0 ? ncu : 1);
+  const int per = ntiles / simds;
+  if (per <= 1) return 3 * ntiles < 5 * simds ? 1 : 2;
+  return per > 4 ? 4 : per;
 }
 
 
@@ -105,6 +110,11 @@ struct EphConst {
 // first work item; planet_rows): the launch's chunk, and the chunks after it
 // that the map may run ahead into.
 constexpr int STREAM_CHUNKS = 8;
+// Rows are published in groups that end with a cache line of 128 bytes: 16 rows of
+// 24 (np + 1) bytes are whole lines for every np, so counts c are published with
+// c + 1 a multiple of 16 (or at a chunk's end), and ring slots are multiples of
+// 16 rows.
+constexpr int ROW_GROUP = 16;
 struct RowStream {
   double* rj;                  // Jacobi planet state [np][3], at step `done`
   double* vj;
@@ -137,9 +147,6 @@ struct QueueLaunch {
   int workers;                 // wavefronts launched
   int block;                   // threads per workgroup (multiple of 64)
   int32_t* error;              // device flag set on an over-long wait
-  bool deep = false;           // planet rows fetched three steps ahead, not one (for
-                               // launches of one wavefront per SIMD)
-  bool spread = false;         // at most one wavefront per SIMD (see lds())
   const RowStream* stream = nullptr;   // the launch writes its own planet rows
   const EphConst* eph = nullptr;       // with the planet map's constants
 
@@ -153,20 +160,14 @@ struct QueueLaunch {
   unsigned long long grabs(int ntiles) const {
     return (unsigned long long)ntiles * nsub + (unsigned long long)blocks() * (block / 64);
   }
-  // LDS a workgroup asks for and does not use: a quarter of a compute unit's
-  // keeps one-wavefront workgroups to four a unit, one per SIMD.
-  unsigned lds() const { return spread && block == 64 ? 40u * 1024 - 512 : 0; }
 };
 
 // A launch with its own planet map whose tiles and map fit one wavefront per
-// SIMD takes each tile through the whole chunk as one item, at most one
-// wavefront to a SIMD: the wavefronts follow the map's rows with their
-// particles in registers, and none shares a SIMD with the map, which would
-// take most of its issue slots.
+// SIMD takes each tile through the whole chunk as one item: the wavefronts follow
+// the map's rows with their particles in registers.
 inline void lone_tiles(QueueLaunch& QL, int ntiles, int ncu) {
   if (!QL.stream || ntiles + 1 > 4 * ncu || QL.block != 64) return;
   QL.nsub = 1;
-  QL.spread = true;
 }
 
 // Particle chunk: nsteps steps through rows[0..nsteps] (row 0 = step0) over

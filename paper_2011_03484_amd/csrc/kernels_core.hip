@@ -71,6 +71,22 @@ TPM_DEV T karg_stream(KargPtr p, size_t off) {
 
 constexpr uint32_t SPIN_LIMIT = 1u << 22;   // about 4 s of polling
 
+// What one wavefront of a launch hands to another that may run on another die
+// (a tile's state between its items): stored through to memory and loaded from
+// there, each value by itself.  An agent-scope release and acquire would do it
+// for plain accesses, by writing back and invalidating the die's whole L2: 20 us
+// an item with every wavefront of the die doing so, and nobody's planet rows
+// stayed cached.  (shared_done: the stores before it have arrived.)
+template <typename T>
+TPM_DEV T shared_load(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+TPM_DEV void shared_store(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+TPM_DEV void shared_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 TPM_DEV unsigned long long wave_uniform(unsigned long long v) {
   uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
   uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
@@ -80,8 +96,9 @@ TPM_DEV unsigned long long wave_uniform(unsigned long long v) {
 // Steps of the launch's chunk whose closing rows are published, once that is
 // more than s (`have` already known to be): the planet map of the same launch
 // writes the rows as the particles follow (planet_rows).  The whole wavefront
-// polls the count with relaxed loads and acquires once when it has moved, so
-// that the rows behind it are read from memory and not from a stale line.
+// polls the count with relaxed loads.  The rows behind it need no acquire: a
+// count ends with a cache line (ROW_GROUP), so no line that holds a published
+// row was read, by anyone in this launch, before all of it was written.
 // A wait ends when the map, which always runs (see particle_queue), publishes
 // its next block; one in which it publishes nothing for the spin limit flags
 // an error and returns s.
@@ -92,7 +109,7 @@ TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
     const int64_t p = (int64_t)wave_uniform((unsigned long long)__hip_atomic_load(
                           cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) - begin;
     if (p > s) {
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // (orders the code only)
       return p < nsteps ? (int)p : nsteps;
     }
     __builtin_amdgcn_s_sleep(16);
@@ -110,9 +127,9 @@ TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
 // (wait_rows).  The step loop is uniform across the
 // wavefront (s_begin, s_end are wave-uniform); removed lanes are masked off
 // and the wavefront leaves early once none is active.  KIT > 0 fixes the
-// Newton count at compile time; DEPTH > 0 fetches each planet row DEPTH
-// steps ahead into VGPRs (for launches with a few wavefronts per SIMD; 0:
-// scalar loads at the point of use, for many).
+// Newton count at compile time; AHEAD fetches each planet row a step ahead into
+// VGPRs (for launches with a few wavefronts per SIMD; else scalar loads at the
+// point of use, for many).
 //
 // UNIV: a drift the fixed-iteration solve refuses is taken in universal
 // variables instead (drift_lanes); the particle is removed as KEPLER only if
@@ -120,17 +137,17 @@ TPM_DEV int wait_rows(KargPtr ka, int s, int nsteps) {
 // KA: w and out are read from the work-queue kernel's argument segment ka
 // where they are used (the item's start and end, a record), which leaves the
 // step loop's scalar registers to its constants.
-template <int NP, int KIT, int DEPTH, bool UNIV = false, bool KA = false>
+template <int NP, int KIT, bool AHEAD, bool UNIV = false, bool KA = false>
 TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A, int i,
                      bool valid, int s_begin, int s_end, KargPtr ka, int& have) {
   constexpr int ROW = 3 * NP + 3;
   const int kiters = KIT > 0 ? KIT : A.kiters;
   if (KA) w = karg_work(ka);
-  valid = valid && w.status[i] == ST_ACTIVE;
   double x = 0, y = 0, z = 0, vx = 0, vy = 0, vz = 0;
   if (valid) {
-    x = w.x[i]; y = w.y[i]; z = w.z[i];
-    vx = w.vx[i]; vy = w.vy[i]; vz = w.vz[i];
+    x = shared_load(w.x + i); y = shared_load(w.y + i); z = shared_load(w.z + i);
+    vx = shared_load(w.vx + i); vy = shared_load(w.vy + i); vz = shared_load(w.vz + i);
+    valid = shared_load(w.status + i) == ST_ACTIVE;
   }
   // A lane's removal record (the state it keeps, step, reason, planet) is
   // written out in the step that removes it.  `act` holds the lanes still
@@ -146,7 +163,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     if (A.handoff && why == ST_ENCOUNTER) {
       wr.x[i] = rx; wr.y[i] = ry; wr.z[i] = rz;
       wr.vx[i] = ux; wr.vy[i] = uy; wr.vz[i] = uz;
-      wr.status[i] = HANDOFF_BASE + (int32_t)(st - A.step0);
+      shared_store(wr.status + i, HANDOFF_BASE + (int32_t)(st - A.step0));
       return;
     }
     const Out o = KA ? karg_out(ka) : out;
@@ -156,7 +173,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     o.step[k] = st;
     o.reason[k] = why;
     o.planet[k] = pl;
-    wr.status[i] = why;
+    shared_store(wr.status + i, why);
   };
   double ax, ay, az;
   if (KA && have <= s_begin) {
@@ -206,7 +223,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
       if (have <= s0) break;                // the wait gave up (flagged)
     }
     const int lim = KA ? min(s_end, have) : s_end;
-    if (DEPTH == 1) {
+    if (AHEAD) {
       // The row that ends step s is fetched during step s - 1, into the one of
       // two alternating VGPR buffers that step s - 1 does not use: with few
       // wavefronts per SIMD nothing else hides that load's latency.
@@ -221,29 +238,6 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
         load_row<NP>(ra, rows + (size_t)min(s + 3, lim) * ROW, zero);
         step(s + 1, rb.v);
       }
-    } else if (DEPTH == 3) {
-      // Three steps ahead, four buffers in turn: with one wavefront per SIMD
-      // the particles run right behind the planet map, and a row just written
-      // on another die can take longer than a step to arrive.
-      const int zero = opaque_zero_vgpr();
-      Row<NP> ra, rb, rc, rd;
-      load_row<NP>(ra, rows + (size_t)(s0 + 1) * ROW, zero);
-      load_row<NP>(rb, rows + (size_t)min(s0 + 2, lim) * ROW, zero);
-      load_row<NP>(rc, rows + (size_t)min(s0 + 3, lim) * ROW, zero);
-      for (int s = s0; s < lim; s += 4) {
-        if (act == 0) break;
-        load_row<NP>(rd, rows + (size_t)min(s + 4, lim) * ROW, zero);
-        step(s, ra.v);
-        if (s + 1 >= lim) break;
-        load_row<NP>(ra, rows + (size_t)min(s + 5, lim) * ROW, zero);
-        step(s + 1, rb.v);
-        if (s + 2 >= lim) break;
-        load_row<NP>(rb, rows + (size_t)min(s + 6, lim) * ROW, zero);
-        step(s + 2, rc.v);
-        if (s + 3 >= lim) break;
-        load_row<NP>(rc, rows + (size_t)min(s + 7, lim) * ROW, zero);
-        step(s + 3, rd.v);
-      }
     } else {
       // many wavefronts per SIMD: rows by scalar loads at their use
       for (int s = s0; s < lim; ++s) {
@@ -256,8 +250,8 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
   }
   if (lane_in(act)) {
     const Work we = KA ? karg_work(ka) : w;
-    we.x[i] = x; we.y[i] = y; we.z[i] = z;
-    we.vx[i] = vx; we.vy[i] = vy; we.vz[i] = vz;
+    shared_store(we.x + i, x); shared_store(we.y + i, y); shared_store(we.z + i, z);
+    shared_store(we.vx + i, vx); shared_store(we.vy + i, vy); shared_store(we.vz + i, vz);
   }
 }
 
@@ -286,7 +280,7 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
 template <int NP>
 TPM_DEV void run_planet_rows(KargPtr ka);
 
-template <int NP, int KIT, bool UNIV, int DEPTH>
+template <int NP, int KIT, bool UNIV>
 __global__ void __launch_bounds__(256, 2)
 particle_queue(Work w, const int32_t* __restrict__ d_nactive, Out out, RowStream R,
                const double* rows, ChunkArgs<NP> A, QueueArgs Q, EphConst E) {
@@ -325,20 +319,17 @@ particle_queue(Work w, const int32_t* __restrict__ d_nactive, Out out, RowStream
         }
         __builtin_amdgcn_s_sleep(2);
       }
-      // One acquire after the wait.  An acquire per poll would invalidate
-      // the caches (L2 included on this multi-die device) on every iteration,
-      // costing every wavefront on the die its cached planet rows.
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // (orders the code only)
     }
     const int s_begin = s * Q.sub_steps;
     const int s_end = min(Q.nsteps, s_begin + Q.sub_steps);
     if (go && s_begin < s_end) {       // the last sub-chunks of a short chunk may be empty
       const int i = t * 64 + lane;
-      advance<NP, KIT, DEPTH, UNIV, true>(w, out, rows, A, i, i < n, s_begin, s_end, ka, have);
+      advance<NP, KIT, true, UNIV, true>(w, out, rows, A, i, i < n, s_begin, s_end, ka, have);
     }
-    // publish completion; the release orders every store of this item
-    __hip_atomic_store(Q.progress + t, Q.epoch + (uint32_t)s + 1u, __ATOMIC_RELEASE,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    // publish completion, after the state has arrived
+    shared_done();
+    shared_store(Q.progress + t, Q.epoch + (uint32_t)s + 1u);
   }
 }
 
@@ -369,9 +360,9 @@ TPM_DEV void batch_item(const SysDev& S, Work w, Out out, const double* __restri
   const bool valid = lane < T.count;
   int have = s_end;                    // the rows are written before the launch
   if (quick_serves(S.kiters, S.ftol))
-    advance<NP, 5, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
+    advance<NP, 5, false>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
   else
-    advance<NP, 0, 0>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
+    advance<NP, 0, false>(w, out, rows, A, i, valid, s_begin, s_end, nullptr, have);
 }
 
 __global__ void __launch_bounds__(256)
@@ -402,10 +393,7 @@ particle_batch_queue(const SysDev* __restrict__ sys, const TileDesc* __restrict_
         }
         __builtin_amdgcn_s_sleep(2);
       }
-      // One acquire after the wait.  An acquire per poll would invalidate
-      // the caches (L2 included on this multi-die device) on every iteration,
-      // costing every wavefront on the die its cached planet rows.
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");   // (orders the code only)
     }
     const int s_begin = s * Q.sub_steps;
     const int s_end = min(Q.nsteps, s_begin + Q.sub_steps);
@@ -424,8 +412,8 @@ particle_batch_queue(const SysDev* __restrict__ sys, const TileDesc* __restrict_
         default: batch_item<8>(S, w, out, ring, Q, T, s_begin, s_end, lane); break;
       }
     }
-    __hip_atomic_store(Q.progress + t, Q.epoch + (uint32_t)s + 1u, __ATOMIC_RELEASE,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    shared_done();
+    shared_store(Q.progress + t, Q.epoch + (uint32_t)s + 1u);
   }
 }
 
@@ -592,27 +580,16 @@ static hipError_t launch_np(const SysConst& S, Work w, const int32_t* d_nactive,
   R.ctr_alone = QL.grabs(Q.ntiles);
   if (Q.ntiles <= 0 && !R.on) return hipSuccess;
   const int nblocks = QL.blocks();
-#define TPM_PQ(KIT, UNIV, DEPTH)                                                                \
-  hipLaunchKernelGGL((particle_queue<NP, KIT, UNIV, DEPTH>), dim3(nblocks), dim3(QL.block),     \
-                     QL.lds(), st,                                                              \
-                     w, d_nactive, out, R, rows, A, Q, E)
+#define TPM_PQ(KIT, UNIV)                                                                     \
+  hipLaunchKernelGGL((particle_queue<NP, KIT, UNIV>), dim3(nblocks), dim3(QL.block), 0, st, w, \
+                     d_nactive, out, R, rows, A, Q, E)
   const bool quick = quick_serves(S.kiters, S.ftol);
-  if (QL.deep) {
-    if (quick) {
-      if (S.universal) TPM_PQ(5, true, 3);
-      else TPM_PQ(5, false, 3);
-    } else {
-      if (S.universal) TPM_PQ(0, true, 3);
-      else TPM_PQ(0, false, 3);
-    }
+  if (quick) {
+    if (S.universal) TPM_PQ(5, true);
+    else TPM_PQ(5, false);
   } else {
-    if (quick) {
-      if (S.universal) TPM_PQ(5, true, 1);
-      else TPM_PQ(5, false, 1);
-    } else {
-      if (S.universal) TPM_PQ(0, true, 1);
-      else TPM_PQ(0, false, 1);
-    }
+    if (S.universal) TPM_PQ(0, true);
+    else TPM_PQ(0, false);
   }
 #undef TPM_PQ
   return hipGetLastError();
@@ -921,7 +898,7 @@ TPM_DEV bool eph_step(const EphConst& E, const EphLane& L, const EphW<NP>& W, do
 // after each block of steps: here nothing to do, go on.
 constexpr int EPH_BLOCK = 64;
 struct EphNoBlockEnd {
-  TPM_DEV int block(int left) const { return min(left, EPH_BLOCK); }
+  TPM_DEV int block(int, int left) const { return min(left, EPH_BLOCK); }
   TPM_DEV bool operator()(int) const { return true; }
 };
 
@@ -1011,7 +988,7 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
   int done = 0;
   while (done < nsteps) {
     const int s0 = done;
-    const int nb = ROWB ? nsteps : block_end.block(nsteps - s0);
+    const int nb = ROWB ? nsteps : block_end.block(s0, nsteps - s0);
     done = s0 + nb;
     if (!ROWB && fast) {
       const double sjx = jx, sjy = jy, sjz = jz, swx = wx, swy = wy, swz = wz;
@@ -1128,7 +1105,7 @@ TPM_DEV int ephemeris_quad(EP E, double* __restrict__ rj, double* __restrict__ v
   int done = 0;
   while (done < nsteps) {
     const int s0 = done;
-    const int nb = block_end.block(nsteps - s0);
+    const int nb = block_end.block(s0, nsteps - s0);
     done = s0 + nb;
     if (fast) {
       const double sj = j, sw = w, sa = a;
@@ -1187,7 +1164,17 @@ struct EphPublish {
   const RowStream& R;
   int64_t done;                              // the count when the body started
   bool ahead;
-  TPM_DEV int block(int left) const { return min(left, max(8, min(32, left >> 2))); }
+  int first;                                 // the chunk's step the body started from
+  // Steps of the block after `s` of the body's: to a count c of the chunk's steps
+  // whose rows 0..c fill cache lines (see wait_rows), or the chunk's end.  About
+  // a quarter of what is left, at most 32, so that the last wait is short.
+  TPM_DEV int block(int s, int left) const {
+    const int c = first + s;
+    const int want = c == 0 ? ROW_GROUP : max(ROW_GROUP, min(2 * ROW_GROUP, left >> 2));
+    int nb = (c + want + 1) / ROW_GROUP * ROW_GROUP - 1 - c;
+    if (nb <= 0) nb += ROW_GROUP;
+    return min(left, nb);
+  }
   TPM_DEV bool operator()(int t) const {
     // the release makes the rows written so far visible before the count
     __hip_atomic_store(R.done, done + t, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -1230,7 +1217,7 @@ static __device__ __attribute__((noinline)) TPM_PLANET_KERNEL void planet_rows(u
         R.step0 + (b - R.begin) + s0, R.flag,
         R.vside ? R.vside + (size_t)slot * 6 * NP : nullptr,
         VEL ? R.vring + (size_t)(slot * R.vslot_rows + s0) * 3 * NP : nullptr, s0 > 0,
-        EphPublish{R, done, j > 0});
+        EphPublish{R, done, j > 0, s0});
     done += n;
     if (n < len - s0) break;
     b += len;

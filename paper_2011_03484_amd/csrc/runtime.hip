@@ -505,6 +505,7 @@ int ensure_handoff(tpm_sim* s, int64_t rows, int64_t slots) {
 
 // Planet-table ring of `slots` slots of `rows` rows for the current planets.
 int ensure_ring(tpm_sim* s, int64_t rows, int64_t slots = NSLOT) {
+  rows = (rows + ROW_GROUP - 1) / ROW_GROUP * ROW_GROUP;
   const size_t bytes = sizeof(double) * (size_t)slots * rows * (3 * s->np + 3);
   if (s->ring_cap < bytes) {
     TPM_HIP(hipStreamSynchronize(s->sE));
@@ -1231,7 +1232,6 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
                                                  : auto_waves_per_simd(ntiles, s->ncu);
       s->last_wps = wps;
       QL.workers = std::max(1, std::min(ntiles * QL.nsub, 4 * s->ncu * wps));
-      QL.deep = wps == 1 && !ho;
       QL.workers = std::min(QL.workers, ntiles);
       QL.block = s->opt.block_threads;
       QL.error = s->d_qerr;
