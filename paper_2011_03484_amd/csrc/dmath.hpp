@@ -159,23 +159,30 @@ TPM_DEV void sincos_poly(double r, double& s, double& m) {
 // The planet map's lone wavefront runs it faster (its time is its instruction
 // count); the particle kernels, with many wavefronts per SIMD, prefer Estrin's
 // shorter chains.  The values agree to rounding.
-TPM_DEV void sincos_poly_horner(double r, double& s, double& m) {
-  const double z = r * r;
-  double ps = fma_(S17, z, S15);
+// (series_horner: their series in z = r^2, sin r = r + r z ps and
+// cos r - 1 = -z/2 + z^2 pc.)
+TPM_DEV void series_horner(double z, double& ps, double& pc) {
+  ps = fma_(S17, z, S15);
   ps = fma_(ps, z, S13);
   ps = fma_(ps, z, S11);
   ps = fma_(ps, z, S9);
   ps = fma_(ps, z, S7);
   ps = fma_(ps, z, S5);
   ps = fma_(ps, z, S3);
-  s = fma_(r * z, ps, r);
-  double pc = fma_(C18, z, C16);
+  pc = fma_(C18, z, C16);
   pc = fma_(pc, z, C14);
   pc = fma_(pc, z, C12);
   pc = fma_(pc, z, C10);
   pc = fma_(pc, z, C8);
   pc = fma_(pc, z, C6);
   pc = fma_(pc, z, C4);
+}
+
+TPM_DEV void sincos_poly_horner(double r, double& s, double& m) {
+  const double z = r * r;
+  double ps, pc;
+  series_horner(z, ps, pc);
+  s = fma_(r * z, ps, r);
   m = fma_(z * z, pc, -0.5 * z);
 }
 

@@ -433,18 +433,14 @@ TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ft
 // taken another path (the short range not allowed, or more Newton steps); the
 // results are the general form's bit for bit where no lane of the wavefront
 // is bad.  The general form leaves `bad` false.
-// STANDIN: lanes without a body already hold such a stand-in (r^2 = v^2 =
-// mu = 1, u = 0, dt = 0), so the fast form needs no selects for them; an
-// unbound body is then bad too.
-template <bool FAST, bool STANDIN = false>
+template <bool FAST>
 TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, double v2, double u,
                        double& f, double& g, double& fd, double& gd, bool& bad) {
-  constexpr bool PLAIN = FAST && STANDIN;
   double r0, rinv;
-  sqrt_rsqrt(PLAIN || lane_on ? r2 : 1.0, r0, rinv);
+  sqrt_rsqrt(lane_on ? r2 : 1.0, r0, rinv);
   double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
   const bool bound = alpha > 0.0;
-  const bool idle = PLAIN ? false : !(lane_on && bound);
+  const bool idle = !(lane_on && bound);
   alpha = idle ? 1.0 : alpha;
   dt = idle ? 0.0 : dt;
   double sa, rsa;
@@ -472,7 +468,6 @@ TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, do
     bool conv;
     xk = planet_newton2(ec, es, om, dM, idle, xk, s, m, conv);
     bad = !(idle | short_args(dM, w)) | !conv;
-    if (PLAIN) bad = bad | !bound;
   } else {
     bad = false;
     if (wave_all(idle | short_args(dM, w)))
@@ -488,6 +483,71 @@ TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, do
   fd = -(a * a) * n * s * rinv * r1inv;
   gd = fma_(a * r1inv, m, 1.0);
   return bound;
+}
+
+// f, g, fdot and gdot of a planet's drift in the fewest instructions (the planet
+// map's lone wavefront is bound by their number), for arcs up to three quarters
+// of a radian and eccentricities up to 0.4: one step of fourth order from the
+// third-order series start (see drift_quick, whose quantities these are), and
+// the sine and cosine carried over to the root by the rotation, where a second
+// Newton step would evaluate them again.  With y = 1/F', u = F y, A = F'' y/2 and
+// B = (y - 1)/6 (the third derivative is 1 - F') the step is -u (1 + u (A + u (2 A^2 -
+// B))), the inverse series of F.  What it leaves is at most eb y d^4 (the next
+// term, 5 A^3 - 5 A B + y/24 of the fourth derivative, is below 0.6 eb y for eb <= 0.4): a lane is
+// served where that is below 2^-54 |x| and |d| <= 2^-14, from where on the
+// rotation's first term left out, d^4/24, would show.  sin x - x is summed from
+// small terms and enters g as such, where sin x minus x would bring in half
+// an ulp of x.  Where it is not
+// served (or out of the ranges, or unbound: NaN) planet_fg takes the lane; the
+// choice is the lane's own, so it does not depend on the map's blocks.  A lane
+// without a body holds a stand-in (r^2 = v^2 = mu = 1, u = 0, dt = 0), which
+// comes out as f = gdot = 1, g = fdot = 0.
+TPM_DEV bool planet_quick(const KepConst& K, double dt, double r2, double v2, double u, double& f,
+                          double& g, double& fd, double& gd) {
+  double r0, rinv;
+  sqrt_rsqrt(r2, r0, rinv);
+  const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
+  double sa, rsa;
+  sqrt_rsqrt(alpha, sa, rsa);
+  const double a = rsa * rsa;             // meets cos x - 1 and sin x - x only
+  const double ms = K.sqrt_mu * sa;       // n a
+  const double dM = ms * alpha * dt;
+  const double ninv = K.inv_sqrt_mu * rsa * a;
+  const double ec = fma_(-r0, alpha, 1.0);
+  const double es = u * sa * K.inv_sqrt_mu;
+  const double eb = __builtin_fabs(ec) + __builtin_fabs(es);
+  const double om = 1.0 - ec;
+  const double ar = a * rinv;             // 1/om
+  const double t = dM * ar;
+  const double h = (0.5 * es) * ar;
+  const double c3 = ar * fma_(es, h, ec * (-1.0 / 6.0));
+  const double x0 = t * fma_(t, fma_(t, c3, -h), 1.0);
+  const double z = x0 * x0;
+  double ps, pc;
+  series_horner(z, ps, pc);
+  const double sx = (x0 * z) * ps;        // sin x0 - x0
+  const double sv = x0 + sx;
+  const double mv = fma_(z * z, pc, -0.5 * z);
+  const double F = fma_(-ec, sv, fma_(-es, mv, x0 - dM));
+  const double y = rcp_newton(fma_(-ec, mv, fma_(es, sv, om)));
+  const double U = F * y;
+  const double A = fma_(ec, sv, fma_(es, mv, es)) * (0.5 * y);
+  const double B = fma_(y, 1.0 / 6.0, -1.0 / 6.0);
+  const double d = U * fma_(U, fma_(U, fma_(A + A, A, -B), A), 1.0);
+  const double x = x0 - d;
+  const double d2 = d * d, q = 0.5 * d2;
+  const double e3 = (d * d2) * (1.0 / 6.0);
+  const double sd = d - e3;               // sin d
+  const double smx = sx + fma_(-mv, sd, fma_(-sv, q, e3));   // sin x - x
+  const double s = x + smx;
+  const double m = fma_(sv, sd, fma_(-(1.0 + mv), q, mv));
+  const double iFp = rcp(fma_(-ec, m, fma_(es, s, om)));
+  f = fma_(ar, m, 1.0);
+  g = fma_(smx, ninv, dt);
+  fd = -((ms * rinv) * (s * iFp));
+  gd = fma_(iFp, m, 1.0);
+  return (__builtin_fabs(x0) <= 0.75) & (eb <= 0.4) & (__builtin_fabs(d) <= 0x1p-14) &
+         ((eb * y) * (d2 * d2) <= 0x1p-54 * __builtin_fabs(x));
 }
 
 // The converged drift of a planet held as three components on one lane.

@@ -12,7 +12,7 @@
 // and a step is
 //  * half kick, one FMA;
 //  * drift: r^2, v^2 and r.v as sums over the quad, a block each, broadcast
-//    along the row; f, g, fdot, gdot by planet_fg; two FMA pairs;
+//    along the row; f, g, fdot, gdot by planet_quick; two FMA pairs;
 //  * one product gives sixteen difference vectors d, four a block: block 0 the
 //    planets' heliocentric positions, block 2 their Jacobi positions, blocks 1
 //    and 3 the planet pairs.  g = d/|d|^3 then costs one evaluation for all;
@@ -28,12 +28,13 @@
 // pair i < j with mu_j in a'_i, -mu_i - mu_i mu_j/eta_{j-1} in a'_j and
 // -mu_i mu_j/eta_{b-1} between them.
 //
-// Bound by the instructions of the one wavefront (about 190 vector ones a step
+// Bound by the instructions of the one wavefront (about 165 vector ones a step
 // against 366, at some 5.5 cycles each; three products of 20 cycles).  Four
-// giant planets: 0.544 us a step, 0.887 before (0.92 inside a particle launch);
-// the error against extended precision over 24 starts and 4,000 steps is 0.87
-// of the other form's (1.7e-12 against 1.9e-12).  With more than four planets
-// the vectors no longer fit one product per lane, and the other form stays.
+// giant planets: 0.49 us a step, 0.887 in the other form (0.56 with planet_fg's
+// two Newton steps for the drift); the error against extended precision over 240
+// starts is that of the other form (2.27e-13 rms after 1,000 steps against
+// 2.25e-13).  With more than four planets the vectors no longer fit one product
+// per lane, and the other form stays.
 #pragma once
 #include "kepler.hpp"
 
@@ -155,13 +156,25 @@ TPM_DEV bool quad_accel(const EphQuad& Q, double j, double& d, double& a, double
   return d2 < Q.hill2;
 }
 
-// Kepler drift of the state (j, w).
+// Kepler drift of the state (j, w).  FAST: `bad` is set on a lane that
+// planet_quick does not serve; else such a lane takes planet_fg.
 template <bool FAST>
 TPM_DEV bool quad_drift(const EphQuad& Q, double& j, double& w, bool& bad) {
   const double p = quad_sum((Q.dot_v ? w : j) * (Q.dot_r ? j : w));
+  const double r2 = row_lane<0>(p), v2 = row_lane<4>(p), u = row_lane<8>(p);
   double f, g, fd, gd;
-  const bool bound = planet_fg<FAST, true>(Q.K, Q.dt, Q.on, row_lane<0>(p), row_lane<4>(p),
-                                           row_lane<8>(p), f, g, fd, gd, bad);
+  const bool served = planet_quick(Q.K, Q.dt, r2, v2, u, f, g, fd, gd);
+  bool bound = true;
+  bad = FAST & !served;
+  if (!FAST && !wave_all(served)) {
+    double f1, g1, fd1, gd1;
+    const bool b = planet_fg<false>(Q.K, Q.dt, Q.on, r2, v2, u, f1, g1, fd1, gd1, bad);
+    bound = served | b;
+    f = served ? f : f1;
+    g = served ? g : g1;
+    fd = served ? fd : fd1;
+    gd = served ? gd : gd1;
+  }
   const double nj = fma_(f, j, g * w);
   w = fma_(fd, j, gd * w);
   j = nj;
