@@ -283,7 +283,12 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
 //    eccentricities up to 0.5, where the third-order one left 2% of the lanes,
 //    and with them seven wavefronts in ten, to a second step.
 //  * |x| <= 0.3 leaves the last terms of the sine and cosine series below
-//    2^-55 of the sum.
+//    2^-55 of the sum.  sin x - x enters g as summed, not as a difference.
+//  * |r| and sqrt(alpha) are one product each, without the correction of
+//    sqrt_rsqrt: an error of theirs meets the result through the arc x, or, |r| in
+//    1 - ec = |r| alpha, shifts the orbit by as much as a rounding of r would.
+//    (1 - ec must come from the same alpha: from v^2 directly the velocities
+//    lose a tenth to a fifth at arcs of 0.1 to 0.25.)  |r|^2 is the step before's.
 //  * gdot = 1 + m/F', fdot = -(n a)(sin x / r0)/F' and n a = sqrt(mu alpha), all
 //    without r1; 1/F' at the root continues the step's reciprocal (F' has moved
 //    by less than 2^-26).
@@ -295,35 +300,33 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
 // drift_fixed.  All of it is the lane's own decision; the branches only skip
 // what no lane of act needs.  Lane predicates are kept as lane masks: as
 // booleans the compiler carries them through vector registers.
-// With it a lone wavefront's step of four planets takes less than the planet
-// map's 0.55 us (0.78 before); 10,000 steps of 13,313 particles 5.8 ms instead
-// of 9.5, of 200,000 15.9 instead of 22.1.  Rounding errors of one drift are the
-// same as drift_fixed's (5.7e-17 rms in position, 7.4e-17 to 8.5e-17 in velocity).
+// With it a lone wavefront's step of four planets takes about 0.52 us (0.78 with
+// drift_fixed; the planet map 0.49); 10,000 steps of 13,313 particles 5.3 ms
+// (9.5 with drift_fixed and the map of then), of 200,000 15.0 (22.1).  Rounding
+// errors of one drift are no larger than drift_fixed's (rms 5.7e-17 in position;
+// in velocity 7.4e-17 to 8.6e-17 against 7.4e-17 to 8.7e-17).
 constexpr double QUICK_FTOL = 1e-14;   // smallest failure threshold it may serve
 
-// sin x and cos x - 1 for |x| <= 0.31.
-TPM_DEV void sincos_short(double x, double& s, double& m) {
+// sin x - x and cos x - 1 for |x| <= 0.31.
+TPM_DEV void sinm_short(double x, double& sx, double& m) {
   const double z = x * x;
   const double z2 = z * z;
   const double z4 = z2 * z2;
   const double s01 = fma_(S5, z, S3), s23 = fma_(S9, z, S7), s45 = fma_(S13, z, S11);
-  s = fma_(x * z, fma_(z4, s45, fma_(z2, s23, s01)), x);
+  sx = (x * z) * fma_(z4, s45, fma_(z2, s23, s01));
   const double c01 = fma_(C6, z, C4), c23 = fma_(C10, z, C8);
   m = fma_(z2, fma_(z4, C12, fma_(z2, c23, c01)), -0.5 * z);
 }
 
-// Returns the fine lanes; the others' states mean nothing.
-TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double& x, double& y,
-                         double& z, double& vx, double& vy, double& vz, double& xk, double& s,
-                         double& m) {
-  const double r2 = fma_(x, x, fma_(y, y, z * z));
+// r2: |r|^2.  Returns the fine lanes; the others' states mean nothing.
+TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double r2, double& x,
+                             double& y, double& z, double& vx, double& vy, double& vz, double& xk,
+                             double& s, double& m) {
   const double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
   const double u = fma_(x, vx, fma_(y, vy, z * vz));
-  double r0, rinv;
-  sqrt_rsqrt(r2, r0, rinv);
+  const double rinv = rsqrt(r2), r0 = r2 * rinv;
   const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
-  double sa, rsa;
-  sqrt_rsqrt(alpha, sa, rsa);             // NaN for unbound lanes, which are not fine
+  const double rsa = rsqrt(alpha), sa = alpha * rsa;   // NaN for unbound lanes: not fine
   const double a = rsa * rsa;             // meets cos x - 1 and sin x - x only
   const double ms = K.sqrt_mu * sa;       // n a
   const double dM = ms * alpha * dt;
@@ -339,37 +342,39 @@ TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double&
   const double c4 = h * fma_(5.0, fma_(h, h, -c3), 1.0 / 12.0);
   xk = t * fma_(t, fma_(t, fma_(t, c4, c3), -h), 1.0);
   const uint64_t range = lanes(__builtin_fabs(t) <= 0.25) & lanes(eb <= 0.75);
-  double iFp;
-  auto newton = [&](double x0, double& xn, double& sn, double& mn, double& yn) {
-    double sv, mv;
-    sincos_short(x0, sv, mv);
+  double iFp, smx;                        // smx: sin x - x
+  auto newton = [&](double x0, double& xn, double& sxn, double& mn, double& yn) {
+    double sx, mv;
+    sinm_short(x0, sx, mv);
+    const double sv = x0 + sx;
     const double F = fma_(-ec, sv, fma_(-es, mv, x0 - dM));
     yn = rcp_newton(fma_(-ec, mv, fma_(es, sv, om)));
     xn = fma_(-F, yn, x0);
     const double d = x0 - xn;
-    sn = fma_(-(1.0 + mv), d, sv);
+    sxn = fma_(-mv, d, sx);
     mn = fma_(sv, d, mv);
     const double ad = __builtin_fabs(d);
     return range & lanes(ad <= 0x1p-28) &
            lanes(eb * yn * (ad * ad) <= 0x1p-54 * __builtin_fabs(xn));
   };
-  uint64_t fine = newton(xk, xk, s, m, iFp);
+  uint64_t fine = newton(xk, xk, smx, m, iFp);
   if (act & ~fine) {
-    double xn, sn, mn, yn;
-    const uint64_t f2 = newton(xk, xn, sn, mn, yn);
+    double xn, sxn, mn, yn;
+    const uint64_t f2 = newton(xk, xn, sxn, mn, yn);
     const bool mine = lane_in(fine);
     xk = mine ? xk : xn;
-    s = mine ? s : sn;
+    smx = mine ? smx : sxn;
     m = mine ? m : mn;
     iFp = mine ? iFp : yn;
     fine |= f2;
   }
+  s = xk + smx;
   {
     const double e = fma_(-fma_(-ec, m, fma_(es, s, om)), iFp, 1.0);
     iFp = fma_(iFp, fma_(e, e, e), iFp);
   }
   const double f = fma_(ar, m, 1.0);
-  const double g = fma_(s - xk, ninv, dt);
+  const double g = fma_(smx, ninv, dt);
   const double fd = -((ms * rinv) * (s * iFp));
   const double gd = fma_(iFp, m, 1.0);
   const double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
@@ -390,11 +395,12 @@ __host__ TPM_DEV bool quick_serves(int kiters, double ftol) {
 }
 
 TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ftol, bool quick,
-                             bool univ, uint64_t act, double& x, double& y, double& z, double& vx,
-                             double& vy, double& vz, double& xk, double& s, double& m) {
+                             bool univ, uint64_t act, double r2, double& x, double& y, double& z,
+                             double& vx, double& vy, double& vz, double& xk, double& s,
+                             double& m) {
   const double ox = x, oy = y, oz = z, ux = vx, uy = vy, uz = vz;
   uint64_t rest = act;
-  if (quick) rest = act & ~drift_quick(K, dt, act, x, y, z, vx, vy, vz, xk, s, m);
+  if (quick) rest = act & ~drift_quick(K, dt, act, r2, x, y, z, vx, vy, vz, xk, s, m);
   if (rest == 0) return 0;
   if (quick && univ) {
     double px = ox, py = oy, pz = oz, qx = ux, qy = uy, qz = uz;
@@ -418,6 +424,14 @@ TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ft
     }
   }
   return lanes(!ok);
+}
+
+// The same from the state alone.
+TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ftol, bool quick,
+                             bool univ, uint64_t act, double& x, double& y, double& z, double& vx,
+                             double& vy, double& vz, double& xk, double& s, double& m) {
+  return drift_lanes(K, dt, kiters, ftol, quick, univ, act, fma_(x, x, fma_(y, y, z * z)), x, y, z,
+                     vx, vy, vz, xk, s, m);
 }
 
 // f, g, fdot and gdot of a planet's converged Kepler drift from r^2, v^2 and
@@ -504,8 +518,7 @@ TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, do
 // comes out as f = gdot = 1, g = fdot = 0.
 TPM_DEV bool planet_quick(const KepConst& K, double dt, double r2, double v2, double u, double& f,
                           double& g, double& fd, double& gd) {
-  double r0, rinv;
-  sqrt_rsqrt(r2, r0, rinv);
+  const double rinv = rsqrt(r2), r0 = r2 * rinv;
   const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
   double sa, rsa;
   sqrt_rsqrt(alpha, sa, rsa);

@@ -175,14 +175,15 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     o.planet[k] = pl;
     shared_store(wr.status + i, why);
   };
-  double ax, ay, az;
+  double ax, ay, az, r2;
   if (KA && have <= s_begin) {
     have = wait_rows(ka, s_begin, A.nsteps);
     if (have <= s_begin) return;            // the wait gave up (flagged)
   }
   {
     const int hit = accel<NP>(rows + (size_t)s_begin * ROW, A.P, x, y, z, ax, ay, az);
-    const bool far = fma_(x, x, fma_(y, y, z * z)) > A.rmax2;
+    r2 = fma_(x, x, fma_(y, y, z * z));
+    const bool far = r2 > A.rmax2;
     if (valid) {
       if (hit >= 0) record(ST_ENCOUNTER, A.step0 + s_begin, hit, x, y, z, vx, vy, vz);
       else if (far) record(ST_ESCAPE, A.step0 + s_begin, -1, x, y, z, vx, vy, vz);
@@ -195,12 +196,13 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     double nx = x, ny = y, nz = z;
     double nvx = fma_(h, ax, vx), nvy = fma_(h, ay, vy), nvz = fma_(h, az, vz);
     double xk, sk, mk;
-    const uint64_t bad = drift_lanes(A.K, A.dt, kiters, A.ftol, KIT == 5, UNIV, act, nx, ny, nz,
-                                     nvx, nvy, nvz, xk, sk, mk);
+    const uint64_t bad = drift_lanes(A.K, A.dt, kiters, A.ftol, KIT == 5, UNIV, act, r2, nx, ny,
+                                     nz, nvx, nvy, nvz, xk, sk, mk);
     double bx, by, bz;
     uint64_t near;
     const auto hit_of = accel_near<NP>(row, A.P, nx, ny, nz, bx, by, bz, near);
-    const uint64_t far = lanes(fma_(nx, nx, fma_(ny, ny, nz * nz)) > A.rmax2);
+    r2 = fma_(nx, nx, fma_(ny, ny, nz * nz));
+    const uint64_t far = lanes(r2 > A.rmax2);
     nvx = fma_(h, bx, nvx); nvy = fma_(h, by, nvy); nvz = fma_(h, bz, nvz);
     const uint64_t gone = act & (bad | near | far);
     if (gone) {
