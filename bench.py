@@ -94,6 +94,9 @@ def counter_figures(path: str = COUNTERS_JSON):
 DEFAULT_CHUNK_STEPS, FIRST_CHUNK_STEPS, DEFAULT_SUB_CHUNKS = 8192, 1024, 64
 
 
+EPH_BENCH_ARGS = "--ephemeris-only --nsteps 100000"
+
+
 def default_chunks(nsteps: int) -> list:
     """Chunk lengths of an on-the-fly run of nsteps with the default options."""
     out, done = [], 0
@@ -118,8 +121,6 @@ def summarize_counters(pmc_dir: str) -> None:
         k = r["Kernel_Name"]
         if "particle_queue" in k:
             return "particle_queue<4,5>"
-        if "ephemeris_chunk" in k:
-            return "ephemeris_chunk<4>"
         if "copyBuffer" in k and int(r["Grid_Size"]) == 131072:
             return "device copy 256 MiB"
         return None
@@ -184,7 +185,8 @@ def summarize_counters(pmc_dir: str) -> None:
             f"{per('SQ_INSTS_VALU_ADD_F64'):.1f} add, {per('SQ_INSTS_VALU_TRANS_F64'):.1f} "
             f"transcendental; flops (FMA = 2) {fpps:.1f}.  The method's five Newton steps count "
             f"{ALGORITHMIC_FLOPS_PER_PARTICLE_STEP[4]} (the algorithmic figure of the roofline); "
-            "lanes stop once converged.  Masked lanes of removed particles are included.",
+            "lanes stop once converged.  Masked lanes of removed particles are included, and so is the "
+            "one wavefront of the launch that runs the planet map.",
             f"* SIMD VALU occupancy: SQ_ACTIVE_INST_VALU / (1024 SIMDs x {kt * 1e3:.1f} ms x 2.4 GHz "
             f"/ 4) = {busy * 100:.0f}%.",
             f"* FP64 rate under the profiler: {fpps:.1f} x {aps:.4g} / {kt * 1e3:.1f} ms = "
@@ -208,7 +210,7 @@ def summarize_counters(pmc_dir: str) -> None:
                "active_particle_steps_per_launch": aps / launches, "summary": os.path.basename(COUNTERS_MD)},
               open(COUNTERS_JSON, "w"), indent=1)
     print("\n".join(out[-6:]))
-    summarize_ephemeris(pmc_dir, tot, cnt, steps, src)
+    summarize_ephemeris(pmc_dir, src)
 
 
 def summarize_resonant_counters(pmc_dir: str) -> None:
@@ -216,22 +218,21 @@ def summarize_resonant_counters(pmc_dir: str) -> None:
     FP64 flops per active particle-step (json) from the rocprofv3 pass in
     pmc_dir/r1, made by `rocprofv3 --pmc <RES_PMC> --kernel-trace -f csv -d
     <pmc_dir>/r1 -o run -- python3 bench.py <RES_PMC_BENCH_ARGS>` with its
-    output in <pmc_dir>/r1.log.  The resonant run's particle launches are the
-    kernel variant with a one-step row prefetch (several wavefronts per SIMD);
-    the small headline run before it uses the three-step one."""
+    output in <pmc_dir>/r1.log.  The resonant run's particle launches are told
+    from the small headline run's before it by their size."""
     import collections
     import csv
-    res_kernel = "particle_queue<4, 5, false, 1>"
+    res_kernel, res_threads = "particle_queue<4, 5, false>", 64 * 1024
     tot = collections.Counter()
     launches = 0
     for r in csv.DictReader(open(os.path.join(pmc_dir, "r1", "run_counter_collection.csv"))):
-        if res_kernel in r["Kernel_Name"]:
+        if res_kernel in r["Kernel_Name"] and int(r["Grid_Size"]) > res_threads:
             tot[r["Counter_Name"]] += float(r["Counter_Value"])
             if r["Counter_Name"] == "SQ_WAVES":
                 launches += 1
     kt = 0.0
     for r in csv.DictReader(open(os.path.join(pmc_dir, "r1", "run_kernel_trace.csv"))):
-        if res_kernel in r["Kernel_Name"]:
+        if res_kernel in r["Kernel_Name"] and int(r["Grid_Size_X"]) > res_threads:
             kt += (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9
     run = json.loads([x for x in open(os.path.join(pmc_dir, "r1.log")) if x.startswith("{")][-1])
     src = run["kernel_sources"]
@@ -248,7 +249,7 @@ def summarize_resonant_counters(pmc_dir: str) -> None:
            f"-o run -- python3 <repo>/bench.py {RES_PMC_BENCH_ARGS} > <out>/r1.log", "",
            f"Kernel sources of the counted run: `bench.kernel_source_hash()` = `{src}`.", "",
            f"Sums over the resonant run's {launches} particle launches ({res_kernel}; the "
-           "1,024-particle headline run before it uses another variant and is left out), from "
+           "1,024-particle headline run before it is left out), from "
            "`run_counter_collection.csv`:", "", "| counter | value |", "|---|---|"]
     for c, v in tot.items():
         out.append(f"| {c} | {v:.6g} |")
@@ -266,60 +267,50 @@ def summarize_resonant_counters(pmc_dir: str) -> None:
     print("\n".join(out[-3:]))
 
 
-def summarize_ephemeris(pmc_dir: str, tot, cnt, steps: int, src: str) -> None:
-    """The planet map's part of the same counter passes (one wavefront, serial
-    in time), per step, and its kernel-trace time beside the particle kernel
-    (pass 2) and alone (`python3 bench.py --ephemeris-only --nsteps 100000`
-    under `rocprofv3 --kernel-trace -f csv -d <pmc_dir>/alone -o run`)."""
+def summarize_ephemeris(pmc_dir: str, src: str) -> None:
+    """The planet map per step (one wavefront, serial in time), from the passes
+    e1 and e2 (the counters of PMC_PASSES p1 and p2) over `python3 bench.py
+    EPH_BENCH_ARGS`, which runs the map alone as ephemeris_chunk."""
+    import collections
     import csv
-    eph = "ephemeris_chunk<4>"
-    g = lambda p, c: tot[(p, eph, c)]
-
-    def trace(path):
-        t, k, n = 0.0, 0, 0
-        for r in csv.DictReader(open(path)):
+    if not os.path.exists(os.path.join(pmc_dir, "e1", "run_counter_collection.csv")):
+        return
+    steps = int(EPH_BENCH_ARGS.split()[-1]) + 1024      # with the warm-up table
+    tot, n, t = collections.defaultdict(float), 0, 0.0
+    for p in ("e1", "e2"):
+        for r in csv.DictReader(open(os.path.join(pmc_dir, p, "run_counter_collection.csv"))):
             if "ephemeris_chunk" in r["Kernel_Name"]:
-                t += (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9
-                k += 1
-        return t, k
-
-    beside, nb = trace(os.path.join(pmc_dir, "p2", "run_kernel_trace.csv"))
-    alone_csv = os.path.join(pmc_dir, "alone", "run_kernel_trace.csv")
-    alone_steps = 100_000
-    alone, na = trace(alone_csv) if os.path.exists(alone_csv) else (None, 0)
-    per = lambda p, c: g(p, c) / steps
-    flops = 64 * per("p1", "SQ_INSTS_VALU_FLOPS_FP64")
+                tot[(p, r["Counter_Name"])] += float(r["Counter_Value"])
+    for r in csv.DictReader(open(os.path.join(pmc_dir, "e2", "run_kernel_trace.csv"))):
+        if "ephemeris_chunk" in r["Kernel_Name"]:
+            t += (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-9
+            n += 1
+    per = lambda p, c: tot[(p, c)] / steps
     out = [f"# ephemeris_chunk<4> counters -- the planet map of giants_100k (4 planets), {steps:,} steps "
-           f"({cnt[('p1', eph, 'SQ_WAVES')]} launches, one wavefront each)", "",
-           "From the same four counter passes as `particle_queue_giants_100k_counters.md` (commands "
-           "there), which run the planet map beside the particle kernel; its time alone from "
-           "`cd /tmp && export TMPDIR=/tmp; rocprofv3 --kernel-trace -f csv -d <out>/alone -o run -- "
-           f"python3 <repo>/bench.py --ephemeris-only --nsteps {alone_steps}`; then "
-           "`python3 bench.py --summarize-counters <out>`.", "",
-           f"Kernel sources of the counted runs: `bench.kernel_source_hash()` = `{src}`.", "",
-           "| counter | sum | per step |", "|---|---|---|"]
-    for (p, lab, c), v in sorted(tot.items()):
-        if lab == eph:
-            out.append(f"| {c} | {v:.6g} | {v / steps:.1f} |")
+           f"({n} launches, one wavefront each)", "",
+           "Commands (`cd /tmp && export TMPDIR=/tmp` first), then `python3 bench.py "
+           "--summarize-counters <out>`:", ""]
+    for e, p in (("e1", "p1"), ("e2", "p2")):
+        out.append(f"    timeout -s KILL 90 rocprofv3 --pmc {PMC_PASSES[p]} --kernel-trace -f csv -d "
+                   f"<out>/{e} -o run -- python3 <repo>/bench.py {EPH_BENCH_ARGS} > <out>/{e}.log")
+    out += ["", f"Kernel sources of the counted runs: `bench.kernel_source_hash()` = `{src}`.", "",
+            "| counter | sum | per step |", "|---|---|---|"]
+    for (p, c), v in sorted(tot.items()):
+        out.append(f"| {c} | {v:.6g} | {v / steps:.1f} |")
     out += ["", "Derived, per step of the map (one wavefront; SQ cycle counters in units of 4 cycles):", "",
-            f"* VALU instructions {per('p1', 'SQ_INSTS_VALU'):.0f}, of them FP64 FMA "
-            f"{per('p1', 'SQ_INSTS_VALU_FMA_F64'):.0f}, mul {per('p1', 'SQ_INSTS_VALU_MUL_F64'):.0f}, "
-            f"add {per('p1', 'SQ_INSTS_VALU_ADD_F64'):.0f}, transcendental "
-            f"{per('p1', 'SQ_INSTS_VALU_TRANS_F64'):.0f}; SALU {per('p2', 'SQ_INSTS_SALU'):.0f}, SMEM "
-            f"{per('p2', 'SQ_INSTS_SMEM'):.0f}; executed FP64 flops (all 64 lanes) {flops:.0f}.",
-            f"* Wave cycles {4 * per('p2', 'SQ_WAVE_CYCLES'):.0f}: VALU issuing "
-            f"{4 * per('p2', 'SQ_ACTIVE_INST_VALU'):.0f}, any instruction issuing "
-            f"{4 * per('p2', 'SQ_ACTIVE_INST_ANY'):.0f}, waiting on a dependency or memory "
-            f"{4 * per('p2', 'SQ_WAIT_ANY'):.0f}, waiting to issue "
-            f"{4 * per('p2', 'SQ_WAIT_INST_ANY'):.0f}.",
-            f"* Kernel-trace time beside the particle kernel (pass 2): {beside * 1e3:.2f} ms for "
-            f"{steps:,} steps in {nb} launches = {beside / steps * 1e6:.3f} us per step."]
-    if alone is not None:
-        out.append(f"* Alone (no particle kernel): {alone * 1e3:.2f} ms for {alone_steps:,} steps in "
-                   f"{na} launches = {alone / alone_steps * 1e6:.3f} us per step.")
+            f"* VALU instructions {per('e1', 'SQ_INSTS_VALU'):.0f} (matrix ones included), of them FP64 FMA "
+            f"{per('e1', 'SQ_INSTS_VALU_FMA_F64'):.0f}, mul {per('e1', 'SQ_INSTS_VALU_MUL_F64'):.0f}, "
+            f"add {per('e1', 'SQ_INSTS_VALU_ADD_F64'):.0f}, transcendental "
+            f"{per('e1', 'SQ_INSTS_VALU_TRANS_F64'):.0f}; SALU {per('e2', 'SQ_INSTS_SALU'):.0f}.",
+            f"* Wave cycles {4 * per('e2', 'SQ_WAVE_CYCLES'):.0f}: VALU issuing "
+            f"{4 * per('e2', 'SQ_ACTIVE_INST_VALU'):.0f}, any instruction issuing "
+            f"{4 * per('e2', 'SQ_ACTIVE_INST_ANY'):.0f}, waiting on a dependency or memory "
+            f"{4 * per('e2', 'SQ_WAIT_ANY'):.0f}, waiting to issue "
+            f"{4 * per('e2', 'SQ_WAIT_INST_ANY'):.0f}.",
+            f"* Kernel-trace time of the counted run: {t * 1e3:.2f} ms = {t / steps * 1e6:.3f} us per step."]
     path = os.path.join(ROOT, "profiles", "ephemeris_chunk_giants_100k_counters.md")
     open(path, "w").write("\n".join(out) + "\n")
-    print("\n".join(out[-4:]))
+    print("\n".join(out[-3:]))
 
 
 # rocprofv3 kernel-trace runs summarized by --summarize-traces DIR: subdirectory
@@ -329,7 +320,7 @@ TRACE_RUNS = {
            "Pipeline timeline -- giants_100k, 100,000 particles x 1,000,000 steps (one benchmark run)",
            "--steps 1 --warmup 0 --no-cpu --no-adjoint --no-batched --no-resonant --no-handoff"),
     "k100k": ("particle_queue_giants_100k_kernel_trace.md",
-              "particle_queue / ephemeris_chunk -- giants_100k, 100,000 particles x 100,000 steps",
+              "particle_queue -- giants_100k, 100,000 particles x 100,000 steps",
               "--nsteps 100000 --steps 1 --warmup 0 --no-cpu --no-adjoint --no-batched --no-resonant "
               "--no-handoff"),
     "ad": ("ad_kernels_adjoint_16k_kernel_trace.md",
@@ -342,7 +333,7 @@ TRACE_RUNS = {
                 "--nsteps 1000 --n 1024 --steps 1 --warmup 0 --no-cpu --no-adjoint --no-resonant "
                 "--no-handoff"),
     "res": ("particle_queue_resonant_200k_kernel_trace.md",
-            "particle_queue / ephemeris_chunk -- resonant_200k, 200,000 particles x 1,000,000 steps",
+            "particle_queue -- resonant_200k, 200,000 particles x 1,000,000 steps",
             "--nsteps 1000 --n 1024 --steps 1 --warmup 0 --no-cpu --no-adjoint --no-batched "
             "--no-handoff"),
     "ho": ("encounter_run_giants_100k_handoff_kernel_trace.md",
@@ -394,7 +385,7 @@ def summarize_traces(tdir: str) -> None:
             st[3] = max(st[3], d)
         total = sum(v[1] for v in stats.values())
         out = [f"# {title}", "",
-               "Command (from the repository root on the GPU box, `cd /tmp && export TMPDIR=/tmp` "
+               "Command (from the repository root, `cd /tmp && export TMPDIR=/tmp` "
                "first), then `python3 bench.py --summarize-traces <out>` for this summary:", "",
                f"    rocprofv3 --kernel-trace -f csv -d <out>/{key} -o run -- python3 <repo>/bench.py "
                f"{args} > <out>/{key}.log", "",
@@ -413,7 +404,6 @@ def summarize_traces(tdir: str) -> None:
 def _trace_details(key, rows, line):
     """Figures of one trace beyond the per-kernel table."""
     pq = [(t0, t1) for k, t0, t1 in rows if "particle_queue" in k]
-    eph = [(t0, t1) for k, t0, t1 in rows if "ephemeris_chunk" in k]
     out = []
     if key in ("tl", "k100k", "res") and pq:
         kern = line.get("kernel", {})
@@ -429,46 +419,39 @@ def _trace_details(key, rows, line):
                 f"{kern.get('launches')} launches, HIP-event average {kern.get('avg_launch_ms', 0):.3f} ms "
                 f"per launch against rocprofv3's {avg:.3f} ms.", ""]
         if key == "tl":
-            span = (max(t1 for _, t1 in pq + eph) - min(t0 for t0, _ in pq + eph)) * 1e-6
+            span = (max(t1 for _, t1 in pq) - min(t0 for t0, _ in pq)) * 1e-6
             bp = sum(t1 - t0 for t0, t1 in pq) * 1e-6
-            be = sum(t1 - t0 for t0, t1 in eph) * 1e-6
             gaps = sum(max(0, pq[i + 1][0] - pq[i][1]) for i in range(len(pq) - 1)) * 1e-6
             out += [f"Span of the run {span:.1f} ms; particle kernels busy {bp:.1f} ms "
-                    f"({100 * bp / span:.0f}%), planet map busy {be:.1f} ms ({100 * be / span:.0f}%); "
-                    f"gaps between particle launches {gaps:.1f} ms in total.", "",
+                    f"({100 * bp / span:.0f}%), the planet map inside them "
+                    f"{kern.get('ephemeris_stream_ms', 0):.1f} ms; gaps between particle launches "
+                    f"{gaps:.1f} ms in total.", "",
                     "Average duration per tenth of the run (launch 0 covers 1,024 steps, the others "
                     "8,192 but the last):", "",
-                    "| launches | particle_queue us | ephemeris_chunk us |", "|---|---|---|"]
-            m = min(len(pq), len(eph))
-            step = max(1, m // 10)
-            for a in range(0, m, step):
-                b = min(m, a + step)
-                out.append(f"| {a}-{b - 1} | {sum(t1 - t0 for t0, t1 in pq[a:b]) / (b - a) / 1e3:.0f} | "
-                           f"{sum(t1 - t0 for t0, t1 in eph[a:b]) / (b - a) / 1e3:.0f} |")
+                    "| launches | particle_queue us |", "|---|---|"]
+            step = max(1, len(pq) // 10)
+            for a in range(0, len(pq), step):
+                b = min(len(pq), a + step)
+                out.append(f"| {a}-{b - 1} | {sum(t1 - t0 for t0, t1 in pq[a:b]) / (b - a) / 1e3:.0f} |")
             out.append("")
     if key == "ad":
         a = line.get("adjoint", {})
-        seg = [(t0, t1) for k, t0, t1 in rows if "ad_segment" in k]
         rev = [(t0, t1) for k, t0, t1 in rows if "ad_reverse" in k]
         out += [f"Adjoint line of the same run: forward {a.get('forward_s', 0) * 1e3:.1f} ms, backward "
                 f"{a.get('backward_s', 0) * 1e3:.1f} ms (x{a.get('backward_over_forward', 0):.2f}); "
                 f"production forward {a.get('production_forward_s', 0) * 1e3:.1f} ms "
                 f"(backward over it x{a.get('backward_over_production_forward', 0):.2f}).", ""]
         if rev:
-            # the timed backward pass: its sweeps and recomputations are the
-            # last nseg of each (a warm-up pass and the forward's segments
-            # come before them)
+            # the timed backward pass: its launches are the last nseg (a warm-up
+            # pass comes before them)
             import re
             m = re.search(r"(\d+) steps, checkpoint every (\d+)", a.get("workload", ""))
             nseg = -(-int(m.group(1)) // int(m.group(2))) if m else len(rev)
-            rev, rec = rev[-nseg:], seg[-nseg:]
-            ov = sum(max(0, min(t1, u1) - max(t0, u0)) for t0, t1 in rec for u0, u1 in rev)
-            span = (max(t1 for _, t1 in rev + rec) - min(t0 for t0, _ in rev + rec)) * 1e-6
-            out += [f"Timed backward pass ({nseg} segments): sweeps (ad_reverse, caller's stream) "
-                    f"{sum(t1 - t0 for t0, t1 in rev) * 1e-6:.1f} ms busy, {sum(t1 - t0 for t0, t1 in rev) * 1e-3 / nseg:.0f} us "
-                    f"each; recomputations (ad_segment, library stream) "
-                    f"{sum(t1 - t0 for t0, t1 in rec) * 1e-6:.1f} ms busy, {ov * 1e-6:.1f} ms of it beside a "
-                    f"sweep; span {span:.1f} ms.", ""]
+            rev = rev[-nseg:]
+            span = (rev[-1][1] - rev[0][0]) * 1e-6
+            out += [f"Timed backward pass ({nseg} segments, each one launch with the next one's "
+                    f"recomputation): {sum(t1 - t0 for t0, t1 in rev) * 1e-6:.1f} ms busy, "
+                    f"{sum(t1 - t0 for t0, t1 in rev) * 1e-3 / nseg:.0f} us each; span {span:.1f} ms.", ""]
     if key == "ho":
         h = line.get("handoff", {})
         enc = [(t0, t1) for k, t0, t1 in rows if "encounter_run" in k]

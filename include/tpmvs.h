@@ -133,7 +133,8 @@ typedef struct {
   int64_t active_particle_steps;  /* particle-steps done while active, last integrate */
   double wall_ms;                 /* last integrate, host wall clock incl. sync   */
   double particle_ms;             /* last integrate, HIP events on the particle stream */
-  double ephemeris_ms;            /* last integrate, HIP events on the ephemeris stream */
+  double ephemeris_ms;            /* last integrate, the planet map (device clock), or the
+                                     interpolation of a history's rows (HIP events)     */
   int64_t chunks;                 /* particle launches in the last integrate      */
   double particle_kernel_ms;      /* last integrate, sum of HIP-event durations of the
                                      particle launches alone (only with time_kernels) */

@@ -251,11 +251,6 @@ hipError_t launch_run_report(const int64_t* dstep, int n, int64_t step_begin, in
                              const int64_t* ticks, const int32_t* qerr, const int32_t* nactive,
                              RunReport* rep, hipStream_t st);
 
-// Steps spent active in [step_begin, step_end) summed over particles (for a
-// backward run the range is taken in absolute order).
-hipError_t launch_active_steps(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
-                               unsigned long long* acc, hipStream_t st);
-
 // ---- many systems in one launch
 // Per-system constants of the batched particle kernel (device array).
 struct SysDev {

@@ -12,9 +12,9 @@
 //    or lane b Jacobi body b.  Wisdom-Holman kick-drift-kick of the planets
 //    (sec. 2.2, planet integration) writing the heliocentric positions and the
 //    indirect term h0 per step.
-//  * compact_*       - stable partition of the working set so removed particles
-//    stop occupying lanes (sec. 2.2, resync interval), by wave ballots, an LDS
-//    scan and ordered block offsets.
+//  * compact_kernel  - stable partition of the working set so removed particles
+//    stop occupying lanes (sec. 2.2, resync interval), by wave ballots and a
+//    look-back over the tiles before.
 //  * finalize        - scatter the active particles back to caller order.
 #include <algorithm>
 
@@ -272,9 +272,10 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
 // launch's workgroups start in, so every wait for rows ends.  As launches of
 // its own the map had to finish a chunk before the particles could start on
 // it, so a call of one or two chunks took the sum of both: 10,000 steps of
-// 13,313 particles 16.7 ms, now 9.5; 1,000 steps of 16,384 particles on one
-// stream 1.74 ms, now 1.01; 10,000 steps of 200,000 particles 29.2 ms, now 21.8.
-
+// 13,313 particles 16.7 ms, then 9.5; 1,000 steps of 16,384 particles on one
+// stream 1.74 ms, then 1.01; 10,000 steps of 200,000 particles 29.2 ms, then 21.8
+// (5.3, 0.57 and 15.0 with the shorter steps since).
+//
 // No part of the item loop runs on a subset of the lanes: the grab, the wait
 // and the publish are executed by the whole wavefront (lane 0 alone adds 1 to
 // the counter), so the readfirstlane that makes their results wave-uniform
@@ -1440,20 +1441,6 @@ TPM_DEV void add_active_steps(const int64_t* __restrict__ dstep, int n, int64_t 
     atomicAdd(acc, (unsigned long long)(part[0] + part[1] + part[2] + part[3]));
 }
 static int active_grid(int n) { return std::max(1, std::min((n + 1023) / 1024, 128)); }
-
-__global__ void __launch_bounds__(256)
-active_steps_kernel(const int64_t* __restrict__ dstep, int n, int64_t step_begin, int64_t step_end,
-                    unsigned long long* acc) {
-  add_active_steps(dstep, n, step_begin, step_end, acc);
-}
-
-hipError_t launch_active_steps(const int64_t* dstep, int n, int64_t step_begin, int64_t step_end,
-                               unsigned long long* acc, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(active_steps_kernel, dim3(active_grid(n)), dim3(256), 0, st, dstep, n,
-                     step_begin, step_end, acc);
-  return hipGetLastError();
-}
 
 // The last workgroup to finish writes the report (its loads of the sum come
 // after every workgroup's addition: each adds, then counts itself done).
