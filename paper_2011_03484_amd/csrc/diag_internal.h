@@ -34,6 +34,14 @@ struct DiagArgs {
 // planet-table row is `row`.
 hipError_t launch_sample(const SysConst& S, Work w, const int32_t* d_nactive, int n_upper,
                          const double* row, int64_t step, const DiagArgs& D, hipStream_t st);
+// Sample states that a particle launch stored (QueueLaunch::samp) at the
+// nsamp global steps step, step + every, ..., local steps first, first + every, ...
+// of the chunk whose rows are `rows` and whose planet velocities (null without
+// resonances) are vrows, [row][np][3].  No snapshot.
+hipError_t launch_sample_stored(const SysConst& S, Work w, Out out, const int32_t* d_nactive,
+                                int n_upper, const double* samp, int64_t stride, int nsamp,
+                                const double* rows, const double* vrows, int first, int every,
+                                int64_t step, const DiagArgs& D, hipStream_t st);
 // Snapshot entries of every slot from the removal records (before launch_sample).
 hipError_t launch_snapshot_base(Out out, int n, double mu0, const DiagArgs& D, hipStream_t st);
 // Accumulators of n particles to their starting values.

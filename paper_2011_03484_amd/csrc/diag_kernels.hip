@@ -67,6 +67,36 @@ TPM_DEV void osc_elements(double mu, double x, double y, double z, double vx, do
 constexpr double TEN_DEG = M_PI / 18.0;
 constexpr double TWO_PI_D = 2.0 * M_PI;
 
+// One sample of particle k: elements el at global step `step`, whose planet row is
+// `row` and whose reference planet's velocity is vref.
+TPM_DEV void accumulate(const DiagArgs& D, int k, int64_t step, const double* el, const double* row,
+                        const double* vref) {
+  if (el[1] > D.emax[k]) {
+    D.emax[k] = el[1];
+    D.estep[k] = step;
+  }
+  if (D.nres == 0) return;
+  // the reference planet's mean longitude, from its position (table row) and
+  // velocity (planet map) about mu0 + mu_ref
+  double pel[6];
+  const double* pr = row + 3 * D.ref;
+  osc_elements(D.mu_ref, pr[0], pr[1], pr[2], vref[0], vref[1], vref[2], pel);
+  const double lam_ref = pel[3] + pel[4] + pel[5];
+  const double varpi = el[3] + el[4];
+  const double lam = varpi + el[5];
+  for (int q = 0; q < D.nres; ++q) {
+    const double phi = D.p[q] * lam - D.q[q] * lam_ref - (D.p[q] - D.q[q]) * varpi;
+    const double w0 = remainder(phi, TWO_PI_D);
+    const double w180 = remainder(phi - M_PI, TWO_PI_D);
+    int32_t f = D.flags[D.nres * k + q];
+    if (__builtin_fabs(w0) < TEN_DEG) f |= 1;
+    if (__builtin_fabs(w180) < TEN_DEG) f |= 2;
+    D.flags[D.nres * k + q] = f;
+    D.lo[D.nres * k + q] = fmin(D.lo[D.nres * k + q], w180);
+    D.hi[D.nres * k + q] = fmax(D.hi[D.nres * k + q], w180);
+  }
+}
+
 template <int NP>
 __global__ void __launch_bounds__(256)
 sample_kernel(Work w, const int32_t* __restrict__ d_nactive, const double* __restrict__ row,
@@ -91,30 +121,45 @@ sample_kernel(Work w, const int32_t* __restrict__ d_nactive, const double* __res
     for (int c = 0; c < 6; ++c) D.snap_el[6 * k + c] = el[c];
   }
   if (!D.emax || hit >= 0 || escaped) return;
-  if (el[1] > D.emax[k]) {
-    D.emax[k] = el[1];
-    D.estep[k] = step;
+  accumulate(D, k, step, el, row, D.vref);
+}
+
+// The same from states that a particle launch stored on its way through the
+// chunk, all its samples in one launch: a boundary with a launch of its own on
+// either side costs about 45 us.  A removed particle is sampled up to its
+// removal: a refused drift's record holds the step it starts from, which has
+// been sampled, the others the boundary that removes it, which is not.
+__global__ void __launch_bounds__(256)
+sample_stored_kernel(Work w, Out out, const int32_t* __restrict__ d_nactive,
+                     const double* __restrict__ samp, int64_t stride, int nsamp,
+                     const double* __restrict__ rows, const double* __restrict__ vrows, int np,
+                     int first, int every, int64_t step, DiagArgs D) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= *d_nactive) return;
+  const int32_t st = w.status[i];
+  const int k = w.slot[i];
+  int64_t last = INT64_MAX;
+  if (st != ST_ACTIVE) last = out.step[k] - (st == ST_KEPLER ? 0 : 1);
+  for (int j = 0; j < nsamp; ++j) {
+    const int64_t g = step + (int64_t)j * every;
+    if (g > last) return;
+    const double* p = samp + 6 * stride * j + i;
+    double el[6];
+    osc_elements(D.mu0, p[0], p[stride], p[2 * stride], p[3 * stride], p[4 * stride],
+                 p[5 * stride], el);
+    const int64_t r = first + (int64_t)j * every;
+    accumulate(D, k, g, el, rows + r * (3 * np + 3), vrows ? vrows + (3 * r * np + 3 * D.ref) : nullptr);
   }
-  if (D.nres == 0) return;
-  // the reference planet's mean longitude, from its position (table row) and
-  // velocity (planet map) about mu0 + mu_ref
-  double pel[6];
-  const double* pr = row + 3 * D.ref;
-  osc_elements(D.mu_ref, pr[0], pr[1], pr[2], D.vref[0], D.vref[1], D.vref[2], pel);
-  const double lam_ref = pel[3] + pel[4] + pel[5];
-  const double varpi = el[3] + el[4];
-  const double lam = varpi + el[5];
-  for (int q = 0; q < D.nres; ++q) {
-    const double phi = D.p[q] * lam - D.q[q] * lam_ref - (D.p[q] - D.q[q]) * varpi;
-    const double w0 = remainder(phi, TWO_PI_D);
-    const double w180 = remainder(phi - M_PI, TWO_PI_D);
-    int32_t f = D.flags[D.nres * k + q];
-    if (__builtin_fabs(w0) < TEN_DEG) f |= 1;
-    if (__builtin_fabs(w180) < TEN_DEG) f |= 2;
-    D.flags[D.nres * k + q] = f;
-    D.lo[D.nres * k + q] = fmin(D.lo[D.nres * k + q], w180);
-    D.hi[D.nres * k + q] = fmax(D.hi[D.nres * k + q], w180);
-  }
+}
+
+hipError_t launch_sample_stored(const SysConst& S, Work w, Out out, const int32_t* d_nactive,
+                                int n_upper, const double* samp, int64_t stride, int nsamp,
+                                const double* rows, const double* vrows, int first, int every,
+                                int64_t step, const DiagArgs& D, hipStream_t st) {
+  if (n_upper <= 0 || nsamp <= 0) return hipSuccess;
+  hipLaunchKernelGGL(sample_stored_kernel, dim3((n_upper + 255) / 256), dim3(256), 0, st, w, out,
+                     d_nactive, samp, stride, nsamp, rows, vrows, S.np, first, every, step, D);
+  return hipGetLastError();
 }
 
 template <int NP>

@@ -148,6 +148,12 @@ struct QueueLaunch {
   int block;                   // threads per workgroup (multiple of 64)
   int32_t* error;              // device flag set on an over-long wait
   const RowStream* stream = nullptr;   // the launch writes its own planet rows
+  // States at sampled steps (diagnostics): those of the active particles at the
+  // chunk's local steps samp_first, samp_first + samp_every, ... go to
+  // samp[k][6][samp_stride] by working-set entry, k the sample.  samp null: none.
+  double* samp = nullptr;
+  int64_t samp_stride = 0;
+  int samp_first = 0, samp_every = 0;
   const EphConst* eph = nullptr;       // with the planet map's constants
 
   // One wavefront more for the planet map.

@@ -17,6 +17,7 @@
 //    look-back over the tiles before.
 //  * finalize        - scatter the active particles back to caller order.
 #include <algorithm>
+#include <climits>
 
 #include "internal.h"
 #include "particle.hpp"
@@ -34,6 +35,12 @@ struct ChunkArgs {
   int kiters, nsteps;
   int64_t step0;
   int handoff;   // within rcrit: hand off to the encounter integrator, not removal
+  // sampled states (see QueueLaunch); every 0: none
+  struct Samples {
+    int first, every;
+    int64_t stride;
+    double* at;
+  } samp;
 };
 
 // Work queue of one launch (see particle_queue).
@@ -219,12 +226,24 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
     vx = nvx; vy = nvy; vz = nvz;
     ax = bx; ay = by; az = bz;
   };
+  // the item's first sampled step (after s_begin: a state at s_begin is the
+  // item's before)
+  int next = INT_MAX;
+  using Samples = typename ChunkArgs<NP>::Samples;
+  constexpr size_t SAMPLES = offsetof(QueueKernelArgs<NP>, A) + offsetof(ChunkArgs<NP>, samp);
+  if (KA) {
+    const Samples q = karg_field<Samples>(ka, SAMPLES);
+    if (q.every > 0) {
+      next = q.first;
+      if (next <= s_begin) next += ((s_begin - next) / q.every + 1) * q.every;
+    }
+  }
   for (int s0 = s_begin;;) {
     if (KA && have <= s0) {
       have = wait_rows(ka, s0, A.nsteps);
       if (have <= s0) break;                // the wait gave up (flagged)
     }
-    const int lim = KA ? min(s_end, have) : s_end;
+    const int lim = KA ? min(min(s_end, have), next) : s_end;
     if (AHEAD) {
       // The row that ends step s is fetched during step s - 1, into the one of
       // two alternating VGPR buffers that step s - 1 does not use: with few
@@ -248,6 +267,16 @@ TPM_DEV void advance(Work w, Out out, const double* rows, const ChunkArgs<NP>& A
       }
     }
     s0 = lim;
+    if (KA && s0 == next) {
+      const Samples q = karg_field<Samples>(ka, SAMPLES);
+      if (lane_in(act)) {
+        const int64_t k = q.stride;
+        double* p = q.at + 6 * k * ((s0 - q.first) / q.every) + i;
+        p[0] = x; p[k] = y; p[2 * k] = z;
+        p[3 * k] = vx; p[4 * k] = vy; p[5 * k] = vz;
+      }
+      next += q.every;
+    }
     if (!KA || s0 >= s_end || act == 0) break;
   }
   if (lane_in(act)) {
@@ -358,6 +387,7 @@ TPM_DEV void batch_item(const SysDev& S, Work w, Out out, const double* __restri
   A.nsteps = Q.nsteps;
   A.step0 = Q.step0;
   A.handoff = 0;
+  A.samp = {};
   const double* rows = ring + S.ring_off + (int64_t)Q.slot * Q.slot_rows * (3 * NP + 3);
   const int i = T.first + lane;
   const bool valid = lane < T.count;
@@ -561,6 +591,7 @@ static hipError_t launch_np(const SysConst& S, Work w, const int32_t* d_nactive,
   A.nsteps = nsteps;
   A.step0 = step0;
   A.handoff = S.handoff;
+  A.samp = {QL.samp_first, QL.samp ? QL.samp_every : 0, QL.samp_stride, QL.samp};
   QueueArgs Q;
   Q.ctr = QL.ctr;
   Q.base = QL.base;
