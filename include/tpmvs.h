@@ -70,7 +70,7 @@ typedef struct {
                              1,024 steps                                                     */
   int32_t resync_chunks;  /* chunks between compactions ("resync interval", sec. 2.2); 0 = 1;
                              with diagnostics on, that many chunks' steps, whose chunks
-                             samples cut short */
+                             samples may cut short */
   int32_t block_threads;  /* particle-kernel workgroup size (64..256, multiple of 64); 0 = 64 */
   int32_t sub_chunks;     /* work items per tile in a full chunk (dynamic load balance); a
                              shorter chunk gets proportionally fewer items of the same
