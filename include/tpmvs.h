@@ -314,8 +314,10 @@ int tpm_set_planet_history(tpm_sim* sim, int64_t nrec, const double* t, const do
  * Device-pointer calls for autograd frameworks: every array is caller-owned
  * device memory, [n][3] row-major float64 unless stated; work is enqueued on
  * the caller's HIP stream `stream` (NULL = null stream) without synchronising,
- * so outputs are ready when that stream reaches them.  The planets are not
- * differentiated.  A removed particle keeps the state of its removal step, so
+ * so outputs are ready when that stream reaches them.  The calls of one sim
+ * share its context and run in the order they are made, also on different
+ * streams (of a stream under capture, the caller keeps them apart); tpm_integrate
+ * may move the planets in between.  The planets are not differentiated.  A removed particle keeps the state of its removal step, so
  * its derivative is that of the map up to that step.
  *
  * tpm_ad_forward: integrates n particles from (d_r0, d_v0) for nsteps steps of

@@ -294,6 +294,11 @@ struct tpm_sim {
     // planets' state and the planet event), which an integrate call waits for
     hipEvent_t ev_tab[2]{}, ev_end = nullptr;
     bool reading = false;
+    // recorded behind the last derivative call, on its stream: the next one, on
+    // whichever stream, and the planet map of the next forward come after it
+    // (they share the table, checkpoints, tapes and work arrays)
+    hipEvent_t ev_use = nullptr;
+    bool used = false;
   } ad;
   std::vector<hipEvent_t> kev;           // per-launch timing events (time_kernels)
   // sampled diagnostics and snapshots (tpm_set_diagnostics)
@@ -353,6 +358,7 @@ struct tpm_sim {
       if (ad.ev_tab[k]) (void)hipEventDestroy(ad.ev_tab[k]);
     }
     if (ad.ev_end) (void)hipEventDestroy(ad.ev_end);
+    if (ad.ev_use) (void)hipEventDestroy(ad.ev_use);
     ad = AD{};
   }
 
@@ -1873,6 +1879,34 @@ int grow(T*& p, size_t& cap, size_t want) {
   return TPM_OK;
 }
 
+// A derivative call on stream st starts behind the last one (ad_begin) and is
+// what the next one waits for (ad_end).  A stream under capture is left alone:
+// it may not wait for work outside the capture, nor may others wait for an
+// event of it, and the order of a graph's replays is the caller's.
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return c != hipStreamCaptureStatusNone;
+}
+
+int ad_begin(tpm_sim* s, hipStream_t st) {
+  auto& A = s->ad;
+  if (A.used && !capturing(st)) TPM_HIP(hipStreamWaitEvent(st, A.ev_use, 0));
+  return TPM_OK;
+}
+
+int ad_end(tpm_sim* s, hipStream_t st) {
+  auto& A = s->ad;
+  if (capturing(st)) return TPM_OK;
+  if (!A.ev_use) TPM_HIP(hipEventCreateWithFlags(&A.ev_use, hipEventDisableTiming));
+  TPM_HIP(hipEventRecord(A.ev_use, st));
+  A.used = true;
+  return TPM_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1926,7 +1960,10 @@ int tpm_ad_forward(tpm_sim* s, int64_t n, const double* d_r0, const double* d_v0
   // holds (an earlier integrate); the caller's stream runs each segment once
   // the piece holding its last row is written, so the planet map and the
   // particle segments overlap.  A later tpm_integrate waits for these pieces
-  // (ev_end).
+  // (ev_end); the pieces wait for the last derivative call, which may still
+  // read the table, on whichever stream it runs.
+  if (int rc = ad_begin(s, st)) return rc;
+  if (A.used) TPM_HIP(hipStreamWaitEvent(s->sE, A.ev_use, 0));
   const SysConst S = s->sys();
   const EphConst E = s->eph();
   const size_t pb = sizeof(double) * 3 * std::max(s->np, 1);
@@ -1966,6 +2003,7 @@ int tpm_ad_forward(tpm_sim* s, int64_t n, const double* d_r0, const double* d_v0
   TPM_HIP(launch_soa_to_aos(A.ckpts + (size_t)nseg * 6 * n, d_rT, d_vT, n, st));
   if (d_step) TPM_HIP(hipMemcpyAsync(d_step, A.dstep, sizeof(int64_t) * n, hipMemcpyDeviceToDevice, st));
   if (d_reason) TPM_HIP(hipMemcpyAsync(d_reason, A.reason, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, st));
+  if (int rc = ad_end(s, st)) return rc;
   A.valid = true;
   return TPM_OK;
 }
@@ -1994,6 +2032,7 @@ int tpm_ad_backward(tpm_sim* s, const double* d_gRT, const double* d_gVT, double
   auto first = [&](int k) { return k * A.ckpt; };
   auto last = [&](int k) { return (int)std::min<int64_t>(A.nsteps, (int64_t)first(k) + A.ckpt); };
   auto from = [&](int k) { return A.ckpts + (size_t)k * 6 * n; };
+  if (int rc = ad_begin(s, st)) return rc;
   TPM_HIP(launch_aos_to_soa(d_gRT, d_gVT, lam, n, st));
   if (const int k = A.nseg - 1; k >= 0)
     TPM_HIP(launch_ad_segment(S, A.dt, n, first(k), last(k), A.table, from(k), nullptr, tape[k % 2],
@@ -2004,7 +2043,7 @@ int tpm_ad_backward(tpm_sim* s, const double* d_gRT, const double* d_gVT, double
   if (A.nseg > 0)
     TPM_HIP(launch_ad_reverse(S, A.dt, n, first(0), last(0), A.table, tape[0], lam, A.dstep, st));
   TPM_HIP(launch_soa_to_aos(lam, d_gR0, d_gV0, n, st));
-  return TPM_OK;
+  return ad_end(s, st);
 }
 
 int tpm_ad_tangent(tpm_sim* s, const double* d_dR0, const double* d_dV0, double* d_dRT,
@@ -2019,6 +2058,7 @@ int tpm_ad_tangent(tpm_sim* s, const double* d_dR0, const double* d_dV0, double*
   const SysConst S = s->sys();
   double* state = A.work;
   double* tang = A.work + 6 * n;
+  if (int rc = ad_begin(s, st)) return rc;
   TPM_HIP(hipMemcpyAsync(state, A.ckpts, sizeof(double) * 6 * n, hipMemcpyDeviceToDevice, st));
   TPM_HIP(launch_aos_to_soa(d_dR0, d_dV0, tang, n, st));
   for (int k = 0; k < A.nseg; ++k) {
@@ -2027,7 +2067,7 @@ int tpm_ad_tangent(tpm_sim* s, const double* d_dR0, const double* d_dV0, double*
     TPM_HIP(launch_ad_tangent(S, A.dt, n, s0, s1, A.table, state, tang, A.treason, k == 0, st));
   }
   TPM_HIP(launch_soa_to_aos(tang, d_dRT, d_dVT, n, st));
-  return TPM_OK;
+  return ad_end(s, st);
 }
 
 }  // extern "C"
