@@ -1573,7 +1573,9 @@ compact_kernel(Work src, Work dst, int32_t* d_nactive, int32_t* scratch,
   uint32_t* ticket = reinterpret_cast<uint32_t*>(scratch);
   uint32_t* done = ticket + 1;
   uint64_t* word = reinterpret_cast<uint64_t*>(scratch + 2);
-  __shared__ int s_tile, s_n, s_off;
+  // (s_last is a word of its own: blocks without a tile have no barrier between
+  // their wavefronts' reads of s_tile and its write)
+  __shared__ int s_tile, s_n, s_off, s_last;
   __shared__ int wcount[CE][CB / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   if (threadIdx.x == 0) {
@@ -1674,10 +1676,10 @@ compact_kernel(Work src, Work dst, int32_t* d_nactive, int32_t* scratch,
   }
   // the last block: every look-back is over
   if (threadIdx.x == 0)
-    s_tile = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
+    s_last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1 ==
              gridDim.x;
   __syncthreads();
-  if (!s_tile) return;
+  if (!s_last) return;
   for (unsigned k = threadIdx.x; k < gridDim.x; k += CB) word[k] = 0;
   if (threadIdx.x < 2) scratch[threadIdx.x] = 0;
 }
