@@ -428,6 +428,10 @@ int tpm_debug_drift(double mu, int64_t n, const double* rv_in, double* rv_out, i
  * (rv_out then holds the input state).  Host arrays. */
 int tpm_debug_drift_universal(double mu, int64_t n, const double* rv_in, double* rv_out,
                               int32_t* ok, double dt, int32_t mode);
+/* Raises sim's work-queue error flag, as a device wait beyond its limit does: the
+ * next tpm_integrate runs to its end and returns TPM_EDEVICE; the flag stays
+ * until new particles are set. */
+int tpm_debug_queue_error(tpm_sim* sim);
 
 #ifdef __cplusplus
 }

@@ -88,6 +88,7 @@ SIGNATURES = {
     "tpm_debug_rsqrt": (C.c_int, [C.c_int64, _P, _P]),
     "tpm_debug_drift": (C.c_int, [C.c_double, C.c_int64, _P, _P, _P, C.c_double, C.c_int32,
                                   C.c_double]),
+    "tpm_debug_queue_error": (C.c_int, [_P]),
     "tpm_debug_drift_universal": (C.c_int, [C.c_double, C.c_int64, _P, _P, _P, C.c_double,
                                             C.c_int32]),
     "tpm_ad_forward": (C.c_int, [_P, C.c_int64, _P, _P, C.c_int64, C.c_double, C.c_int32, _P, _P,

@@ -271,6 +271,7 @@ struct tpm_sim {
   int32_t* d_qerr = nullptr;             // work-queue error flag
   uint32_t* d_done = nullptr;            // workgroups of the closing kernel that are done
   unsigned long long acc_seen = 0;       // *d_acc at the end of the last call
+  bool open = false;                     // an integrate call began and did not come to its end
   unsigned long long q_base = 0;         // host copy of the item counter
   uint32_t q_epoch = 0;                  // host copy of the tiles' progress
   tpm_stats stats{};
@@ -522,6 +523,30 @@ int ensure_handoff(tpm_sim* s, int64_t rows, int64_t slots) {
     TPM_HIP(hipMalloc(&s->d_snap, sizeof(int32_t) * slots));
     s->snap_slots = slots;
   }
+  return TPM_OK;
+}
+
+// After an integrate call that failed under way: waits for what it enqueued and
+// takes the host's copies of the device's counts (planet rows published, the
+// map's time, active steps, queue items, active entries) from the device; the
+// counts read back on the way are dropped, and the encounter list is empty.
+int resume(tpm_sim* s) {
+  const hipStream_t sH = device_streams(s->opt.device).sH;
+  for (hipStream_t st : {s->sE, s->sP, sH})
+    if (st) TPM_HIP(hipStreamSynchronize(st));
+  char h[512];
+  TPM_HIP(hipMemcpy(h, s->d_base, sizeof(h), hipMemcpyDeviceToHost));
+  auto get = [&](auto& to, const void* at) { std::memcpy(&to, h + ((const char*)at - s->d_base), sizeof(to)); };
+  get(s->rows_done, s->d_stream);
+  get(s->map_ticks, s->d_stream + 1);
+  get(s->acc_seen, s->d_acc);
+  get(s->q_base, s->d_qctr);
+  get(s->n_active, s->d_nactive);
+  s->cnt_seen = s->cnt_issued;
+  const uint32_t zero = 0;
+  TPM_HIP(hipMemcpy(s->d_done, &zero, sizeof(zero), hipMemcpyHostToDevice));
+  if (s->enc.count) TPM_HIP(hipMemcpy(s->enc.count, &zero, sizeof(zero), hipMemcpyHostToDevice));
+  s->open = false;
   return TPM_OK;
 }
 
@@ -1111,6 +1136,10 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   }
   s->stats.chunks = 0;
   s->stats.compactions = 0;
+  if (s->open) {                          // the call before failed
+    if (int rc = resume(s)) return rc;
+  }
+  s->open = true;
   if (s->ad.reading) {                    // a forward may still read the planets
     TPM_HIP(hipStreamWaitEvent(s->sP, s->ad.ev_end, 0));
     s->ad.reading = false;
@@ -1410,6 +1439,7 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   }
   const unsigned long long acc = rep.acc - s->acc_seen;
   s->acc_seen = rep.acc;
+  s->open = false;
   auto w1 = std::chrono::steady_clock::now();
   double kms = 0.0;
   if (timed)
@@ -1863,6 +1893,16 @@ int tpm_debug_drift_universal(double mu, int64_t n, const double* rv_in, double*
                               int32_t* ok, double dt, int32_t mode) {
   if (mode != 1 && mode != 2) return fail(TPM_EINVAL, "mode must be 1 or 2");
   return debug_drift(mu, n, rv_in, rv_out, ok, dt, 5, 0.0, mode);
+}
+
+int tpm_debug_queue_error(tpm_sim* s) {
+  if (!s) return fail(TPM_EINVAL, "sim is NULL");
+  TPM_HIP(hipSetDevice(s->opt.device));
+  std::lock_guard<std::mutex> dev_lock(device_streams(s->opt.device).lock);
+  TPM_HIP(hipStreamSynchronize(s->sP));
+  const int32_t one = 1;
+  TPM_HIP(hipMemcpy(s->d_qerr, &one, sizeof(one), hipMemcpyHostToDevice));
+  return TPM_OK;
 }
 
 }  // extern "C"
