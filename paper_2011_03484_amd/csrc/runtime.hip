@@ -2571,14 +2571,18 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
       tune_cache()[key] = choice;
     }
   }
-  // A run of fewer than four chunks is cut into four (of at least 128 steps): the
-  // planet maps of a chunk go on beside the particles of the one before, so only
-  // the first chunk's stand alone.  800 steps of 96 systems of 1 to 8 planets and
-  // 90,541 particles 2.18 ms in chunks of 512 steps, 1.85 in chunks of 200.  Items and
-  // compactions keep their steps.
+  // A run of fewer than four tuned chunks is cut into four: the planet maps of a
+  // chunk go on beside the particles of the one before, so only the first chunk's
+  // stand alone.  800 steps of 96 systems of 1 to 8 planets and 90,541 particles
+  // 2.08 ms in chunks of 512 steps, 1.77 in chunks of 200.  Not a run that fits the
+  // shortest candidate, whose ring has one slot (cut, its chunks would go one
+  // after the other: 512 steps of 200 systems 2.22 ms for 1.84): with four slots the
+  // run gains there too (1.79), but capturing and instantiating the added
+  // launches costs the call more (4.6 ms for 4.4; 300 steps of 96 systems 2.4 for
+  // 2.15, where 600 steps take 2.9 for 3.15).  Items and compactions keep their steps.
   TuneChoice shape = choice;
-  if (o.chunk_steps == 0 && nsteps < 4 * (int64_t)choice.chunk) {
-    const int len = (int)std::min<int64_t>(choice.chunk, std::max<int64_t>(128, (nsteps + 3) / 4));
+  if (o.chunk_steps == 0 && nsteps > kChunks[0] && nsteps < 4 * (int64_t)choice.chunk) {
+    const int len = (int)std::min<int64_t>(choice.chunk, (nsteps + 3) / 4);
     shape.chunk = len;
     shape.sub_chunks = std::max(1, (choice.sub_chunks * len + choice.chunk / 2) / choice.chunk);
     shape.resync = (int)((choice.resync * (int64_t)choice.chunk + len - 1) / len);
