@@ -140,10 +140,10 @@ typedef struct {
                                      particle launches alone (only with time_kernels) */
   int64_t compactions;            /* compactions in the last integrate            */
   int64_t count_by_reason[4];     /* over all particles                           */
-  int32_t sub_chunks;             /* work-queue shape used (after autotuning)     */
-  int32_t waves_per_simd;
-  int32_t block_threads;          /* workgroup size, chunk length and compaction  */
-  int32_t chunk_steps;            /* interval used (after autotuning)             */
+  int32_t sub_chunks;             /* work-queue shape (given or chosen by the tuner;   */
+  int32_t waves_per_simd;         /* the launches of a short many-system run are cut   */
+  int32_t block_threads;          /* from it), workgroup size, chunk length and        */
+  int32_t chunk_steps;            /* compaction interval                               */
   int32_t resync_chunks;
   int64_t handoffs;               /* close-encounter hand-offs in the last integrate */
 } tpm_stats;
@@ -357,13 +357,17 @@ int tpm_ad_tangent(tpm_sim* sim, const double* d_dR0, const double* d_dV0, doubl
  * from the initial state, per step, and sets the compaction interval so that
  * one compaction costs under 1% of the chunks it follows; choices are cached
  * per (device, systems, particles, steps, planet-count histogram, fixed
- * options) and never change results.  The planet maps of all systems run as
+ * options) and never change results.  With chunk_steps 0 a run of more than 512
+ * steps but fewer than four chunks of the chosen length is launched in four
+ * shorter ones (counted in stats.chunks, while stats.chunk_steps is the chosen
+ * length): work items and compactions chosen by the tuner then keep about their
+ * steps, those given their numbers per launch and between compactions.  The planet maps of all systems run as
  * one launch per chunk and the particles of all systems as one work queue
  * (tiles of 64 particles of one system, most planets first); every
  * resync_chunks chunks the working set is compacted and the tiles rebuilt on
  * the device.  The whole run is captured into one HIP graph and launched once.
  * stats (may be NULL) receives the graph's run time, the active
- * particle-steps and the chosen shape.  planet_flag (may be NULL) receives per system
+ * particle-steps, the launches and compactions and the chosen shape.  planet_flag (may be NULL) receives per system
  * the first of these events: -1 none, t >= 0 two planets within a mutual
  * Hill radius at step t, -2 a planet orbit found unbound in a drift (before
  * any close pair; it wins a tie with a pair seen at the end of the same step).

@@ -2579,13 +2579,16 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
   // after the other: 512 steps of 200 systems 2.22 ms for 1.84): with four slots the
   // run gains there too (1.79), but capturing and instantiating the added
   // launches costs the call more (4.6 ms for 4.4; 300 steps of 96 systems 2.4 for
-  // 2.15, where 600 steps take 2.9 for 3.15).  Items and compactions keep their steps.
+  // 2.15, where 600 steps take 2.9 for 3.15).  Items and compactions keep their
+  // steps where the tuner chose them, and their numbers where the caller did.
   TuneChoice shape = choice;
   if (o.chunk_steps == 0 && nsteps > kChunks[0] && nsteps < 4 * (int64_t)choice.chunk) {
     const int len = (int)std::min<int64_t>(choice.chunk, (nsteps + 3) / 4);
     shape.chunk = len;
-    shape.sub_chunks = std::max(1, (choice.sub_chunks * len + choice.chunk / 2) / choice.chunk);
-    shape.resync = (int)((choice.resync * (int64_t)choice.chunk + len - 1) / len);
+    if (o.sub_chunks <= 0)
+      shape.sub_chunks = std::max(1, (choice.sub_chunks * len + choice.chunk / 2) / choice.chunk);
+    if (o.resync_chunks == 0)
+      shape.resync = (int)((choice.resync * (int64_t)choice.chunk + len - 1) / len);
   }
   const int K = shape.chunk;
   const int64_t nchunks = (nsteps + K - 1) / K;
@@ -2657,6 +2660,7 @@ extern "C" int tpm_batch_integrate(int32_t nsys, const double* mu0, const int32_
     st.particle_ms = run_ms;
     st.ephemeris_ms = run_ms;
     st.chunks = nchunks;
+    // the chosen shape; a short run's launches are cut from it (nchunks of them)
     st.sub_chunks = choice.sub_chunks;
     st.waves_per_simd = choice.waves_per_simd;
     st.block_threads = choice.block;

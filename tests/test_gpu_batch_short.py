@@ -34,3 +34,15 @@ def test_cut_only_where_chunks_overlap(tpm, T, chunks):
     systems = W.make_batched(nsys=7, nmin=40, nmax=300, seed=62)
     _, st = tpm.batch_integrate(systems, nsteps=T, strict=False)
     assert st["chunks"] == chunks
+
+
+@pytest.mark.parametrize("T", [300, 800, 1900])
+@pytest.mark.parametrize("resync", [1, 2])
+def test_given_options_stay(tpm, T, resync):
+    """An interval of compactions that is given is not rescaled in a cut run."""
+    systems = W.make_batched(nsys=7, nmin=40, nmax=300, seed=63)
+    _, st = tpm.batch_integrate(systems, nsteps=T, strict=False, resync_chunks=resync, sub_chunks=4)
+    assert st["resync_chunks"] == resync and st["sub_chunks"] == 4
+    cut = 512 < T < 4 * st["chunk_steps"]
+    assert st["chunks"] == (4 if cut else -(-T // st["chunk_steps"]))
+    assert st["compactions"] == (st["chunks"] - 1) // resync
