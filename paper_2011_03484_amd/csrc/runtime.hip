@@ -117,6 +117,8 @@ int64_t handoff_ring_bytes() {
   }
   return HANDOFF_RING_BYTES;
 }
+// Rows of a ring slot that holds `rows`: whole row groups (ROW_GROUP).
+int64_t slot_rows_for(int64_t rows) { return (rows + ROW_GROUP - 1) / ROW_GROUP * ROW_GROUP; }
 constexpr int NCNT = 8;    // in-flight active-count readbacks
 // A simulation's small device block: planet state, flags and counters in the
 // first 512 bytes, conversion scratch (12 MAX_NP doubles) behind them.
@@ -552,7 +554,7 @@ int resume(tpm_sim* s) {
 
 // Planet-table ring of `slots` slots of `rows` rows for the current planets.
 int ensure_ring(tpm_sim* s, int64_t rows, int64_t slots = NSLOT) {
-  rows = (rows + ROW_GROUP - 1) / ROW_GROUP * ROW_GROUP;
+  rows = slot_rows_for(rows);
   const size_t bytes = sizeof(double) * (size_t)slots * rows * (3 * s->np + 3);
   if (s->ring_cap < bytes) {
     TPM_HIP(hipStreamSynchronize(s->sE));
@@ -1009,7 +1011,7 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
     return fail(TPM_EINVAL, "the run's row times leave the planet history");
   if (s->opt.handoff_substeps > 0 && !s->d_table && !s->d_hist) {
     const int64_t K = s->opt.chunk_steps;
-    const int64_t per_slot = (K + 1) * (3 * s->np + 3 + 3 * std::max(s->np, 1)) * 8;
+    const int64_t per_slot = slot_rows_for(K + 1) * (3 * s->np + 3 + 3 * std::max(s->np, 1)) * 8;
     const int64_t max_slots = std::max<int64_t>(2, handoff_ring_bytes() / per_slot);
     const int64_t seg = std::min<int64_t>(K, FIRST_CHUNK_STEPS) + (max_slots - 1) * K;
     if (nsteps > seg) {
