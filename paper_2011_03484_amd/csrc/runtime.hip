@@ -1068,31 +1068,37 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
   // at chunk ends only (resonances with a history), a launch ends at each sample.
   // 25,001 particles sampled every 100 of 2,000 steps: 1.82 ms stored, 2.31 with a
   // launch a sample.
-  const bool stored = D.on && !D.snap && D.emax && (D.nres == 0 || live);
-  const int64_t max_samples =
-      stored && D.every < K
-          ? std::max<int64_t>(1, std::min<int64_t>(K, SAMPLE_BYTES / (48 * std::max<int64_t>(s->n, 1))))
-          : 1;
+  // (also where the memory for it is not to be had.)
+  bool stored = D.on && !D.snap && D.emax && (D.nres == 0 || live);
   auto samples = [&](int64_t b, int64_t e) -> int64_t {      // in steps (b, e] of the call
     return (s->step + e) / D.every - (s->step + b) / D.every;
   };
   // Chunk c covers steps [cb[c], cb[c + 1]) of this call: the first K0 steps
   // long, the others K, each with at most max_samples samples, the last of them
   // at its end if there are that many.
-  std::vector<int64_t> cb{0};
-  int64_t most = 0;
-  while (cb.back() < nsteps) {
-    const int64_t b = cb.back();
-    int64_t e = std::min(nsteps, b + (cb.size() == 1 ? K0 : K));
-    if (D.on) {
-      e = std::min(e, ((s->step + b) / D.every + max_samples) * D.every - s->step);
-      most = std::max(most, samples(b, e));
+  std::vector<int64_t> cb;
+  int64_t most;
+  auto cut = [&]() {
+    const int64_t max_samples =
+        stored && D.every < K
+            ? std::max<int64_t>(1, std::min<int64_t>(K, SAMPLE_BYTES / (48 * std::max<int64_t>(s->n, 1))))
+            : 1;
+    cb.assign(1, 0);
+    most = 0;
+    while (cb.back() < nsteps) {
+      const int64_t b = cb.back();
+      int64_t e = std::min(nsteps, b + (cb.size() == 1 ? K0 : K));
+      if (D.on) {
+        e = std::min(e, ((s->step + b) / D.every + max_samples) * D.every - s->step);
+        most = std::max(most, samples(b, e));
+      }
+      cb.push_back(e);
     }
-    cb.push_back(e);
-  }
+  };
+  cut();
   auto begin = [&](int64_t c) -> int64_t { return cb[c]; };
   auto length = [&](int64_t c) -> int { return (int)(cb[c + 1] - cb[c]); };
-  const int64_t nchunks = (int64_t)cb.size() - 1;
+  int64_t nchunks = (int64_t)cb.size() - 1;
   // With the hand-off the ring keeps every chunk of the call (slot c for chunk
   // c), so that the encounter stream may lag behind the particle stream.
   const int64_t ring_slots = ho ? std::max<int64_t>(nchunks, 1) : NSLOT;
@@ -1102,19 +1108,29 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
     if (rc) return rc;
   }
   if (stored) {
-    const size_t bytes = (size_t)48 * s->n * std::max<int64_t>(most, 1);
-    if (s->samp_cap < bytes) {
-      TPM_HIP(hipStreamSynchronize(s->sP));
-      s->release_samples();
-      TPM_HIP(hipMalloc(&s->d_samp, bytes));
-      s->samp_cap = bytes;
-    }
-    if (D.nres > 0) {
-      int rc = ensure_vring(s, s->ring_rows, ring_slots, [&]() -> int {
+    auto room = [&]() -> int {
+      const size_t bytes = (size_t)48 * s->n * std::max<int64_t>(most, 1);
+      if (s->samp_cap < bytes) {
+        TPM_HIP(hipStreamSynchronize(s->sP));
+        s->release_samples();
+        TPM_HIP(hipMalloc(&s->d_samp, bytes));
+        s->samp_cap = bytes;
+      }
+      if (D.nres == 0) return TPM_OK;
+      return ensure_vring(s, s->ring_rows, ring_slots, [&]() -> int {
         TPM_HIP(hipStreamSynchronize(s->sP));
         return TPM_OK;
       });
-      if (rc) return rc;
+    };
+    const int rc = room();
+    if (rc == TPM_ENOMEM) {               // a launch ends at each sample instead
+      (void)hipGetLastError();
+      s->release_samples();
+      stored = false;
+      cut();
+      nchunks = (int64_t)cb.size() - 1;
+    } else if (rc) {
+      return rc;
     }
   }
   hipStream_t sH = nullptr;
