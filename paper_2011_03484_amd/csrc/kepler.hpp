@@ -158,30 +158,6 @@ TPM_DEV double planet_newton(double ec, double es, double om, double dM, bool id
   return xk;
 }
 
-// The planet map's branch-free step (see the fast blocks of the planet map):
-// exactly two Newton steps in the short sin/cos range, the same arithmetic as
-// planet_newton<true> takes when it leaves after its second step.  `conv` is
-// what that exit requires of the lane (idle, or a second correction of at
-// most 2^-30 |x|); where it is false on any lane, planet_newton would have
-// gone on and the caller redoes the step on the general path.
-TPM_DEV double planet_newton2(double ec, double es, double om, double dM, bool idle, double xk,
-                              double& s, double& m, bool& conv) {
-#pragma unroll
-  for (int it = 0; it < 2; ++it) {
-    double sv, mv;
-    sincos_it<true>(xk, sv, mv);
-    const double F = fma_(-ec, sv, fma_(-es, mv, xk - dM));
-    const double Fp = fma_(-ec, mv, fma_(es, sv, om));
-    const double xn = fma_(-F, rcp_newton(Fp), xk);
-    const double d = xk - xn;
-    conv = idle | (__builtin_fabs(d) <= 0x1p-30 * __builtin_fabs(xn));
-    s = fma_(-(1.0 + mv), d, sv);
-    m = fma_(sv, d, mv);
-    xk = xn;
-  }
-  return xk;
-}
-
 // Starter of the particles' Newton solve: with p = 1 - ec and t = dM/p, the
 // series root of F = 0 through third order in t,
 //   x0 = t - (es/(2p)) t^2 + (es^2/(2p^2) - ec/(6p)) t^3
@@ -442,14 +418,8 @@ TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ft
 // stand-in bound orbit (alpha = 1): dM = 0, x = 0, f = gdot = 1 and
 // g = fdot = 0 exactly, so its state is left as it was without any select on
 // the result.
-// FAST: no wave-uniform branch; two Newton steps in the short sin/cos range
-// (planet_newton2).  `bad` is set on a lane where the general form would have
-// taken another path (the short range not allowed, or more Newton steps); the
-// results are the general form's bit for bit where no lane of the wavefront
-// is bad.  The general form leaves `bad` false.
-template <bool FAST>
 TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, double v2, double u,
-                       double& f, double& g, double& fd, double& gd, bool& bad) {
+                       double& f, double& g, double& fd, double& gd) {
   double r0, rinv;
   sqrt_rsqrt(lane_on ? r2 : 1.0, r0, rinv);
   double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
@@ -478,17 +448,10 @@ TPM_DEV bool planet_fg(const KepConst& K, double dt, bool lane_on, double r2, do
   double w = 2.0 * (__builtin_fabs(ec) + __builtin_fabs(es));
   xk = __builtin_fmin(__builtin_fmax(xk, dM - w), dM + w);
   double s, m;
-  if (FAST) {
-    bool conv;
-    xk = planet_newton2(ec, es, om, dM, idle, xk, s, m, conv);
-    bad = !(idle | short_args(dM, w)) | !conv;
-  } else {
-    bad = false;
-    if (wave_all(idle | short_args(dM, w)))
-      xk = planet_newton<true>(ec, es, om, dM, idle, xk, s, m);
-    else
-      xk = planet_newton<false>(ec, es, om, dM, idle, xk, s, m);
-  }
+  if (wave_all(idle | short_args(dM, w)))
+    xk = planet_newton<true>(ec, es, om, dM, idle, xk, s, m);
+  else
+    xk = planet_newton<false>(ec, es, om, dM, idle, xk, s, m);
   double Fp = fma_(-ec, m, fma_(es, s, om));
   double r1 = a * Fp;
   double r1inv = rcp(r1);
@@ -563,20 +526,32 @@ TPM_DEV bool planet_quick(const KepConst& K, double dt, double r2, double v2, do
          ((eb * y) * (d2 * d2) <= 0x1p-54 * __builtin_fabs(x));
 }
 
-// The converged drift of a planet held as three components on one lane.
+// The drift of a planet held as three components on one lane (nb: 0 there, 1 on a
+// lane without a body, whose state is zero and whose dt is 0: it stays).  FAST:
+// `bad` is set on a lane that planet_quick does not serve; else such a lane
+// takes planet_fg.  Returns false on a body found unbound.
 template <bool FAST>
-TPM_DEV bool drift_converged_t(const KepConst& K, double dt, bool lane_on,
-                               double& x, double& y, double& z,
-                               double& vx, double& vy, double& vz, bool& bad) {
-  double r2 = fma_(x, x, fma_(y, y, z * z));
-  double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
-  double u = fma_(x, vx, fma_(y, vy, z * vz));
+TPM_DEV bool planet_drift(const KepConst& K, double dt, bool lane_on, double nb, double& x,
+                          double& y, double& z, double& vx, double& vy, double& vz, bool& bad) {
+  const double r2 = fma_(x, x, fma_(y, y, fma_(z, z, nb)));
+  const double v2 = fma_(vx, vx, fma_(vy, vy, fma_(vz, vz, nb)));
+  const double u = fma_(x, vx, fma_(y, vy, z * vz));
   double f, g, fd, gd;
-  const bool bound = planet_fg<FAST>(K, dt, lane_on, r2, v2, u, f, g, fd, gd, bad);
-  double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
-  double nvx = fma_(fd, x, gd * vx), nvy = fma_(fd, y, gd * vy), nvz = fma_(fd, z, gd * vz);
+  const bool served = planet_quick(K, dt, r2, v2, u, f, g, fd, gd) | !lane_on;
+  bool bound = true;
+  bad = FAST & !served;
+  if (!FAST && !wave_all(served)) {
+    double f1, g1, fd1, gd1;
+    const bool b = planet_fg(K, dt, lane_on, r2, v2, u, f1, g1, fd1, gd1);
+    bound = served | b;
+    f = served ? f : f1;
+    g = served ? g : g1;
+    fd = served ? fd : fd1;
+    gd = served ? gd : gd1;
+  }
+  const double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
+  vx = fma_(fd, x, gd * vx); vy = fma_(fd, y, gd * vy); vz = fma_(fd, z, gd * vz);
   x = nx; y = ny; z = nz;
-  vx = nvx; vy = nvy; vz = nvz;
   return bound;
 }
 

@@ -651,7 +651,7 @@ hipError_t launch_particle_chunk(const SysConst& S, Work w, const int32_t* d_nac
 // latency: one wavefront, lane b (1..NP) holds Jacobi body b, lane 0 the
 // central body.  Values every lane needs are broadcast with v_readlane into
 // scalar registers (no LDS round trip), and everything per step is branch-free
-// except the wave-uniform Newton loop of the planets' Kepler drifts.
+// except the general form of the planets' Kepler drifts.
 
 // Value of v on lane `src` (a compile-time constant), returned wave-uniform
 // in an SGPR pair.
@@ -728,6 +728,7 @@ struct EphLane {
   double cw;                      // weight of the central term in the lane's own kick
   double nb;                      // 0 on body lanes, 1 elsewhere (keeps an rsqrt finite)
   double c15;                     // 1.5 (held in a VGPR by the single-system map)
+  double dt;                      // the step, 0 on lanes that hold no body
   KepConst K;                     // Kepler constant mu'_b for the drift
 };
 
@@ -908,9 +909,9 @@ TPM_DEV bool eph_step(const EphConst& E, const EphLane& L, const EphW<NP>& W, do
   double ox, oy, oz;
   wx = fma_(h, ax, wx); wy = fma_(h, ay, wy); wz = fma_(h, az, wz);
   bool bad;
-  const bool bound = drift_converged_t<FAST>(L.K, dt, L.body, jx, jy, jz, wx, wy, wz, bad);
-  if (FAST) bad = bad | (events & L.body & !bound);
-  else first_ev = __builtin_elementwise_min(first_ev, (L.body && !bound) ? key1 : UINT32_MAX);
+  const bool bound =
+      planet_drift<FAST>(L.K, L.dt, L.body, L.nb, jx, jy, jz, wx, wy, wz, bad);
+  if (!FAST) first_ev = __builtin_elementwise_min(first_ev, (L.body && !bound) ? key1 : UINT32_MAX);
   helio_step<NP, ROWB>(E, W, jx, jy, jz, hx, hy, hz, ox, oy, oz);
   eph_accel<NP, ROWB>(E, L, W, jx, jy, jz, hx, hy, hz, ox, oy, oz, ax, ay, az);
   wx = fma_(h, ax, wx); wy = fma_(h, ay, wy); wz = fma_(h, az, wz);
@@ -958,6 +959,7 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
   L.lane = threadIdx.x & 63;
   L.body = L.lane >= 1 && L.lane <= NP;
   L.mup = 1.0; L.ie_prev = 0.0; L.nb = L.body ? 0.0 : 1.0;
+  L.dt = L.body ? dt : 0.0;
 #pragma unroll
   for (int b = 1; b <= NP; ++b)
     if (L.lane == b) { L.mup = E.mup[b]; L.ie_prev = E.inv_eta[b - 1]; }
@@ -975,14 +977,26 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
     L.K = KepConst{L.mup, rcp(L.mup), smu, rsmu};
   }
   double jx = 0, jy = 0, jz = 0, wx = 0, wy = 0, wz = 0;
-  if (L.body) {
-    jx = rj[3 * (L.lane - 1) + 0]; jy = rj[3 * (L.lane - 1) + 1]; jz = rj[3 * (L.lane - 1) + 2];
-    wx = vj[3 * (L.lane - 1) + 0]; wy = vj[3 * (L.lane - 1) + 1]; wz = vj[3 * (L.lane - 1) + 2];
-  }
   double hx[NP + 1], hy[NP + 1], hz[NP + 1];
   double ox, oy, oz, ax, ay, az;
-  helio_step<NP, ROWB>(E, W, jx, jy, jz, hx, hy, hz, ox, oy, oz);
-  eph_accel<NP, ROWB>(E, L, W, jx, jy, jz, hx, hy, hz, ox, oy, oz, ax, ay, az);
+  // the state from and to memory, and the acceleration at it (the same bits as
+  // the one carried on)
+  auto get_state = [&]() {
+    jx = jy = jz = wx = wy = wz = 0.0;
+    if (L.body) {
+      jx = rj[3 * (L.lane - 1) + 0]; jy = rj[3 * (L.lane - 1) + 1]; jz = rj[3 * (L.lane - 1) + 2];
+      wx = vj[3 * (L.lane - 1) + 0]; wy = vj[3 * (L.lane - 1) + 1]; wz = vj[3 * (L.lane - 1) + 2];
+    }
+    helio_step<NP, ROWB>(E, W, jx, jy, jz, hx, hy, hz, ox, oy, oz);
+    eph_accel<NP, ROWB>(E, L, W, jx, jy, jz, hx, hy, hz, ox, oy, oz, ax, ay, az);
+  };
+  auto put_state = [&]() {
+    if (L.body) {
+      rj[3 * (L.lane - 1) + 0] = jx; rj[3 * (L.lane - 1) + 1] = jy; rj[3 * (L.lane - 1) + 2] = jz;
+      vj[3 * (L.lane - 1) + 0] = wx; vj[3 * (L.lane - 1) + 1] = wy; vj[3 * (L.lane - 1) + 2] = wz;
+    }
+  };
+  get_state();
   // Row entries: lane b writes planet b's heliocentric position, lane 0 (the
   // central body, whose own position is the origin) writes h0 = -a_0, both as
   // fma(rsign, a, o) with rsign = 0 on body lanes and -1 on lane 0.
@@ -1006,17 +1020,21 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
   if (vside && !resumed)
     write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside);
   if (VEL && !resumed) write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vrows);
-  // Blocks of steps.  Giant planets on near-circular orbits take
-  // the general drift's short sin/cos path and leave its Newton loop after
-  // two steps every time, and meet no event; the fast form runs exactly that,
-  // with none of the general form's wave-uniform branches, and only notes on
-  // each lane whether the general form would have done otherwise.  A block in
-  // which any lane did is restored from its start and run again in the
-  // general form, as is the rest of the launch.  Either way the rows and the
-  // state are the general form's bit for bit.  Once the run's first event is
-  // on record (*flag != -1) later events cannot change it and no longer stop
-  // the fast form.  (The many-system map keeps the general form: its
-  // wavefronts share SIMDs with the particles, which hide its branches.)
+  // Blocks of steps.  Planets on near-circular orbits are served by planet_quick
+  // every time and meet no event; the fast form runs exactly that, with none of
+  // the general form's wave-uniform branches, and only notes on each lane
+  // whether the general form would have done otherwise.  A block in which any
+  // lane did is restored from its start and run again in the general form, as is
+  // the rest of the launch.  Either way the rows and the state are the general
+  // form's bit for bit.  Once the run's first event is on record (*flag != -1) a
+  // close pair cannot change it and no longer stops the fast form.  (The
+  // many-system map keeps the general form: its wavefronts share SIMDs with the
+  // particles, which hide its branches.)
+  // A block's start is kept in memory: in registers it took eighteen more
+  // through the fast loop, which with eight planets then no longer fits the 256
+  // of a particle launch's wavefront (nine reloads a step: 1.83 us a step where
+  // the map as a kernel of its own took 1.35).  So and with planet_quick 0.95, 1.06,
+  // 1.11 and 1.26 us a step at five to eight planets (1.03, 1.13, 1.32, 1.83 before).
   const bool events = *flag == -1;
   bool fast = !ROWB;
   int done = 0;
@@ -1025,8 +1043,7 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
     const int nb = ROWB ? nsteps : block_end.block(s0, nsteps - s0);
     done = s0 + nb;
     if (!ROWB && fast) {
-      const double sjx = jx, sjy = jy, sjz = jz, swx = wx, swy = wy, swz = wz;
-      const double sax = ax, say = ay, saz = az;
+      put_state();
       bool bad = false;
       for (int t = 0; t < nb; ++t) {
         const int s = s0 + t;
@@ -1040,8 +1057,7 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
         if (!block_end(done)) break;
         continue;
       }
-      jx = sjx; jy = sjy; jz = sjz; wx = swx; wy = swy; wz = swz;
-      ax = sax; ay = say; az = saz;
+      get_state();
       fast = false;
     }
     for (int t = 0; t < nb; ++t) {
@@ -1055,10 +1071,7 @@ TPM_DEV int ephemeris_body(const EphConst& E, double* __restrict__ rj, double* _
   }
   if (vside && done == nsteps)
     write_helio_velocities<NP, ROWB>(E, W, L.body, L.lane, wx, wy, wz, vside + 3 * NP);
-  if (L.body) {
-    rj[3 * (L.lane - 1) + 0] = jx; rj[3 * (L.lane - 1) + 1] = jy; rj[3 * (L.lane - 1) + 2] = jz;
-    vj[3 * (L.lane - 1) + 0] = wx; vj[3 * (L.lane - 1) + 1] = wy; vj[3 * (L.lane - 1) + 2] = wz;
-  }
+  put_state();
   // earliest event over the wavefront: unbound -> -2, a close pair -> its step
   uint32_t ev = first_ev;
 #pragma unroll
@@ -1189,19 +1202,20 @@ TPM_DEV int planet_map(EP E, double* rj, double* vj, double* rows, int nsteps, d
 }
 
 // The row stream's blocks: what the particles of the same launch follow the
-// map by, so they are short, a quarter of the steps to go but at least 8 and at
-// most 32 (publishing a block cost the map nothing that showed: the same time
-// per step with blocks of 32 as with blocks of 128).  After each the count of
-// published steps goes up; a map that runs ahead of its launch's chunk stops
-// once no other wavefront of the launch is at work.
+// map by.  They end where rows fill cache lines (see wait_rows), at counts one
+// short of a multiple of ROW_GROUP: 15 steps, then 16 or 32, about a quarter of
+// those to go.  A block's end costs the map about a microsecond (1.16 us a step at
+// six planets, 1.15 with blocks of up to 64), but particles about as fast as the map
+// wait once for the steps by which a block is longer than the one before: with
+// blocks of up to 64, 500 steps of one planet took 446 us for 434.  After each the
+// count of published steps goes up; a map that runs ahead of its launch's chunk
+// stops once no other wavefront of the launch is at work.
 struct EphPublish {
   const RowStream& R;
   int64_t done;                              // the count when the body started
   bool ahead;
   int first;                                 // the chunk's step the body started from
-  // Steps of the block after `s` of the body's: to a count c of the chunk's steps
-  // whose rows 0..c fill cache lines (see wait_rows), or the chunk's end.  About
-  // a quarter of what is left, at most 32, so that the last wait is short.
+  // Steps of the block after `s` of the body's.
   TPM_DEV int block(int s, int left) const {
     const int c = first + s;
     const int want = c == 0 ? ROW_GROUP : max(ROW_GROUP, min(2 * ROW_GROUP, left >> 2));

@@ -168,7 +168,7 @@ TPM_DEV bool quad_drift(const EphQuad& Q, double& j, double& w, bool& bad) {
   bad = FAST & !served;
   if (!FAST && !wave_all(served)) {
     double f1, g1, fd1, gd1;
-    const bool b = planet_fg<false>(Q.K, Q.dt, Q.on, r2, v2, u, f1, g1, fd1, gd1, bad);
+    const bool b = planet_fg(Q.K, Q.dt, Q.on, r2, v2, u, f1, g1, fd1, gd1);
     bound = served | b;
     f = served ? f : f1;
     g = served ? g : g1;
