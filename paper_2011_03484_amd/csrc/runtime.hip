@@ -71,6 +71,10 @@ struct DeviceStreams {
   struct ::tpm_sim* batch = nullptr;
   char* arena = nullptr;
   size_t arena_cap = 0;
+  // pinned staging (STAGE_BYTES) for results that are smaller than the cost of
+  // copying them one by one: one for the device's simulations, used under the
+  // lock, made on first use
+  char* stage = nullptr;
 };
 constexpr size_t ARENA_KEEP = size_t(256) << 20;
 
@@ -123,10 +127,9 @@ constexpr int NCNT = 8;    // in-flight active-count readbacks
 // A simulation's small device block: planet state, flags and counters in the
 // first 512 bytes, conversion scratch (12 MAX_NP doubles) behind them.
 constexpr size_t BASE_BYTES = 512 + sizeof(double) * 12 * MAX_NP;
-// Its pinned block: counts, the report of a call's end, and staging for results
-// that are smaller than the cost of copying them one by one.
-constexpr size_t STAGE_BYTES = size_t(1) << 20;
-constexpr size_t PIN_BYTES = 256 + STAGE_BYTES;
+// Its pinned block: counts and the report of a call's end.
+constexpr size_t PIN_BYTES = 256;
+constexpr size_t STAGE_BYTES = size_t(1) << 20;   // see DeviceStreams
 
 template <class T>
 void dfree(T*& p) {
@@ -247,7 +250,6 @@ struct tpm_sim {
   Out out{};
   int32_t* h_pin = nullptr;             // [0..NCNT) active counts, [16..] scratch
   RunReport* h_rep = nullptr;           // pinned: what the device reports at a call's end
-  char* h_stage = nullptr;              // pinned: small results on their way to the caller
   hipEvent_t ev_cnt[NCNT]{};             // one per in-flight count readback
   int64_t cnt_issued = 0, cnt_seen = 0;  // readbacks issued / consumed
   unsigned long long* d_acc = nullptr;
@@ -783,7 +785,6 @@ int new_sim(const tpm_options& o, bool auto_sub, const hipDeviceProp_t& prop, tp
     return TPM_EDEVICE;
   }
   s->h_rep = (RunReport*)((char*)s->h_pin + 128);
-  s->h_stage = (char*)s->h_pin + 256;
   s->d_rj = (double*)s->d_base;
   s->d_vj = s->d_rj + 3 * MAX_NP;
   s->d_flag = (int64_t*)(s->d_vj + 3 * MAX_NP);
@@ -1485,9 +1486,10 @@ int tpm_get_particles(tpm_sim* s, double* r, double* v, int64_t* deact_step, int
   TPM_HIP(launch_finalize(s->work[s->cur], s->d_nactive, s->n_active, s->out, s->sP));
   if ((size_t)n * 64 <= STAGE_BYTES) {
     // all of it in one copy (the results lie together), then to the caller
-    TPM_HIP(hipMemcpyAsync(s->h_stage, s->out.r, n * 64, hipMemcpyDeviceToHost, s->sP));
+    char*& h = device_streams(s->opt.device).stage;
+    if (!h) TPM_HIP(hipHostMalloc(&h, STAGE_BYTES, hipHostMallocDefault));
+    TPM_HIP(hipMemcpyAsync(h, s->out.r, n * 64, hipMemcpyDeviceToHost, s->sP));
     TPM_HIP(hipStreamSynchronize(s->sP));
-    const char* h = s->h_stage;
     if (r) std::memcpy(r, h, n * 24);
     if (v) std::memcpy(v, h + n * 24, n * 24);
     if (deact_step) std::memcpy(deact_step, h + n * 48, n * 8);
