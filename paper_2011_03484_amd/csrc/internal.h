@@ -187,12 +187,9 @@ hipError_t launch_particle_chunk(const SysConst& S, Work w, const int32_t* d_nac
 // approach (or -2 for an unbound planet) if it is still -1.  vside (may be
 // null) receives the heliocentric planet velocities at rows 0 and nsteps,
 // [2][np][3].
-// vrows (may be null) receives the heliocentric planet velocities of every
-// row, [nsteps+1][np][3] (for the encounter integrator's interpolation).
 hipError_t launch_ephemeris_chunk(const EphConst& E, double* rj, double* vj, double* rows,
                                   int nsteps, double dt, int64_t step0, int64_t* flag,
-                                  hipStream_t st, double* vside = nullptr,
-                                  double* vrows = nullptr);
+                                  hipStream_t st, double* vside = nullptr);
 
 // ---- close-encounter hand-off
 // Move the working set's handed-off entries (status >= HANDOFF_BASE, set by

@@ -1281,15 +1281,15 @@ TPM_DEV void run_planet_rows(KargPtr ka) {
   else planet_rows<NP, false>(p);
 }
 
-template <int NP, bool VEL>
+template <int NP>
 __global__ void __launch_bounds__(64) TPM_PLANET_KERNEL
 ephemeris_chunk(EphConst E, double* __restrict__ rj, double* __restrict__ vj,
                 double* __restrict__ rows, int nsteps, double dt, int64_t step0,
-                int64_t* __restrict__ flag, double* __restrict__ vside, double* __restrict__ vrows) {
+                int64_t* __restrict__ flag, double* __restrict__ vside) {
   (void)E;                           // the first argument, read from the argument segment
-  planet_map<NP, false, VEL>(
+  planet_map<NP, false, false>(
       karg_pointer<EphConst>((KargPtr)__builtin_amdgcn_kernarg_segment_ptr(), 0), rj, vj, rows,
-      nsteps, dt, step0, flag, vside, vrows);
+      nsteps, dt, step0, flag, vside);
 }
 
 // Many systems at once: workgroup b runs system b (its constants, Jacobi
@@ -1333,24 +1333,19 @@ hipError_t launch_ephemeris_batch(const EphConst* E, double* rj, double* vj, dou
 
 template <int NP>
 static hipError_t eph_np(const EphConst& E, double* rj, double* vj, double* rows, int nsteps,
-                         double dt, int64_t step0, int64_t* flag, double* vside, double* vrows,
-                         hipStream_t st) {
-  if (vrows)
-    hipLaunchKernelGGL((ephemeris_chunk<NP, true>), dim3(1), dim3(64), 0, st, E, rj, vj, rows,
-                       nsteps, dt, step0, flag, vside, vrows);
-  else
-    hipLaunchKernelGGL((ephemeris_chunk<NP, false>), dim3(1), dim3(64), 0, st, E, rj, vj, rows,
-                       nsteps, dt, step0, flag, vside, vrows);
+                         double dt, int64_t step0, int64_t* flag, double* vside, hipStream_t st) {
+  hipLaunchKernelGGL((ephemeris_chunk<NP>), dim3(1), dim3(64), 0, st, E, rj, vj, rows, nsteps, dt,
+                     step0, flag, vside);
   return hipGetLastError();
 }
 
 hipError_t launch_ephemeris_chunk(const EphConst& E, double* rj, double* vj, double* rows,
                                   int nsteps, double dt, int64_t step0, int64_t* flag,
-                                  hipStream_t st, double* vside, double* vrows) {
+                                  hipStream_t st, double* vside) {
   if (nsteps < 0 || nsteps > MAX_EPH_STEPS) return hipErrorInvalidValue;
   switch (E.np) {
 #define TPM_EPH(N) \
-    case N: return eph_np<N>(E, rj, vj, rows, nsteps, dt, step0, flag, vside, vrows, st);
+    case N: return eph_np<N>(E, rj, vj, rows, nsteps, dt, step0, flag, vside, st);
     TPM_EPH(0) TPM_EPH(1) TPM_EPH(2) TPM_EPH(3) TPM_EPH(4) TPM_EPH(5) TPM_EPH(6) TPM_EPH(7)
     TPM_EPH(8)
 #undef TPM_EPH

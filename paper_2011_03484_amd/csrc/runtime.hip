@@ -1314,7 +1314,7 @@ int tpm_integrate(tpm_sim* s, int64_t nsteps, double dt) {
       // sampled before the chunk's launch: its first row is needed now
       if (live)
         TPM_HIP(launch_ephemeris_chunk(E, s->d_rj, s->d_vj, (double*)rows, 0, dt, step0, s->d_flag,
-                                       s->sP, (double*)vel, nullptr));
+                                       s->sP, (double*)vel));
       int rc = sample(step0, rows, vel, n_grid);
       if (rc) return rc;
     }
