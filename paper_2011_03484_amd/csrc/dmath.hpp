@@ -186,19 +186,8 @@ TPM_DEV void sincos_poly_horner(double r, double& s, double& m) {
   m = fma_(z * z, pc, -0.5 * z);
 }
 
-// sin(x), cos(x) and cos(x) - 1 for |x| up to about 2^20.  When every active
-// lane of the wavefront has |x| <= 0.78 (< pi/4, so the quadrant count is 0
-// and the reduction leaves x unchanged) the reduction is skipped; the values
-// are the same (the full path would only turn a -0 input into +0).  The only
-// branch is that wave-uniform one.  cos(x) - 1 comes from the series in the
-// first quadrant; beyond it |cos(x) - 1| >= 1 - cos(pi/4) and the difference
-// loses at most two bits.
-TPM_DEV void sincos3(double x, double& s, double& c, double& m) {
-  if (wave_all(__builtin_fabs(x) <= 0.78)) {
-    sincos_poly(x, s, m);
-    c = 1.0 + m;
-    return;
-  }
+// The path of sincos3 for any argument: reduction by multiples of pi/2.
+TPM_DEV void sincos3_reduced(double x, double& s, double& c, double& m) {
   double q = __builtin_rint(x * TWO_OVER_PI);
   double r = fma_(-q, PIO2_HI, x);
   r = fma_(-q, PIO2_LO, r);
@@ -212,6 +201,22 @@ TPM_DEV void sincos3(double x, double& s, double& c, double& m) {
   s = (iq & 2) ? -ss : ss;
   c = ((iq + 1) & 2) ? -cc : cc;
   m = (iq & 3) == 0 ? pm : c - 1.0;
+}
+
+// sin(x), cos(x) and cos(x) - 1 for |x| up to about 2^20.  When every active
+// lane of the wavefront has |x| <= 0.78 (< pi/4, so the quadrant count is 0
+// and the reduction leaves x unchanged) the reduction is skipped; the values
+// are the same (the full path would only turn a -0 input into +0).  The only
+// branch is that wave-uniform one.  cos(x) - 1 comes from the series in the
+// first quadrant; beyond it |cos(x) - 1| >= 1 - cos(pi/4) and the difference
+// loses at most two bits.
+TPM_DEV void sincos3(double x, double& s, double& c, double& m) {
+  if (wave_all(__builtin_fabs(x) <= 0.78)) {
+    sincos_poly(x, s, m);
+    c = 1.0 + m;
+    return;
+  }
+  sincos3_reduced(x, s, c, m);
 }
 
 // sin(x) and cos(x) - 1 (see sincos3).

@@ -271,9 +271,9 @@ TPM_DEV bool drift_fixed(const KepConst& K, double dt, int kiters, double ftol,
 // A Newton step from x to x - d leaves an error of |F''| d^2 / (2 F'(x)) where d
 // is so small that F' hardly changes, and |F''| <= eb: a lane is `fine` with
 // |d| <= 2^-28 and eb d^2 / F'(x) <= 2^-54 |x - d|, half of which is left at
-// most.  The few that are not after one step take a second one, and a lane
-// still not fine (or out of the ranges, or unbound: NaN) is left to
-// drift_fixed.  All of it is the lane's own decision; the branches only skip
+// most.  The few lanes in the ranges that are not after one step take a second
+// one, and a lane still not fine (or out of the ranges, or unbound: NaN) is left
+// to drift_wide and drift_fixed.  All of it is the lane's own decision; the branches only skip
 // what no lane of act needs.  Lane predicates are kept as lane masks: as
 // booleans the compiler carries them through vector registers.
 // With it a lone wavefront's step of four planets takes about 0.52 us (0.78 with
@@ -334,10 +334,12 @@ TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double 
            lanes(eb * yn * (ad * ad) <= 0x1p-54 * __builtin_fabs(xn));
   };
   uint64_t fine = newton(xk, xk, smx, m, iFp);
-  if (act & ~fine) {
+  if (act & range & ~fine) {
     double xn, sxn, mn, yn;
     const uint64_t f2 = newton(xk, xn, sxn, mn, yn);
-    const bool mine = lane_in(fine);
+    // (lanes out of the ranges keep their first iterate, whoever shares the
+    // wavefront: drift_wide goes on from it)
+    const bool mine = lane_in(fine | ~range);
     xk = mine ? xk : xn;
     smx = mine ? smx : sxn;
     m = mine ? m : mn;
@@ -359,13 +361,90 @@ TPM_DEV uint64_t drift_quick(const KepConst& K, double dt, uint64_t act, double 
   return fine;
 }
 
-// The particles' drift of the lanes of act: drift_quick where `quick` is set and
-// it serves; with `univ` (a refused drift is then taken in universal variables,
-// so whether the fixed-count solve refuses does not matter)
-// drift_universal_quick where that serves; drift_fixed elsewhere, and with univ
-// drift_universal where it refuses.  Returns the lanes of act whose drift is
-// refused in the end (their state, and that of lanes outside act, means
-// nothing).
+// The wide drift: a converged solve where drift_quick does not serve but the
+// fixed-count solve cannot refuse either, t^2 <= (1 - e^2) max(1, 4 (1 - e^2)) with
+// t = dM/(1 - ec) as in drift_quick (arcs up to two radians on circular orbits, half a
+// radian at e = 0.87, 0.14 at e = 0.99).  There F after five Newton steps from the
+// third-order starter is at rounding, below 7e-16 over twenty million draws up to
+// the edge (the first refusals come with t 1.2 times larger, at e = 0.94), so
+// thresholds from QUICK_FTOL up need no evaluation, and |dM| < 2.4 has no whole
+// period.  drift_quick has left an iterate xk (its start and one Newton step); full-range
+// Newton steps go on from there, with drift_quick's stopping rule: one to three at
+// moderate arcs, where the fixed-count solve takes three to five and its
+// bookkeeping; four at the most, and a lane that has not stopped by then is left to
+// that solve.  The elements are drift_fixed's, to rounding (at these arcs the
+// shortcuts of drift_quick would show), f, g, fdot and gdot drift_quick's forms.
+// `low`: the lanes of small eccentricity (e^2 <= 0.28).
+// Without it every lane out of drift_quick's ranges costs its wavefront that
+// attempt and the fixed-count solve: 2,000 steps of 64 particles at 15 steps an
+// orbit, planets from a table, 2.46 ms (1.94 with the fixed-count solve alone), with
+// it 1.77; of 100,000 particles at e = 0.6 to 0.9, 60 steps an orbit, 4.9 (4.5) and 3.8.
+TPM_DEV uint64_t drift_wide(const KepConst& K, double dt, uint64_t act, double r2, double& x,
+                            double& y, double& z, double& vx, double& vy, double& vz, double& xk,
+                            double& s, double& m, uint64_t& low) {
+  const double v2 = fma_(vx, vx, fma_(vy, vy, vz * vz));
+  const double u = fma_(x, vx, fma_(y, vy, z * vz));
+  double r0, rinv, sa, rsa;
+  sqrt_rsqrt(r2, r0, rinv);
+  const double alpha = fma_(-v2, K.inv_mu, 2.0 * rinv);
+  sqrt_rsqrt(alpha, sa, rsa);             // NaN for unbound lanes: not served
+  double a = rsa * rsa;
+  a = fma_(a, fma_(-alpha, a, 1.0), a);
+  const double ms = K.sqrt_mu * sa;       // n a
+  const double dM = ms * alpha * dt;
+  const double ninv = K.inv_sqrt_mu * rsa * a;
+  const double ec = fma_(-r0, alpha, 1.0);
+  const double es = u * sa * K.inv_sqrt_mu;
+  const double eb = __builtin_fabs(ec) + __builtin_fabs(es);
+  const double om = 1.0 - ec;
+  const double ar = a * rinv;             // 1/om
+  const double t = dM * ar;
+  const double q = fma_(-es, es, fma_(-ec, ec, 1.0));   // 1 - e^2
+  low = lanes(q >= 0.72);
+  const uint64_t wide = act & lanes(t * t <= q * __builtin_fmax(1.0, 4.0 * q));
+  if (wide == 0) return 0;
+  uint64_t todo = wide;
+  double iFp = 0.0;
+  for (int it = 0; it < 4 && todo != 0; ++it) {
+    double sv, cv, mv;
+    if (todo & ~lanes(__builtin_fabs(xk) <= 0.78)) sincos3_reduced(xk, sv, cv, mv);
+    else sincos_poly(xk, sv, mv);
+    const double F = fma_(-ec, sv, fma_(-es, mv, xk - dM));
+    const double yn = rcp_newton(fma_(-ec, mv, fma_(es, sv, om)));
+    const double xn = fma_(-F, yn, xk);
+    const double d = xk - xn;
+    const double ad = __builtin_fabs(d);
+    const bool go = lane_in(todo);
+    xk = go ? xn : xk;
+    s = go ? fma_(-(1.0 + mv), d, sv) : s;
+    m = go ? fma_(sv, d, mv) : m;
+    iFp = go ? yn : iFp;
+    todo &= ~(lanes(ad <= 0x1p-28) &
+              lanes(eb * yn * (ad * ad) <= 0x1p-54 * __builtin_fabs(xn)));
+  }
+  {
+    const double e = fma_(-fma_(-ec, m, fma_(es, s, om)), iFp, 1.0);
+    iFp = fma_(iFp, fma_(e, e, e), iFp);
+  }
+  const double f = fma_(ar, m, 1.0);
+  const double g = fma_(s - xk, ninv, dt);
+  const double fd = -((ms * rinv) * (s * iFp));
+  const double gd = fma_(iFp, m, 1.0);
+  const double nx = fma_(f, x, g * vx), ny = fma_(f, y, g * vy), nz = fma_(f, z, g * vz);
+  vx = fma_(fd, x, gd * vx); vy = fma_(fd, y, gd * vy); vz = fma_(fd, z, gd * vz);
+  x = nx; y = ny; z = nz;
+  return wide & ~todo;
+}
+
+// The particles' drift of the lanes of act: where `quick` is set, drift_quick where
+// it serves, then drift_wide where that does, and with `univ` (a refused drift is
+// then taken in universal variables, so whether the fixed-count solve refuses does
+// not matter) drift_universal_quick where that serves, but for orbits of small
+// eccentricity, which are left by their arcs alone (long ones, that it does not
+// reach: at six steps an orbit its attempt took half the time of a step);
+// drift_fixed elsewhere, and with univ drift_universal where it refuses.  Returns
+// the lanes of act whose drift is refused in the end (their state, and that of
+// lanes outside act, means nothing).
 __host__ TPM_DEV bool quick_serves(int kiters, double ftol) {
   return kiters == 5 && ftol >= QUICK_FTOL;
 }
@@ -378,15 +457,32 @@ TPM_DEV uint64_t drift_lanes(const KepConst& K, double dt, int kiters, double ft
   uint64_t rest = act;
   if (quick) rest = act & ~drift_quick(K, dt, act, r2, x, y, z, vx, vy, vz, xk, s, m);
   if (rest == 0) return 0;
-  if (quick && univ) {
+  if (quick) {
+    // (behind drift_quick rather than in it: values that may come from either, carried
+    // through one common end, made its own lanes' step 20% longer)
+    uint64_t low;
     double px = ox, py = oy, pz = oz, qx = ux, qy = uy, qz = uz;
-    const uint64_t served = drift_universal_quick(K, dt, rest, px, py, pz, qx, qy, qz);
-    if (lane_in(served)) {
+    double wk = xk, ws = 0.0, wm = 0.0;
+    const uint64_t wide = drift_wide(K, dt, rest, r2, px, py, pz, qx, qy, qz, wk, ws, wm, low);
+    if (lane_in(wide)) {
       x = px; y = py; z = pz;
       vx = qx; vy = qy; vz = qz;
+      xk = wk; s = ws; m = wm;
     }
-    rest &= ~served;
+    rest &= ~wide;
     if (rest == 0) return 0;
+    if (univ && (rest & ~low)) {
+      px = ox; py = oy; pz = oz;
+      qx = ux; qy = uy; qz = uz;
+      const uint64_t served =
+          drift_universal_quick(K, dt, rest & ~low, px, py, pz, qx, qy, qz);
+      if (lane_in(served)) {
+        x = px; y = py; z = pz;
+        vx = qx; vy = qy; vz = qz;
+      }
+      rest &= ~served;
+      if (rest == 0) return 0;
+    }
   }
   bool ok = true;
   if (lane_in(rest)) {
