@@ -178,8 +178,9 @@ def summarize_counters(pmc_dir: str) -> None:
     busy = g("p2", "SQ_ACTIVE_INST_VALU") / (1024 * kt * 2.4e9 / 4)
     out += ["", f"Derived (particle kernel; kernel-trace time of pass 2 = {kt * 1e3:.1f} ms for "
                 f"{kn} launches; {aps:,} active particle-steps):", "",
-            f"* VALU instructions per wavefront-step: {g('p1', 'SQ_INSTS_VALU'):.4g} / ({waves:.0f} "
-            f"waves x {steps:,} steps) = {g('p1', 'SQ_INSTS_VALU') / (waves * steps):.0f}.",
+            f"* VALU instructions per step of a tile of 64 particles: 64 x {g('p1', 'SQ_INSTS_VALU'):.4g} / "
+            f"{aps:.4g} active particle-steps = {per('SQ_INSTS_VALU'):.0f} (tiles that have lost "
+            f"particles count for less than one here; {waves:.0f} wavefronts share the tiles).",
             f"* Executed FP64 per active particle-step (64 x instructions / particle-steps): "
             f"{per('SQ_INSTS_VALU_FMA_F64'):.1f} FMA, {per('SQ_INSTS_VALU_MUL_F64'):.1f} mul, "
             f"{per('SQ_INSTS_VALU_ADD_F64'):.1f} add, {per('SQ_INSTS_VALU_TRANS_F64'):.1f} "
@@ -254,6 +255,8 @@ def summarize_resonant_counters(pmc_dir: str) -> None:
     for c, v in tot.items():
         out.append(f"| {c} | {v:.6g} |")
     out += ["", f"Derived ({aps:,} active particle-steps; kernel-trace time {kt * 1e3:.1f} ms):", "",
+            f"* VALU instructions per step of a tile of 64 particles: 64 x {tot['SQ_INSTS_VALU']:.4g} / "
+            f"{aps:.4g} active particle-steps = {per('SQ_INSTS_VALU'):.0f}.",
             f"* Executed FP64 per active particle-step (64 x instructions / particle-steps): "
             f"{per('SQ_INSTS_VALU_FMA_F64'):.1f} FMA, {per('SQ_INSTS_VALU_MUL_F64'):.1f} mul, "
             f"{per('SQ_INSTS_VALU_ADD_F64'):.1f} add, {per('SQ_INSTS_VALU_TRANS_F64'):.1f} "
