@@ -28,8 +28,9 @@
 // pair i < j with mu_j in a'_i, -mu_i - mu_i mu_j/eta_{j-1} in a'_j and
 // -mu_i mu_j/eta_{b-1} between them.
 //
-// Bound by the instructions of the one wavefront (about 165 vector ones a step
-// against 366, at some 5.5 cycles each; three products of 20 cycles).  Four
+// Bound by the instructions of the one wavefront (by the counters 209 vector ones a
+// step, its three products of 20 cycles among them, against 405 of the other form when
+// it held four planets; 5 to 6 cycles each).  Four
 // giant planets: 0.49 us a step, 0.887 in the other form (0.56 with planet_fg's
 // two Newton steps for the drift); the error against extended precision over 240
 // starts is that of the other form (2.27e-13 rms after 1,000 steps against
